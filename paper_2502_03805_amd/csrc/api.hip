@@ -79,6 +79,12 @@ Workspace carve_workspace(const Dims &d, int dtype, int max_budget)
     // last, so that the offsets above do not depend on max_budget
     w.alloc_tmp = off; off = align256(off + ((size_t)2 * d.batch + (size_t)d.batch * d.Hkv * (max_budget > 0 ? max_budget : 0)) * 4);
     w.total = off;
+    // fp32 layers: scratch of one score call, over the allocation's list (never live in the same call).  A workspace that
+    // ends at `total` is still accepted by every call; the score then takes the vector kernel.
+    w.w_split = w.alloc_tmp;
+    w.total_split = w.total;
+    if (dtype == CKV_F32 && vproj_split_supported(d))
+        w.total_split = std::max(w.total, align256(w.w_split + vproj_split_bytes(d)));
     return w;
 }
 
@@ -128,7 +134,7 @@ size_t criticalkv_workspace_bytes(const ckv_layer_desc *desc, int32_t max_budget
     if (resolve(desc, &d) != CKV_OK || max_budget < 0) return 0;
     // sized for either w_o layout and either norm so that one allocation serves every call on this layer
     d.norm = CKV_NORM_L2;
-    return carve_workspace(d, desc->dtype, max_budget).total;
+    return carve_workspace(d, desc->dtype, max_budget).total_split;
 }
 
 static void mark(void *const *ev, int slot, hipStream_t s)
@@ -143,7 +149,7 @@ struct ScorePlan {
     char *base;
     float *a_raw, *vnorm, *part, *stats;
     const void *w_t; // the projection in output-major layout (the caller's, or the workspace copy)
-    bool attn_only, have_gram, need_wt, tile_a, wave_a, mfma_v, l2_mfma;
+    bool attn_only, have_gram, need_wt, tile_a, wave_a, mfma_v, l2_mfma, split_v;
     int chunks;
     hipStream_t s;
 };
@@ -165,8 +171,10 @@ static int score_plan(const ckv_layer_desc *desc, const void *q_win, const void 
         return CKV_E_INVALID_ARG;
     p.have_gram = desc->flags & CKV_WO_IS_GRAM;
     if (p.have_gram && !(mfma_allowed(desc) && vproj_l2_mfma_supported(d))) return CKV_E_UNSUPPORTED;
-    p.need_wt = !p.attn_only && !p.have_gram && !(desc->flags & CKV_WO_OUT_IN);
     p.ws = carve_workspace(d, desc->dtype, 0);
+    p.split_v = !p.attn_only && desc->dtype == CKV_F32 && !(desc->flags & CKV_NO_MFMA) && vproj_split_supported(d) &&
+                workspace_bytes >= p.ws.total_split;
+    p.need_wt = !p.attn_only && !p.have_gram && !p.split_v && !(desc->flags & CKV_WO_OUT_IN);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < p.ws.total) return CKV_E_WORKSPACE;
     p.s = (hipStream_t)hip_stream;
     p.base = (char *)workspace;
@@ -241,7 +249,9 @@ static int score_magnitudes(const ScorePlan &p, const ckv_layer_desc *desc, cons
             gram = g;
         }
         e = launch_vproj_l2_mfma(d, v, gram, p.vnorm, s);
-    } else if (d.norm == CKV_NORM_L1 && p.mfma_v)
+    } else if (p.split_v)
+        e = launch_vproj_split(d, desc->flags & CKV_WO_OUT_IN, v, w_o, p.base + p.ws.w_split, p.vnorm, s);
+    else if (d.norm == CKV_NORM_L1 && p.mfma_v)
         e = launch_vproj_mfma(d, v, p.w_t, p.vnorm, s);
     else
         e = launch_vproj_generic(d, desc->dtype, v, p.w_t, p.vnorm, s);

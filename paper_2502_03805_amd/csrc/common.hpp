@@ -40,6 +40,8 @@ struct Workspace {
     size_t alloc_tmp;  // budget allocation: pool budgets, counts and the pooled index list
     size_t sel_scratch; // digit histograms, per-head state, per-slice counts of the selection kernels
     size_t total;
+    size_t w_split;    // fp32 layers: the three-part copy of W_O; lies behind what every call needs (see carve_workspace)
+    size_t total_split;
     int max_chunks;    // capacity of stats_part per window row
 };
 
@@ -76,6 +78,12 @@ hipError_t launch_attn_colsum_wave(const Dims &d, const void *q, const void *k, 
 hipError_t launch_vproj_generic(const Dims &d, int dtype, const void *v, const void *w_t, float *vnorm,
                                 hipStream_t s);
 hipError_t launch_vproj_mfma(const Dims &d, const void *v, const void *w_t, float *vnorm, hipStream_t s);
+// the same (either norm) for fp32 layers, on the bf16 matrix cores with every operand split into three parts; w_o in
+// either layout, w3 holds vproj_split_bytes(d) of scratch
+bool vproj_split_supported(const Dims &d);
+size_t vproj_split_bytes(const Dims &d);
+hipError_t launch_vproj_split(const Dims &d, int out_in, const void *v, const void *w_o, void *w3, float *vnorm,
+                              hipStream_t s);
 // L2 norm through the Gram matrix W_O^h W_O^h^T (bf16, d_h = 128)
 bool vproj_l2_mfma_supported(const Dims &d);
 size_t vproj_l2_workspace_bytes(const Dims &d);

@@ -1,0 +1,307 @@
+// Per-entry L1 (or L2) magnitude of the projected value for fp32 layers, on the bf16 matrix cores
+// (Theorem 3.3; Algorithm 1, lines 2-3):  N^h_i = sum_c | sum_t V^g[i,t] * W_O^h[t,c] |.
+//
+// An fp32 number is the sum of three bf16 numbers (3 x 8 significant bits, the same exponent range):
+//   x = x0 + x1 + x2,  x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1), both differences exact.
+// With round-to-nearest |x1| <= 2^-9 |x0| and |x2| <= 2^-18 |x0|, so of the nine products of v * w the three that are
+// left out (v1 w2, v2 w1, v2 w2) are below 2^-26 of it, under half an ulp of the fp32 product; the six others are exact
+// in the MFMA's fp32 accumulators and are added smallest first.  Nothing is held in 16 bits that was held in 32: the
+// three parts together are the number.
+//
+//   split     W_O once per call into [head][d_model][3 parts][d_h] (and from the canonical layout to output-major)
+//   project   the tiling of the bf16 kernel: a wave keeps RB blocks of 16 token rows (all three parts) as MFMA
+//             fragments, the head's parts stream through LDS in tiles of 32 columns (24 KiB at d_h 128, double
+//             buffered, direct buffer->LDS loads, 16-byte chunks swizzled), six MFMAs per (k-step, row block), the
+//             previous column block's |acc| drained under them.
+//
+// What bounds it: the matrix cores; six bf16 MFMAs per fp32 product still leave 2.7 times the rate of the fp32 MFMA
+// (157 TFLOP/s nominal).  Measured at 16 query heads over 4 kv heads, d_h 128, d_model 2048, 8192 tokens: the score call
+// 2.63 ms with the vector kernel (27 TFLOP/s), 0.388 ms with this one; 4 heads, d_h 64, d_model 256, 1024 tokens: the
+// vector kernel's 84 us become 10.  Relative error of the magnitudes against 64 bits: 6.6e-7 before, 2.1e-7 now (the
+// d_model sum runs in 16 accumulators instead of one).
+#include <type_traits>
+
+#include "common.hpp"
+
+namespace ckv {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+constexpr int VS_THREADS = 256;
+constexpr int VS_WAVES = 4;
+constexpr int VS_TN = 32;   // output columns per LDS tile (every supported d_model is a multiple)
+constexpr int VS_PARTS = 3;
+
+#define LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
+
+// The three bf16 parts of x.  A value whose nearest bf16 is infinite (the last half step below FLT_MAX) takes the
+// truncated first part, and an infinity or NaN is its own first part with zeros behind it.
+__device__ __forceinline__ void split3(float x, uint32_t &p0, uint32_t &p1, uint32_t &p2)
+{
+    const uint32_t u = __float_as_uint(x);
+    uint32_t h = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+    if ((h & 0x7F80u) == 0x7F80u || (u & 0x7F800000u) == 0x7F800000u)
+        h = (u >> 16) | ((u & 0x7FFFFFFFu) > 0x7F800000u ? 0x40u : 0u);
+    p0 = h & 0xFFFFu;
+    const bool finite = (u & 0x7F800000u) != 0x7F800000u;
+    const float r = finite ? x - __uint_as_float(p0 << 16) : 0.f;
+    const uint32_t ur = __float_as_uint(r);
+    p1 = (ur + 0x7FFFu + ((ur >> 16) & 1u)) >> 16;
+    const float r2 = r - __uint_as_float(p1 << 16);
+    p2 = __float_as_uint(r2) >> 16; // at most 8 significant bits are left: exact
+}
+
+// Eight consecutive values as three fragments.
+__device__ __forceinline__ void split8(const float4 &a, const float4 &b, bf16x8 (&f)[VS_PARTS])
+{
+    const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    uint32_t w[VS_PARTS][4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        uint32_t lo[VS_PARTS], hi[VS_PARTS];
+        split3(x[2 * e], lo[0], lo[1], lo[2]);
+        split3(x[2 * e + 1], hi[0], hi[1], hi[2]);
+#pragma unroll
+        for (int p = 0; p < VS_PARTS; ++p) w[p][e] = lo[p] | (hi[p] << 16);
+    }
+#pragma unroll
+    for (int p = 0; p < VS_PARTS; ++p) f[p] = __builtin_bit_cast(bf16x8, make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]));
+}
+
+// ---- split of W_O -----------------------------------------------------------------------------------
+// Output-major source [d_model][H * d_h]: a thread takes 8 neighbouring values of one output column.
+__global__ __launch_bounds__(256) void split_wo_kernel(const float *__restrict__ w, bf16_t *__restrict__ out, int H, int dh,
+                                                       int dm)
+{
+    const int per_col = H * dh / 8;
+    const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= (size_t)dm * per_col) return;
+    const int c = (int)(t / per_col), e = (int)(t % per_col) * 8, h = e / dh, d = e % dh;
+    const float4 *src = reinterpret_cast<const float4 *>(w + (size_t)c * H * dh + e);
+    bf16x8 f[VS_PARTS];
+    split8(src[0], src[1], f);
+    bf16_t *dst = out + ((size_t)h * dm + c) * VS_PARTS * dh + d;
+#pragma unroll
+    for (int p = 0; p < VS_PARTS; ++p) *reinterpret_cast<bf16x8 *>(dst + (size_t)p * dh) = f[p];
+}
+
+// Canonical source [H * d_h][d_model]: a 64 x 32 block (d_h by columns) is turned in LDS on the way.
+__global__ __launch_bounds__(256) void split_wo_turn_kernel(const float *__restrict__ w, bf16_t *__restrict__ out, int dh,
+                                                            int dm)
+{
+    __shared__ float tile[64][33];
+    const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 64; // d_model is a multiple of 32, H * d_h one of 64
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) tile[ty + 8 * j][tx] = w[(size_t)(r0 + ty + 8 * j) * dm + c0 + tx];
+    __syncthreads();
+    const int c = threadIdx.x >> 3, e = (threadIdx.x & 7) * 8;
+    float x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = tile[e + j][c];
+    bf16x8 f[VS_PARTS];
+    split8(make_float4(x[0], x[1], x[2], x[3]), make_float4(x[4], x[5], x[6], x[7]), f);
+    const int h = r0 / dh, d = r0 % dh + e;
+    bf16_t *dst = out + ((size_t)h * dm + c0 + c) * VS_PARTS * dh + d;
+#pragma unroll
+    for (int p = 0; p < VS_PARTS; ++p) *reinterpret_cast<bf16x8 *>(dst + (size_t)p * dh) = f[p];
+}
+
+// ---- projection -------------------------------------------------------------------------------------
+template <int DH>
+struct SGeo {
+    static constexpr int KS = DH / 32;                     // k-steps of one 16x16x32 MFMA chain
+    static constexpr int ROW_BYTES = DH * 2;               // one part of one column: 16 or 8 chunks of 16 bytes
+    static constexpr int CPR = ROW_BYTES / 16;
+    static constexpr int COL_BYTES = VS_PARTS * ROW_BYTES; // the three parts of a column are neighbours
+    static constexpr int TILE_BYTES = VS_TN * COL_BYTES;   // 24 or 12 KiB
+    static constexpr int LOADS = TILE_BYTES / 1024 / VS_WAVES; // direct loads per wave per tile
+    // chunk q of a row of column c sits at slot q ^ swz(c): the 16 columns of a fragment read then fall on
+    // different banks (d_h 64: two columns share the 256 bytes of a bank row, so neighbours take the same key)
+    __host__ __device__ static constexpr int swz(int c) { return DH == 128 ? (c & 15) : ((c >> 1) & 7); }
+};
+
+template <int DH, int RB, bool L2>
+__global__ __launch_bounds__(VS_THREADS, 2) void vproj_split_kernel(const float *__restrict__ v, const bf16_t *__restrict__ w3,
+                                                                    float *__restrict__ vnorm, int H, int G, int n, int dm,
+                                                                    int64_t vs0, int64_t vs1, int64_t vs2, int row_tiles,
+                                                                    int heads)
+{
+    using geo = SGeo<DH>;
+    constexpr int KS = geo::KS, CB = VS_TN / 16;
+    __shared__ __attribute__((aligned(1024))) char lds[2 * geo::TILE_BYTES];
+    // workgroup L runs on XCD L % 8; an XCD takes consecutive query heads one after the other, so that the workgroups
+    // resident on it stream the same head's parts out of its L2
+    const int xcd = blockIdx.x & 7, k_in_xcd = blockIdx.x >> 3;
+    const int hpx = (heads + 7) >> 3;
+    const int in_xcd = k_in_xcd / row_tiles, hb = xcd * hpx + in_xcd; // batch * H + head
+    if (in_xcd >= hpx || hb >= heads) return;                         // uniform over the workgroup
+    const int tile_x = k_in_xcd % row_tiles;
+    const int h = hb % H, bi = hb / H, g = h / G;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, kc = lane >> 4;
+    const int row0 = (tile_x * VS_WAVES + wave) * (RB * 16);
+
+    // one head's parts: d_model * COL_BYTES (the host checks that this stays below 2 GiB)
+    const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(w3 + (size_t)h * dm * VS_PARTS * DH), 0, dm * geo::COL_BYTES, 0x00020000);
+    // load j of this wave fills KiB m = j * 4 + wave of the tile; a lane's 16 bytes belong to column col, part row p
+    auto issue_load = [&](int tile, int j, char *buf) {
+        const int kib = j * VS_WAVES + wave;
+        const int byte = kib * 1024 + lane * 16;             // where this lane's chunk lands in the tile
+        const int row = byte / geo::ROW_BYTES, slot = (byte % geo::ROW_BYTES) / 16;
+        const int col = row / VS_PARTS;
+        const uint32_t voff = (uint32_t)(row * geo::ROW_BYTES + ((slot ^ geo::swz(col)) * 16));
+        const uint32_t soff = (uint32_t)tile * geo::TILE_BYTES;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, LDS_PTR(buf + kib * 1024), 16, voff, soff, 0, 0);
+    };
+#pragma unroll
+    for (int j = 0; j < geo::LOADS; ++j) issue_load(0, j, lds);
+
+    // the three parts of the wave's token rows (16 rows x 32 k per fragment), resident in registers
+    bf16x8 a[RB][KS][VS_PARTS];
+    const float *vbase = v + bi * vs0 + g * vs1;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        const int row = min(row0 + rb * 16 + l16, n - 1);
+        const float *p = vbase + (int64_t)row * vs2 + kc * 8;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const float4 x = *reinterpret_cast<const float4 *>(p + s * 32), y = *reinterpret_cast<const float4 *>(p + s * 32 + 4);
+            split8(x, y, a[rb][s]);
+        }
+    }
+    float sum[RB][4];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sum[rb][j] = 0.f;
+    f32x4 acc[2][RB];
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) acc[p][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // byte offsets of the fragments of part 0 inside a 16-column block; part p lies ROW_BYTES * p behind
+    int boff[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) boff[s] = l16 * geo::COL_BYTES + (((4 * s + kc) ^ geo::swz(l16)) * 16);
+    bf16x8 b[KS][VS_PARTS];
+    auto read_b = [&](const char *block, int s, int p) {
+        b[s][p] = *reinterpret_cast<const bf16x8 *>(block + boff[s] + p * geo::ROW_BYTES);
+    };
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int p = 0; p < VS_PARTS; ++p) read_b(lds, s, p);
+
+    const int tiles = dm / VS_TN;
+    auto drain = [&](float &to, float x) { to = L2 ? fmaf(x, x, to) : to + fabsf(x); };
+    auto tile_step = [&](auto buf_c, int t) {
+        constexpr int BUF = decltype(buf_c)::value;
+        const char *cur = lds + BUF * geo::TILE_BYTES;
+        char *nxt = lds + (BUF ^ 1) * geo::TILE_BYTES;
+        const int tn = min(t + 1, tiles - 1); // the last iteration re-fetches its own tile into the idle buffer
+#pragma unroll
+        for (int j = 0; j < geo::LOADS; ++j) issue_load(tn, j, nxt);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            const int pp = cb & 1;
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                // (part of W_O, part of V), smallest products first
+                constexpr int WP[6] = {2, 1, 0, 1, 0, 0}, VP[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+                for (int q = 0; q < 6; ++q) {
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb) {
+                        if (s == 0 && q == 0)
+                            acc[pp][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[s][WP[q]], a[rb][s][VP[q]], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                        else
+                            acc[pp][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[s][WP[q]], a[rb][s][VP[q]], acc[pp][rb], 0, 0, 0);
+                    }
+                    // after a part's last use in this block, its slot takes the next block's fragment
+                    if (cb + 1 < CB && (q == 0 || q == 3 || q == 5)) read_b(cur + (cb + 1) * 16 * geo::COL_BYTES, s, WP[q]);
+                    // the previous column block's products, spread over the k-steps
+                    if (q < RB) {
+#pragma unroll
+                        for (int e = 0; e < 4 / KS; ++e) drain(sum[q][s * (4 / KS) + e], acc[pp ^ 1][q][s * (4 / KS) + e]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int p = 0; p < VS_PARTS; ++p) read_b(nxt, s, p);
+    };
+    static_assert(RB <= 6, "one row block is drained per product group");
+    for (int t = 0; t < tiles; t += 2) {
+        tile_step(std::integral_constant<int, 0>{}, t);
+        if (t + 1 < tiles) tile_step(std::integral_constant<int, 1>{}, t + 1);
+    }
+    float *out = vnorm + (size_t)hb * (size_t)n;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) drain(sum[rb][j], acc[(CB - 1) & 1][rb][j]);
+        float x = (sum[rb][0] + sum[rb][1]) + (sum[rb][2] + sum[rb][3]);
+        x += __shfl_xor(x, 16);
+        x += __shfl_xor(x, 32);
+        const int row = row0 + rb * 16 + l16;
+        if (kc == 0 && row < n) out[row] = L2 ? sqrtf(x) : x;
+    }
+}
+
+template <int DH, int RB>
+static void launch_project(const Dims &d, const void *v, const bf16_t *w3, float *vnorm, hipStream_t s)
+{
+    const int rows_per_wg = VS_WAVES * RB * 16, row_tiles = (d.n + rows_per_wg - 1) / rows_per_wg;
+    const int heads = d.batch * d.H;
+    const dim3 grid((unsigned)(8ll * ((heads + 7) / 8) * row_tiles)), block(VS_THREADS);
+    if (d.norm == CKV_NORM_L2)
+        hipLaunchKernelGGL((vproj_split_kernel<DH, RB, true>), grid, block, 0, s, (const float *)v, w3, vnorm, d.H, d.G, d.n,
+                           d.dm, d.vs[0], d.vs[1], d.vs[2], row_tiles, heads);
+    else
+        hipLaunchKernelGGL((vproj_split_kernel<DH, RB, false>), grid, block, 0, s, (const float *)v, w3, vnorm, d.H, d.G, d.n,
+                           d.dm, d.vs[0], d.vs[1], d.vs[2], row_tiles, heads);
+}
+
+size_t vproj_split_bytes(const Dims &d) { return (size_t)d.H * d.dh * d.dm * VS_PARTS * 2; }
+
+bool vproj_split_supported(const Dims &d)
+{
+    return (d.dh == 64 || d.dh == 128) && d.dm % VS_TN == 0 && (size_t)d.dm * VS_PARTS * d.dh * 2 < ((size_t)1 << 31) &&
+           ((long long)d.batch * d.H + 8) * (d.n / 64 + 2) < (1ll << 31) &&
+           (long long)d.dm * (d.H * (long long)d.dh / 8) < (256ll << 31) && d.H * (long long)d.dh / 64 < 65536;
+}
+
+hipError_t launch_vproj_split(const Dims &d, int out_in, const void *v, const void *w_o, void *w3, float *vnorm, hipStream_t s)
+{
+    if (out_in) {
+        const size_t threads = (size_t)d.dm * (d.H * d.dh / 8);
+        hipLaunchKernelGGL(split_wo_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, (const float *)w_o,
+                           (bf16_t *)w3, d.H, d.dh, d.dm);
+    } else {
+        hipLaunchKernelGGL(split_wo_turn_kernel, dim3(d.dm / 32, d.H * d.dh / 64), dim3(256), 0, s, (const float *)w_o,
+                           (bf16_t *)w3, d.dh, d.dm);
+    }
+    // Row blocks per wave: the most the registers hold (all three parts of RB x 16 rows) re-reads W_O least, but a short
+    // launch then leaves CUs without work: one block per wave while even that gives at most one workgroup per CU slot.
+    const long long wgs1 = (long long)d.batch * d.H * ((d.n + VS_WAVES * 16 - 1) / (VS_WAVES * 16));
+    if (d.dh == 64) {
+        if (wgs1 <= 512) launch_project<64, 1>(d, v, (const bf16_t *)w3, vnorm, s);
+        else launch_project<64, 5>(d, v, (const bf16_t *)w3, vnorm, s);
+    } else {
+        if (wgs1 <= 512) launch_project<128, 1>(d, v, (const bf16_t *)w3, vnorm, s);
+        else launch_project<128, 3>(d, v, (const bf16_t *)w3, vnorm, s);
+    }
+    return hipGetLastError();
+}
+
+} // namespace ckv

@@ -1,0 +1,94 @@
+"""Edges of the kernels' tiles and of the rules that choose between kernels, one small case each (GPU)."""
+import numpy as np
+import pytest
+
+from helpers import cfg_desc
+from workload import CONFIGS, make_layer
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import paper_2502_03805_amd as P
+    P.load()
+    return P
+
+
+def magnitudes64(v, w_o, H, norm):
+    """Row norms of V^g W_O^h in float64: v [b,Hkv,n,dh], w_o [H*dh, d_model] -> [b,H,n]."""
+    b, Hkv, n, dh = v.shape
+    out = np.empty((b, H, n))
+    for bi in range(b):
+        for h in range(H):
+            p = v[bi, h * Hkv // H].astype(np.float64) @ w_o[h * dh:(h + 1) * dh].astype(np.float64)
+            out[bi, h] = np.abs(p).sum(-1) if norm == 1 else np.sqrt(np.square(p).sum(-1))
+    return out
+
+
+def score(P, desc, q, k, v, w_o, ws_bytes=None):
+    import torch
+    b, H, Hkv, n = desc.batch, desc.n_q_heads, desc.n_kv_heads, desc.n_ctx
+    ws = torch.empty(P.workspace_bytes(desc, 1) if ws_bytes is None else ws_bytes, dtype=torch.uint8, device="cuda")
+    attn = torch.empty((b, Hkv, n), dtype=torch.float32, device="cuda")
+    crit, vnorm = torch.empty_like(attn), torch.empty((b, H, n), dtype=torch.float32, device="cuda")
+    P.criticalkv_score(desc, q, k, v, w_o, attn, crit, vnorm, workspace=ws)
+    torch.cuda.synchronize()
+    return attn.cpu().numpy(), crit.cpu().numpy(), vnorm.cpu().numpy()
+
+
+# ---- fp32 magnitudes on the matrix cores (every operand as three bf16 parts) ---------------------------------------
+# n around one and several workgroups of either row-block count, d_model of one tile and of an odd number of tiles
+@pytest.mark.parametrize("norm", [1, 2])
+@pytest.mark.parametrize("wo_out_in", [False, True])
+@pytest.mark.parametrize("dh,H,Hkv,n,dm", [(128, 2, 1, 63, 32), (128, 8, 2, 65, 96), (128, 32, 8, 1217, 64),
+                                           (64, 3, 3, 64, 32), (64, 8, 2, 257, 160), (64, 40, 8, 961, 96)])
+def test_fp32_magnitudes_against_float64(P, dh, H, Hkv, n, dm, wo_out_in, norm):
+    """The split's relative error is below half an fp32 ulp per product; the sums are fp32 (d_h terms, then d_model / 16
+    magnitudes per accumulator): 2e-6 covers both, and the vector kernel's error is the yardstick."""
+    import torch
+    cfg = CONFIGS["tiny"].with_(head_dim=dh, n_q_heads=H, n_kv_heads=Hkv, n_ctx=n, d_model=dm, window=8, batch=2)
+    t = make_layer(cfg)
+    ref = magnitudes64(t["v"], t["w_o"], H, norm)
+    dev = {name: torch.from_numpy(a).cuda() for name, a in t.items()}
+    w = dev["w_o"].t().contiguous() if wo_out_in else dev["w_o"]
+    v = torch.zeros((2, n, Hkv, dh + 4), device="cuda")[..., :dh].permute(0, 2, 1, 3)  # a strided cache: [b, n, Hkv, dh+4]
+    v.copy_(dev["v"])
+    flags = P.CKV_WO_OUT_IN if wo_out_in else 0
+    err = {}
+    for name, extra in (("split", 0), ("vector", P.CKV_NO_MFMA)):
+        desc = cfg_desc(P, cfg, flags=flags | extra, norm=norm, v_stride=v.stride()[:3])
+        got = score(P, desc, dev["q_win"], dev["k"], v, w)[2]
+        err[name] = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+        assert np.abs(got - ref).max() <= 2e-6 * np.abs(ref).max()
+    assert err["split"] <= max(1.05 * err["vector"], 2e-7), err
+
+
+@pytest.mark.parametrize("v_scale,w_scale", [(1e30, 1e-30), (1e-25, 1e25), (3.0e38, 1e-20), (1e-30, 1e-3)])
+def test_fp32_magnitudes_over_the_exponent_range(P, v_scale, w_scale):
+    """Entries up to the last half step below FLT_MAX (whose nearest bf16 is infinite) and down to 1e-30."""
+    import torch
+    cfg = CONFIGS["tiny"].with_(n_ctx=130, d_model=64)
+    t = make_layer(cfg)
+    v = np.clip(t["v"] / np.abs(t["v"]).max(), -1, 1).astype(np.float32) * np.float32(v_scale)
+    if v_scale > 1e38:
+        v[0, 0, 5, 3], v[0, 1, 7, 0] = np.finfo(np.float32).max, -np.finfo(np.float32).max
+    w = (t["w_o"] * np.float32(w_scale)).astype(np.float32)
+    ref = magnitudes64(v, w, cfg.n_q_heads, 1)
+    got = score(P, cfg_desc(P, cfg), *(torch.from_numpy(a).cuda() for a in (t["q_win"], t["k"], v, w)))[2]
+    assert np.isfinite(got).all()
+    assert np.abs(got / ref - 1).max() <= 2e-6
+
+
+def test_fp32_score_accepts_a_workspace_without_room_for_the_split(P):
+    """A workspace that ends before the split's scratch is accepted and gives the vector kernel's bits."""
+    import torch
+    cfg = CONFIGS["tiny"].with_(n_ctx=300)
+    t = make_layer(cfg)
+    dev = [torch.from_numpy(t[name]).cuda() for name in ("q_win", "k", "v", "w_o")]
+    desc = cfg_desc(P, cfg)
+    split_bytes = cfg.n_q_heads * cfg.head_dim * cfg.d_model * 6
+    small = score(P, desc, *dev, ws_bytes=P.workspace_bytes(desc, 0) - split_bytes + 256)
+    vector = score(P, cfg_desc(P, cfg, flags=P.CKV_NO_MFMA), *dev)
+    for a, b in zip(small, vector):
+        assert np.array_equal(a, b)
