@@ -148,8 +148,8 @@ struct ScorePlan {
     Workspace ws;
     char *base;
     float *a_raw, *vnorm, *part, *stats;
-    const void *w_t; // the projection in output-major layout (the caller's, or the workspace copy)
-    bool attn_only, have_gram, need_wt, tile_a, wave_a, mfma_v, l2_mfma, split_v;
+    const void *w_t; // the projection in the layout the magnitudes are computed from (the caller's, or the workspace copy)
+    bool attn_only, have_gram, turn_wo, tile_a, wave_a, mfma_v, l2_mfma, split_v;
     int chunks;
     hipStream_t s;
 };
@@ -174,7 +174,6 @@ static int score_plan(const ckv_layer_desc *desc, const void *q_win, const void 
     p.ws = carve_workspace(d, desc->dtype, 0);
     p.split_v = !p.attn_only && desc->dtype == CKV_F32 && !(desc->flags & CKV_NO_MFMA) && vproj_split_supported(d) &&
                 workspace_bytes >= p.ws.total_split;
-    p.need_wt = !p.attn_only && !p.have_gram && !p.split_v && !(desc->flags & CKV_WO_OUT_IN);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < p.ws.total) return CKV_E_WORKSPACE;
     p.s = (hipStream_t)hip_stream;
     p.base = (char *)workspace;
@@ -182,7 +181,6 @@ static int score_plan(const ckv_layer_desc *desc, const void *q_win, const void 
     p.vnorm = p.attn_only ? nullptr : vnorm_opt ? vnorm_opt : (float *)(p.base + p.ws.vnorm);
     p.part = (float *)(p.base + p.ws.stats_part);
     p.stats = (float *)(p.base + p.ws.stats);
-    p.w_t = p.need_wt ? (const void *)(p.base + p.ws.w_t) : w_o;
     // matrix-core attention: one wave per query head over shared key tiles where a kv group has at most four
     // 32-row blocks of window queries (the 4:1 group with a 32-row window), wave-private key streams otherwise
     const int row_blocks = d.G * ((d.W + 31) / 32);
@@ -190,17 +188,25 @@ static int score_plan(const ckv_layer_desc *desc, const void *q_win, const void 
     p.wave_a = mfma_allowed(desc) && !p.tile_a && attn_wave_supported(d);
     p.mfma_v = mfma_allowed(desc) && vproj_mfma_supported(d);
     p.l2_mfma = d.norm == CKV_NORM_L2 && mfma_allowed(desc) && vproj_l2_mfma_supported(d);
+    // the projection kernels stream the output-major layout, the Gram matrices are computed from the canonical one, and
+    // the fp32 split reads either
+    const bool out_in = desc->flags & CKV_WO_OUT_IN;
+    p.turn_wo = !p.attn_only && !p.have_gram && !p.split_v && (p.l2_mfma ? out_in : !out_in);
+    p.w_t = p.turn_wo ? (const void *)(p.base + p.ws.w_t) : w_o;
     p.chunks = p.tile_a ? mfma_attn_chunks(d) : p.wave_a ? wave_attn_chunks(d) : generic_attn_chunks(d);
     if (p.chunks > p.ws.max_chunks) return CKV_E_WORKSPACE;
     *out = p;
     return CKV_OK;
 }
 
-// Layout change of a canonical W_O (nothing when the caller hands over the output-major form).
+// Layout change of W_O (nothing when the caller hands over the form the magnitudes are computed from).
 static int score_layout(const ScorePlan &p, const ckv_layer_desc *desc, const void *w_o, void *const *ev)
 {
     mark(ev, 2 * CKV_STAGE_WO_LAYOUT, p.s);
-    if (p.need_wt && launch_transpose_wo(p.d, desc->dtype, w_o, p.base + p.ws.w_t, p.s) != hipSuccess) return CKV_E_HIP;
+    if (p.turn_wo) {
+        const int in = p.d.H * p.d.dh, rows = p.l2_mfma ? p.d.dm : in, cols = p.l2_mfma ? in : p.d.dm;
+        if (launch_transpose(desc->dtype, w_o, p.base + p.ws.w_t, rows, cols, p.s) != hipSuccess) return CKV_E_HIP;
+    }
     mark(ev, 2 * CKV_STAGE_WO_LAYOUT + 1, p.s);
     return CKV_OK;
 }
@@ -312,17 +318,15 @@ int criticalkv_prepare_gram(const ckv_layer_desc *desc, const void *w_o, void *g
     if (misaligned16(w_o) || misaligned16(gram_out)) return CKV_E_INVALID_ARG;
     if (desc->dtype != CKV_BF16 || !vproj_l2_mfma_supported(d)) return CKV_E_UNSUPPORTED;
     d.norm = CKV_NORM_L2; // the carve below must contain the Gram scratch whatever norm the descriptor names
-    const bool need_wt = !(desc->flags & CKV_WO_OUT_IN);
     const Workspace ws = carve_workspace(d, desc->dtype, 0);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < ws.total) return CKV_E_WORKSPACE;
     hipStream_t s = (hipStream_t)hip_stream;
     char *base = (char *)workspace;
-    const void *w_t = w_o;
-    if (need_wt) {
-        if (launch_transpose_wo(d, desc->dtype, w_o, base + ws.w_t, s) != hipSuccess) return CKV_E_HIP;
-        w_t = base + ws.w_t;
+    if (desc->flags & CKV_WO_OUT_IN) { // the Gram kernel reads the canonical layout
+        if (launch_transpose(desc->dtype, w_o, base + ws.w_t, d.dm, d.H * d.dh, s) != hipSuccess) return CKV_E_HIP;
+        w_o = base + ws.w_t;
     }
-    return launch_gram(d, w_t, gram_out, base + ws.l2_scratch, s) == hipSuccess ? CKV_OK : CKV_E_HIP;
+    return launch_gram(d, w_o, gram_out, base + ws.l2_scratch, s) == hipSuccess ? CKV_OK : CKV_E_HIP;
 }
 
 int criticalkv_select(const ckv_layer_desc *desc, const float *attn, const float *crit, const int32_t *budget,
@@ -382,7 +386,8 @@ int criticalkv_prepare_wo(const ckv_layer_desc *desc, const void *w_o, void *w_o
     if (rc != CKV_OK) return rc;
     if (!w_o || !w_out || w_o == w_out || misaligned16(w_o) || misaligned16(w_out)) return CKV_E_INVALID_ARG;
     if (desc->flags & (CKV_WO_OUT_IN | CKV_WO_IS_GRAM)) return CKV_E_INVALID_ARG;
-    return launch_transpose_wo(d, desc->dtype, w_o, w_out, (hipStream_t)hip_stream) == hipSuccess ? CKV_OK : CKV_E_HIP;
+    return launch_transpose(desc->dtype, w_o, w_out, d.H * d.dh, d.dm, (hipStream_t)hip_stream) == hipSuccess ? CKV_OK
+                                                                                                        : CKV_E_HIP;
 }
 
 int criticalkv_allocate(const ckv_layer_desc *desc, const float *attn, int32_t total_budget, float floor_frac,

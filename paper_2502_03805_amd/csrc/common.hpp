@@ -88,11 +88,11 @@ hipError_t launch_vproj_split(const Dims &d, int out_in, const void *v, const vo
 bool vproj_l2_mfma_supported(const Dims &d);
 size_t vproj_l2_workspace_bytes(const Dims &d);
 size_t vproj_l2_gram_bytes(const Dims &d); // the split bf16 Gram matrices alone
-// gram: the prepared Gram matrices; when null they are computed from w_t into scratch first
-hipError_t launch_gram(const Dims &d, const void *w_t, void *gram_out, void *partial_scratch, hipStream_t s);
+// w_o: the canonical [H*dh, d_model] projection
+hipError_t launch_gram(const Dims &d, const void *w_o, void *gram_out, void *partial_scratch, hipStream_t s);
 hipError_t launch_vproj_l2_mfma(const Dims &d, const void *v, const void *gram, float *vnorm, hipStream_t s);
-// [H*dh, d_model] -> [d_model, H*dh]
-hipError_t launch_transpose_wo(const Dims &d, int dtype, const void *w_o, void *w_t, hipStream_t s);
+// [rows, cols] -> [cols, rows]; rows and cols are multiples of 8 (bf16) or 4 (fp32) elements
+hipError_t launch_transpose(int dtype, const void *in, void *out, int rows, int cols, hipStream_t s);
 // pool + eps + product + group mean; crit may be null (only the pooled attention is written)
 hipError_t launch_combine(const Dims &d, const float *a_raw, const float *vnorm, float *attn, float *crit,
                           hipStream_t s);

@@ -70,28 +70,59 @@ hipError_t launch_vproj_generic(const Dims &d, int dtype, const void *v, const v
     return d.dh == 64 ? vproj_generic_t<bf16_t, 64>(d, v, w_t, vnorm, s) : vproj_generic_t<bf16_t, 128>(d, v, w_t, vnorm, s);
 }
 
-// ---- W_O layout change: [H*dh, d_model] -> [d_model, H*dh] ---------------------------------------
+// ---- layout change: [rows, cols] -> [cols, rows] ---------------------------------------------------
+// Bound by memory.  No LDS: a lane turns a square block of 16-byte rows (8 x 8 bf16 or 4 x 4 fp32) in registers, and the
+// wave's 8 x 8 lanes make every load and every store instruction move whole 128-byte lines; eight (four) loads are in
+// flight per lane.  4096 x 4096 bf16: 21.5 us with a 32 x 32 LDS tile of single elements, 13 us like this (64 MiB,
+// 5.1 TB/s; a copy of 1 GiB runs at that rate).
+// In place of bounds checks inside a block: rows and cols are multiples of the block (cols of 32, rows of 64).
+__device__ __forceinline__ void turn_block(uint4 (&x)[8]) // 8 x 8 of 16 bits
+{
+    uint32_t w[8][4];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { w[i][0] = x[i].x; w[i][1] = x[i].y; w[i][2] = x[i].z; w[i][3] = x[i].w; }
+    // word k of output row j holds rows 2k and 2k + 1 of column j
+    uint32_t o[8][4];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            o[j][k] = __builtin_amdgcn_perm(w[2 * k + 1][j >> 1], w[2 * k][j >> 1], (j & 1) ? 0x07060302u : 0x05040100u);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = make_uint4(o[j][0], o[j][1], o[j][2], o[j][3]);
+}
+__device__ __forceinline__ void turn_block(uint4 (&x)[4]) // 4 x 4 of 32 bits
+{
+    const uint4 a = x[0], b = x[1], c = x[2], d = x[3];
+    x[0] = make_uint4(a.x, b.x, c.x, d.x); x[1] = make_uint4(a.y, b.y, c.y, d.y);
+    x[2] = make_uint4(a.z, b.z, c.z, d.z); x[3] = make_uint4(a.w, b.w, c.w, d.w);
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void transpose_kernel(const T *__restrict__ in, T *__restrict__ out, int rows, int cols)
 {
-    __shared__ T tile[32][33];
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5; // 32 x 8
-    const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
-    for (int j = ty; j < 32; j += 8)
-        if (r0 + j < rows && c0 + tx < cols) tile[j][tx] = in[(size_t)(r0 + j) * cols + c0 + tx];
-    __syncthreads();
-    for (int j = ty; j < 32; j += 8)
-        if (c0 + j < cols && r0 + tx < rows) out[(size_t)(c0 + j) * rows + r0 + tx] = tile[tx][j];
+    constexpr int E = 16 / sizeof(T); // block edge: elements per 16 bytes
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // the eight lanes of a load that differ in lane & 7 read neighbouring column blocks of a row; in a store, the eight
+    // that differ in lane >> 3 write neighbouring row blocks of a column
+    const int lr = blockIdx.y * (8 * E) + (lane >> 3) * E, lc = (blockIdx.x * 4 + wave) * (8 * E) + (lane & 7) * E;
+    if (lr >= rows || lc >= cols) return;
+    uint4 x[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) x[i] = *reinterpret_cast<const uint4 *>(in + (size_t)(lr + i) * cols + lc);
+    turn_block(x);
+#pragma unroll
+    for (int j = 0; j < E; ++j) *reinterpret_cast<uint4 *>(out + (size_t)(lc + j) * rows + lr) = x[j];
 }
 
-hipError_t launch_transpose_wo(const Dims &d, int dtype, const void *w_o, void *w_t, hipStream_t s)
+hipError_t launch_transpose(int dtype, const void *in, void *out, int rows, int cols, hipStream_t s)
 {
-    const int rows = d.H * d.dh, cols = d.dm;
-    dim3 grid((cols + 31) / 32, (rows + 31) / 32);
+    const int edge = dtype == CKV_F32 ? 32 : 64; // rows and columns of one wave's tile; four waves side by side
+    dim3 grid((cols + 4 * edge - 1) / (4 * edge), (rows + edge - 1) / edge);
     if (dtype == CKV_F32)
-        hipLaunchKernelGGL(transpose_kernel<float>, grid, dim3(256), 0, s, (const float *)w_o, (float *)w_t, rows, cols);
+        hipLaunchKernelGGL(transpose_kernel<float>, grid, dim3(256), 0, s, (const float *)in, (float *)out, rows, cols);
     else
-        hipLaunchKernelGGL(transpose_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t *)w_o, (bf16_t *)w_t, rows, cols);
+        hipLaunchKernelGGL(transpose_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t *)in, (bf16_t *)out, rows, cols);
     return hipGetLastError();
 }
 

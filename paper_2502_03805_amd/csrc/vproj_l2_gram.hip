@@ -5,8 +5,8 @@
 // The shortcut is exact for the 2-norm only (for L1 the n x d_model products are needed).  It replaces the
 // n x d_h x d_model contraction by n x d_h x d_h: 32 times less MFMA work at d_model = 4096.
 //
-//   gram_partial  G^h over a slice of the d_model columns, fp32 on the vector ALUs (W_O is a weight:
-//                 this is a per-layer constant, a few GFLOP)
+//   gram_partial  G^h over a slice of the d_model columns on the matrix cores, from the canonical W_O (exact products,
+//                 fp32 sums; W_O is a weight: this is a per-layer constant, a few GFLOP)
 //   gram_finish   sums the slices, folds the symmetric G onto its lower block triangle (32 x 32 blocks: those
 //                 below the diagonal doubled, those above dropped -- the quadratic form is unchanged and
 //                 12 of the 32 block products fall away) and splits it into two bf16 matrices G_hi + G_lo
@@ -26,7 +26,6 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int GL_DH = 128;
 constexpr int GL_SLICES = 4;          // d_model slices of the Gram partial sums
-constexpr int GL_TILE_C = 128;        // columns of W_O staged per LDS tile in gram_partial
 constexpr int GL_G_BYTES = GL_DH * GL_DH * 2; // one bf16 Gram matrix: 32 KiB
 
 #define LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
@@ -38,69 +37,139 @@ __device__ __forceinline__ bf16_t f32_to_bf16_rne(float x)
     return (bf16_t)(u >> 16);
 }
 
-// partial[head][slice][t][u] = sum over the slice's columns c of w_t[c][h*128+t] * w_t[c][h*128+u]
-__global__ __launch_bounds__(256) void gram_partial_kernel(const bf16_t *__restrict__ w_t, float *__restrict__ partial,
-                                                           int H, int dm)
+// partial[head][slice][u][t] = sum over the slice's columns c of W_O[h*128+u][c] * W_O[h*128+t][c], for the 32 x 32 blocks
+// on and below the diagonal (G is symmetric).
+//
+// v_mfma_f32_16x16x4_f32: a lane holds row (A) / column (B) lane % 16 at k = lane / 16; accumulator v is row
+// 4 * (lane / 16) + v, column lane % 16.  The products of bf16 values are exact in fp32 and the instruction adds its four
+// products one after the other, so a chain over ascending columns has the bits of a scalar fmaf loop (checked against
+// one).  The bf16 form of the instruction would be faster still, but it sums in another order, and every value of G that
+// lies near a tie of G_hi's rounding would then move between the two parts of the stored constant.
+//
+// Work split: a chain runs over a whole slice, so the blocks are what is dealt out: 40 blocks of 16 x 16 per (head,
+// slice), 20 per workgroup, two per wave (one accumulator chain each; five per wave leave a SIMD with one wave, which
+// does not cover its own waits: 47 us instead of 38).  The workgroup's tile, 128 rows x 64 columns of the
+// canonical W_O (rows contiguous along d_model), sits in LDS with each row's even words before its odd ones, so that a
+// lane's values of 16 columns are one 16-byte read (single words: 56 us instead of 47, both with five blocks per wave), at a pitch of 36 words (the 16 rows
+// of a read start on 16 different bank groups); the next two tiles are in registers meanwhile.  Bound by the fp32 matrix rate (157 TFLOP/s nominal;
+// 2.7 GFLOP at 32 heads and d_model 4096 are 17 us; measured 38 us).  With fp32 products on the vector ALUs from the output-major layout it
+// took 229 us, and a layout change of 21 us before it.
+constexpr int GP_CHUNK = 64;                   // columns per LDS tile
+constexpr int GP_HALF = GP_CHUNK / 4;          // words of a row that lanes with k = 0, 1 read (the others read the rest)
+constexpr int GP_PITCH = 2 * GP_HALF + 4;      // words per row
+constexpr int GP_WAVES = 10;                   // waves per workgroup
+constexpr int GP_BLOCKS = 2;                   // 16 x 16 blocks per wave
+constexpr int GP_STAGERS = 512;                // threads that move the tile, two 16-byte pieces each
+
+__global__ __launch_bounds__(64 * GP_WAVES) void gram_partial_kernel(const bf16_t *__restrict__ w_o, float *__restrict__ partial, int dm)
 {
-    __shared__ __attribute__((aligned(16))) bf16_t tile[GL_TILE_C * GL_DH]; // [c][t], 32 KiB
+    __shared__ __attribute__((aligned(16))) uint32_t tile[2][GL_DH * GP_PITCH];
     const int h = blockIdx.x, slice = blockIdx.y;
-    const int cols = dm / GL_SLICES; // host guarantees dm % (GL_SLICES * GL_TILE_C) == 0
-    const size_t ldw = (size_t)H * GL_DH;
-    const int t0 = (threadIdx.x >> 4) * 8, u0 = (threadIdx.x & 15) * 8;
-    float acc[8][8];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, kg = lane >> 4;
+    const int cols = dm / GL_SLICES; // host guarantees dm % (GL_SLICES * GP_CHUNK) == 0
+    // blocks in row order: block row i (16 rows of G) has (i | 1) + 1 blocks, up to the end of its 32 x 32 diagonal block
+    int bi[GP_BLOCKS], bj[GP_BLOCKS];
+    {
+        int at = (blockIdx.z * GP_WAVES + wave) * GP_BLOCKS, i = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = 0.f;
-    for (int c0 = slice * cols; c0 < (slice + 1) * cols; c0 += GL_TILE_C) {
-        __syncthreads();
-        for (int e = threadIdx.x; e < GL_TILE_C * GL_DH / 8; e += 256) { // 16-byte pieces
-            const int c = e >> 4, piece = e & 15;
-            *reinterpret_cast<uint4 *>(&tile[c * GL_DH + piece * 8]) =
-                *reinterpret_cast<const uint4 *>(w_t + (size_t)(c0 + c) * ldw + (size_t)h * GL_DH + piece * 8);
+        for (int x = 0; x < GP_BLOCKS; ++x) {
+            int left = x == 0 ? at : bj[x - 1] + 1;
+            while (left > (i | 1)) { left -= (i | 1) + 1; ++i; }
+            bi[x] = i;
+            bj[x] = left;
         }
-        __syncthreads();
-        for (int c = 0; c < GL_TILE_C; ++c) {
-            float a[8], b[8];
-            const uint4 ra = *reinterpret_cast<const uint4 *>(&tile[c * GL_DH + t0]);
-            const uint4 rb = *reinterpret_cast<const uint4 *>(&tile[c * GL_DH + u0]);
-            const uint32_t ua[4] = {ra.x, ra.y, ra.z, ra.w}, ub[4] = {rb.x, rb.y, rb.z, rb.w};
+    }
+    int aoff[GP_BLOCKS], boff[GP_BLOCKS]; // word of this lane's row inside the tile, for k = lane / 16 of the first four columns
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                a[2 * j] = __uint_as_float(ua[j] << 16); a[2 * j + 1] = __uint_as_float(ua[j] & 0xFFFF0000u);
-                b[2 * j] = __uint_as_float(ub[j] << 16); b[2 * j + 1] = __uint_as_float(ub[j] & 0xFFFF0000u);
+    for (int x = 0; x < GP_BLOCKS; ++x) {
+        aoff[x] = (bi[x] * 16 + l16) * GP_PITCH + (kg >> 1) * GP_HALF;
+        boff[x] = (bj[x] * 16 + l16) * GP_PITCH + (kg >> 1) * GP_HALF;
+    }
+    // odd columns are the upper halves of their words; a bf16 value is the upper half of its fp32
+    const uint32_t pick = (kg & 1) ? 0x07060C0Cu : 0x05040C0Cu;
+    auto value = [&](uint32_t w) { return __uint_as_float(__builtin_amdgcn_perm(w, 0u, pick)); };
+
+    // staging: 8 pieces per row; two tiles are in flight in registers while a third is worked on
+    const bool stager = wave < GP_STAGERS / 64; // uniform over the wave
+    const bf16_t *src = w_o + ((size_t)h * GL_DH + (threadIdx.x >> 3) % (GL_DH / 2)) * dm + slice * cols + (threadIdx.x & 7) * 8;
+    const int tiles = cols / GP_CHUNK; // even: d_model is a multiple of 512
+    auto fetch = [&](int t, uint4 (&piece)[2]) {
+        const int c0 = min(t, tiles - 1) * GP_CHUNK;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) piece[j] = *reinterpret_cast<const uint4 *>(src + (size_t)j * (GL_DH / 2) * dm + c0);
+    };
+    auto stash = [&](uint32_t *to, const uint4 (&piece)[2]) {
+        if (!stager) return;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            uint32_t *p = to + (j * (GL_DH / 2) + (threadIdx.x >> 3)) * GP_PITCH + (threadIdx.x & 7) * 2;
+            *reinterpret_cast<uint2 *>(p) = make_uint2(piece[j].x, piece[j].z);
+            *reinterpret_cast<uint2 *>(p + GP_HALF) = make_uint2(piece[j].y, piece[j].w);
+        }
+    };
+    f32x4 acc[GP_BLOCKS];
+#pragma unroll
+    for (int x = 0; x < GP_BLOCKS; ++x) acc[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto work = [&](const uint32_t *cur) {
+#pragma unroll
+        for (int q = 0; q < GP_HALF / 4; ++q) { // 16 columns: four words per lane and operand, four steps of the chains
+            uint4 a[GP_BLOCKS], b[GP_BLOCKS];
+#pragma unroll
+            for (int x = 0; x < GP_BLOCKS; ++x) {
+                a[x] = *reinterpret_cast<const uint4 *>(cur + aoff[x] + 4 * q);
+                b[x] = *reinterpret_cast<const uint4 *>(cur + boff[x] + 4 * q);
             }
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
+            for (int k = 0; k < 4; ++k)
 #pragma unroll
-                for (int j = 0; j < 8; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+                for (int x = 0; x < GP_BLOCKS; ++x) {
+                    const uint32_t wa = k == 0 ? a[x].x : k == 1 ? a[x].y : k == 2 ? a[x].z : a[x].w;
+                    const uint32_t wb = k == 0 ? b[x].x : k == 1 ? b[x].y : k == 2 ? b[x].z : b[x].w;
+                    acc[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(value(wa), value(wb), acc[x], 0, 0, 0);
+                }
         }
+    };
+    uint4 even[2], odd[2]; // pieces of the next even and odd tile
+    fetch(0, even);
+    fetch(1, odd);
+    stash(tile[0], even);
+    __syncthreads();
+    for (int t = 0; t < tiles; t += 2) {
+        fetch(t + 2, even);
+        work(tile[0]);
+        stash(tile[1], odd); // (read last before the previous barrier)
+        __syncthreads();
+        fetch(t + 3, odd);
+        work(tile[1]);
+        stash(tile[0], even);
+        __syncthreads();
     }
     float *dst = partial + ((size_t)h * GL_SLICES + slice) * GL_DH * GL_DH;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int x = 0; x < GP_BLOCKS; ++x)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) dst[(t0 + i) * GL_DH + u0 + j] = acc[i][j];
+        for (int v = 0; v < 4; ++v) dst[(bi[x] * 16 + 4 * kg + v) * GL_DH + bj[x] * 16 + l16] = acc[x][v];
 }
 
 // G = sum of the slices (fixed order), folded onto its lower block triangle, split into hi + lo bf16;
-// gram[head][0 = hi, 1 = lo][u][t]
+// gram[head][0 = hi, 1 = lo][u][t].  One element per thread, 64 workgroups per head (a single workgroup per head: 22 us).
 __global__ __launch_bounds__(256) void gram_finish_kernel(const float *__restrict__ partial, bf16_t *__restrict__ gram)
 {
-    const int h = blockIdx.x;
-    for (int e = threadIdx.x; e < GL_DH * GL_DH; e += 256) {
-        float g = 0.f;
+    const int h = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x; // e = u * 128 + t
+    const int bu = e >> 12, bt = (e & (GL_DH - 1)) >> 5;
+    float g = 0.f;
+    if (bt <= bu) { // (the other blocks hold nothing)
 #pragma unroll
         for (int s = 0; s < GL_SLICES; ++s) g += partial[((size_t)h * GL_SLICES + s) * GL_DH * GL_DH + e];
-        // G is symmetric, so v G v^T = sum over the 32 x 32 blocks (bu, bt) on and below the diagonal, the ones
-        // below it counted twice: the kernel reads those blocks only (20 of the 32 block products)
-        const int bu = e >> 12, bt = (e & (GL_DH - 1)) >> 5; // e = u * 128 + t
-        g = bt < bu ? 2.f * g : bt == bu ? g : 0.f;
-        const bf16_t hi = f32_to_bf16_rne(g);
-        const bf16_t lo = f32_to_bf16_rne(g - bf16_to_f32(hi));
-        gram[((size_t)h * 2 + 0) * GL_DH * GL_DH + e] = hi;
-        gram[((size_t)h * 2 + 1) * GL_DH * GL_DH + e] = lo;
     }
+    // v G v^T = sum over the 32 x 32 blocks (bu, bt) on and below the diagonal, the ones below it counted twice: the
+    // kernel reads those blocks only (20 of the 32 block products)
+    g = bt < bu ? 2.f * g : g;
+    const bf16_t hi = f32_to_bf16_rne(g);
+    const bf16_t lo = f32_to_bf16_rne(g - bf16_to_f32(hi));
+    gram[((size_t)h * 2 + 0) * GL_DH * GL_DH + e] = hi;
+    gram[((size_t)h * 2 + 1) * GL_DH * GL_DH + e] = lo;
 }
 
 // N^h_i for HEADS query heads of a kv group and one range of rows, with the heads' Gram matrices resident in LDS.
@@ -268,7 +337,7 @@ __global__ __launch_bounds__(HEADS * 256, HEADS == 1 ? 2 : 1) void vproj_l2_resi
 bool vproj_l2_mfma_supported(const Dims &d)
 {
     // (the V rows of one kv head are addressed through a buffer descriptor with 32-bit byte offsets)
-    return d.dh == GL_DH && d.dm % (GL_SLICES * GL_TILE_C) == 0 &&
+    return d.dh == GL_DH && d.dm % 512 == 0 &&
            (((int64_t)(d.n - 1) * d.vs[2] + GL_DH) * 2) < ((int64_t)1 << 31);
 }
 
@@ -280,11 +349,11 @@ size_t vproj_l2_workspace_bytes(const Dims &d)
     return (size_t)d.H * GL_SLICES * GL_DH * GL_DH * 4 + vproj_l2_gram_bytes(d);
 }
 
-hipError_t launch_gram(const Dims &d, const void *w_t, void *gram_out, void *partial_scratch, hipStream_t s)
+hipError_t launch_gram(const Dims &d, const void *w_o, void *gram_out, void *partial_scratch, hipStream_t s)
 {
     float *partial = (float *)partial_scratch;
-    hipLaunchKernelGGL(gram_partial_kernel, dim3(d.H, GL_SLICES), dim3(256), 0, s, (const bf16_t *)w_t, partial, d.H, d.dm);
-    hipLaunchKernelGGL(gram_finish_kernel, dim3(d.H), dim3(256), 0, s, partial, (bf16_t *)gram_out);
+    hipLaunchKernelGGL(gram_partial_kernel, dim3(d.H, GL_SLICES, 2), dim3(64 * GP_WAVES), 0, s, (const bf16_t *)w_o, partial, d.dm);
+    hipLaunchKernelGGL(gram_finish_kernel, dim3(GL_DH * GL_DH / 256, d.H), dim3(256), 0, s, partial, (bf16_t *)gram_out);
     return hipGetLastError();
 }
 

@@ -92,3 +92,38 @@ def test_fp32_score_accepts_a_workspace_without_room_for_the_split(P):
     vector = score(P, cfg_desc(P, cfg, flags=P.CKV_NO_MFMA), *dev)
     for a, b in zip(small, vector):
         assert np.array_equal(a, b)
+
+
+# ---- layout change of W_O and the Gram constant -----------------------------------------------------------------------
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("H,dh,dm", [(1, 64, 32), (3, 64, 96), (2, 128, 160), (5, 128, 544), (32, 128, 4096)])
+def test_layout_change_is_exact(P, H, dh, dm, dtype):
+    """Rows and columns around the blocks a lane and a wave turn."""
+    import torch
+    cfg = CONFIGS["tiny"].with_(n_q_heads=H, n_kv_heads=H, head_dim=dh, d_model=dm, dtype=dtype)
+    w = torch.randn(H * dh, dm, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    out = torch.full((dm, H * dh), float("nan"), dtype=w.dtype, device="cuda")
+    P.criticalkv_prepare_wo(cfg_desc(P, cfg), w, out)
+    assert torch.equal(out, w.t())
+
+
+@pytest.mark.parametrize("wo_out_in", [False, True])
+@pytest.mark.parametrize("H,dm", [(1, 512), (3, 1024), (8, 4608)])
+def test_gram_constant_against_float64(P, H, dm, wo_out_in):
+    """hi + lo of the folded Gram matrices: fp32 sums of exact products over d_model (relative to the diagonal, whose terms
+    do not cancel), split with a relative error of 2^-17."""
+    import torch
+    cfg = CONFIGS["llama32k"].with_(n_q_heads=H, n_kv_heads=H, d_model=dm, n_ctx=64)
+    w = (0.02 * torch.randn(H * 128, dm, device="cuda")).to(torch.bfloat16)
+    desc = cfg_desc(P, cfg, flags=P.CKV_WO_OUT_IN if wo_out_in else 0)
+    gram = torch.empty(P.gram_bytes(desc), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(P.workspace_bytes(desc, 1), dtype=torch.uint8, device="cuda")
+    P.criticalkv_prepare_gram(desc, w.t().contiguous() if wo_out_in else w, gram, workspace=ws)
+    got = gram.view(torch.bfloat16).view(H, 2, 128, 128).double().sum(1).cpu().numpy()
+    wh = w.double().cpu().numpy().reshape(H, 128, dm)
+    ref = wh @ wh.transpose(0, 2, 1)
+    block = np.arange(128) // 32
+    fold = np.where(block[:, None] > block[None, :], 2.0, np.where(block[:, None] == block[None, :], 1.0, 0.0))
+    diag = np.sqrt(np.einsum("hii->hi", ref))
+    scale = diag[:, :, None] * diag[:, None, :]
+    assert (np.abs(got - ref * fold) <= 2.0 ** -16 * np.abs(ref * fold) + 2e-6 * scale).all()
