@@ -78,6 +78,9 @@ hipError_t launch_attn_colsum_wave(const Dims &d, const void *q, const void *k, 
 hipError_t launch_vproj_generic(const Dims &d, int dtype, const void *v, const void *w_t, float *vnorm,
                                 hipStream_t s);
 hipError_t launch_vproj_mfma(const Dims &d, const void *v, const void *w_t, float *vnorm, hipStream_t s);
+// Row blocks per wave of a projection launch: of `choices`, the one whose rounds of workgroups cost least (the first of
+// equals).  An XCD runs 64 workgroups at a time; a round costs RB + c2 with more than 32 of them, 0.48 RB + c1 with fewer.
+int cheapest_rounds(const Dims &d, int rows_per_block, double c2, double c1, const int *choices, int count);
 // the same (either norm) for fp32 layers, on the bf16 matrix cores with every operand split into three parts; w_o in
 // either layout, w3 holds vproj_split_bytes(d) of scratch
 bool vproj_split_supported(const Dims &d);

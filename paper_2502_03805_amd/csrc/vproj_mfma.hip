@@ -217,14 +217,56 @@ static void launch_rb(const Dims &d, const void *v, const void *w_t, float *vnor
                        (const bf16_t *)w_t, vnorm, d.H, d.G, d.n, d.dm, d.vs[0], d.vs[1], d.vs[2], row_tiles, heads, pair);
 }
 
+int cheapest_rounds(const Dims &d, int rows_per_block, double c2, double c1, const int *choices, int count)
+{
+    const long long heads_per_xcd = ((long long)d.batch * d.H + 7) / 8;
+    int best = choices[0];
+    double least = 0.0;
+    for (int i = 0; i < count; ++i) {
+        const int rb = choices[i], rows = rows_per_block * rb;
+        const long long wgs = heads_per_xcd * ((d.n + rows - 1) / rows), rest = wgs % 64;
+        const double cost = (double)(wgs / 64) * (rb + c2) + (rest > 32 ? rb + c2 : rest > 0 ? 0.48 * rb + c1 : 0.0);
+        if (i == 0 || cost < least) { least = cost; best = rb; }
+    }
+    return best;
+}
+
+// Row blocks per wave.  Many blocks stream W_O less often; few cut a short launch into enough workgroups to fill the
+// chip (an XCD holds 64: two per CU), and the last round of workgroups is paid for whole.  A round's time was measured
+// (d_model 4096, 2 .. 7 blocks; the ratios hold at 2048 and 5120) as proportional to RB + c when every CU holds two
+// workgroups and to 0.48 RB + c1 when it holds one, with c = 1.07, c1 = 0.90 at d_h 128 and c = 1.84, c1 = 1.83 at
+// d_h 64; the choice is the RB whose rounds cost least.  Against the fixed 6 (7 for the longest launches) that this
+// replaces, 32 heads, us: n 1024 57.5 -> 34.4 (2 blocks), 2048 60.2 -> 50.7 (4), 4096 112.4 -> 91.6 (4), 8192
+// 178.3 -> 176.0 (4); 6 and 7 as before from 12288 on.  d_h 64, d_model 2048: n 1024 20.6 -> 13.8, 8192 53.2 -> 48.6 (8
+// blocks), 4 x 30000 646 -> 611 (10).
+static int pick_row_blocks(const Dims &d, const int *choices, int count)
+{
+    return cheapest_rounds(d, VM_WAVES * 16, d.dh == 128 ? 1.07 : 1.84, d.dh == 128 ? 0.90 : 1.83, choices, count);
+}
+
 hipError_t launch_vproj_mfma(const Dims &d, const void *v, const void *w_t, float *vnorm, hipStream_t s)
 {
-    // 7 row blocks per wave stream W_O 14 % less often than 6, but the workgroups are longer; measured, that wins
-    // once the launch has many rounds of workgroups (1.4 % at 128K) and loses on short launches (2 % at 32K)
-    const long long wgs7 = (long long)d.batch * d.H * ((d.n + VM_WAVES * 7 * 16 - 1) / (VM_WAVES * 7 * 16));
-    if (d.dh == 64) launch_rb<64, 6>(d, v, w_t, vnorm, s);
-    else if (wgs7 >= 4096) launch_rb<128, 7>(d, v, w_t, vnorm, s);
-    else launch_rb<128, 6>(d, v, w_t, vnorm, s);
+    if (d.dh == 64) { // (12 blocks spill)
+        const int choices[] = {10, 8, 6, 4, 3, 2};
+        switch (pick_row_blocks(d, choices, 6)) {
+        case 10: launch_rb<64, 10>(d, v, w_t, vnorm, s); break;
+        case 8: launch_rb<64, 8>(d, v, w_t, vnorm, s); break;
+        case 6: launch_rb<64, 6>(d, v, w_t, vnorm, s); break;
+        case 4: launch_rb<64, 4>(d, v, w_t, vnorm, s); break;
+        case 3: launch_rb<64, 3>(d, v, w_t, vnorm, s); break;
+        default: launch_rb<64, 2>(d, v, w_t, vnorm, s); break;
+        }
+    } else { // (8 blocks spill)
+        const int choices[] = {7, 6, 5, 4, 3, 2};
+        switch (pick_row_blocks(d, choices, 6)) {
+        case 7: launch_rb<128, 7>(d, v, w_t, vnorm, s); break;
+        case 6: launch_rb<128, 6>(d, v, w_t, vnorm, s); break;
+        case 5: launch_rb<128, 5>(d, v, w_t, vnorm, s); break;
+        case 4: launch_rb<128, 4>(d, v, w_t, vnorm, s); break;
+        case 3: launch_rb<128, 3>(d, v, w_t, vnorm, s); break;
+        default: launch_rb<128, 2>(d, v, w_t, vnorm, s); break;
+        }
+    }
     return hipGetLastError();
 }
 

@@ -281,6 +281,15 @@ bool vproj_split_supported(const Dims &d)
            (long long)d.dm * (d.H * (long long)d.dh / 8) < (256ll << 31) && d.H * (long long)d.dh / 64 < 65536;
 }
 
+// Row blocks per wave, by the cost of the launch's rounds: an XCD holds 64 workgroups (two per CU); a round's time was
+// measured as proportional to RB + c2 with two workgroups on every CU and to 0.48 RB + c1 with one (16 heads, d_model 2048:
+// c2 = 0.40, c1 = 0.38 at d_h 128, 0.50 and 0.55 at d_h 64), as for the bf16 kernel.  The stage's time there with 1 / 2 / 3
+// blocks, us: n 1024 60 / 81 / 106, 4096 149 / 143 / 179, 6144 214 / 205 / 197, 16384 537 / 509 / 525.
+static int pick_row_blocks(const Dims &d, const int *choices, int count)
+{
+    return cheapest_rounds(d, VS_WAVES * 16, d.dh == 128 ? 0.40 : 0.50, d.dh == 128 ? 0.38 : 0.55, choices, count);
+}
+
 hipError_t launch_vproj_split(const Dims &d, int out_in, const void *v, const void *w_o, void *w3, float *vnorm, hipStream_t s)
 {
     if (out_in) {
@@ -291,15 +300,21 @@ hipError_t launch_vproj_split(const Dims &d, int out_in, const void *v, const vo
         hipLaunchKernelGGL(split_wo_turn_kernel, dim3(d.dm / 32, d.H * d.dh / 64), dim3(256), 0, s, (const float *)w_o,
                            (bf16_t *)w3, d.dh, d.dm);
     }
-    // Row blocks per wave: the most the registers hold (all three parts of RB x 16 rows) re-reads W_O least, but a short
-    // launch then leaves CUs without work: one block per wave while even that gives at most one workgroup per CU slot.
-    const long long wgs1 = (long long)d.batch * d.H * ((d.n + VS_WAVES * 16 - 1) / (VS_WAVES * 16));
-    if (d.dh == 64) {
-        if (wgs1 <= 512) launch_project<64, 1>(d, v, (const bf16_t *)w3, vnorm, s);
-        else launch_project<64, 5>(d, v, (const bf16_t *)w3, vnorm, s);
-    } else {
-        if (wgs1 <= 512) launch_project<128, 1>(d, v, (const bf16_t *)w3, vnorm, s);
-        else launch_project<128, 3>(d, v, (const bf16_t *)w3, vnorm, s);
+    if (d.dh == 64) { // (six blocks spill, and five are nowhere the best)
+        const int choices[] = {4, 3, 2, 1};
+        switch (pick_row_blocks(d, choices, 4)) {
+        case 4: launch_project<64, 4>(d, v, (const bf16_t *)w3, vnorm, s); break;
+        case 3: launch_project<64, 3>(d, v, (const bf16_t *)w3, vnorm, s); break;
+        case 2: launch_project<64, 2>(d, v, (const bf16_t *)w3, vnorm, s); break;
+        default: launch_project<64, 1>(d, v, (const bf16_t *)w3, vnorm, s); break;
+        }
+    } else { // (the registers hold three)
+        const int choices[] = {3, 2, 1};
+        switch (pick_row_blocks(d, choices, 3)) {
+        case 3: launch_project<128, 3>(d, v, (const bf16_t *)w3, vnorm, s); break;
+        case 2: launch_project<128, 2>(d, v, (const bf16_t *)w3, vnorm, s); break;
+        default: launch_project<128, 1>(d, v, (const bf16_t *)w3, vnorm, s); break;
+        }
     }
     return hipGetLastError();
 }

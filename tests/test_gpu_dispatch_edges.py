@@ -127,3 +127,26 @@ def test_gram_constant_against_float64(P, H, dm, wo_out_in):
     diag = np.sqrt(np.einsum("hii->hi", ref))
     scale = diag[:, :, None] * diag[:, None, :]
     assert (np.abs(got - ref * fold) <= 2.0 ** -16 * np.abs(ref * fold) + 2e-6 * scale).all()
+
+
+# ---- row blocks per wave of the projection ----------------------------------------------------------------------------
+@pytest.mark.parametrize("dtype,dh,H,Hkv,dm,ns", [
+    # 8 * 64 = 512 workgroups are one full round: n on both sides of every change of the choice
+    ("bf16", 128, 32, 8, 128, (511, 1025, 1537, 2049, 3073, 4097, 6145, 8193)),
+    ("bf16", 64, 32, 8, 256, (511, 1025, 3073, 4097, 8193, 10241)),
+    ("f32", 128, 16, 4, 32, (1025, 2049, 6145)),
+    ("f32", 64, 16, 4, 32, (1025, 2049, 3073, 8193)),
+])
+def test_magnitudes_with_every_row_block_count(P, dtype, dh, H, Hkv, dm, ns):
+    """fp32 sums of exact products (bf16: d_h of them, then d_model magnitudes): 2e-6 of the result."""
+    import torch
+    for n in ns:
+        cfg = CONFIGS["llama32k"].with_(n_q_heads=H, n_kv_heads=Hkv, head_dim=dh, d_model=dm, n_ctx=n, dtype=dtype, window=8)
+        g = torch.Generator(device="cuda").manual_seed(n)
+        dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+        q, k, v = (torch.randn(s, generator=g, device="cuda").to(dt) for s in ((1, H, 8, dh), (1, Hkv, n, dh), (1, Hkv, n, dh)))
+        w = torch.randn((H * dh, dm), generator=g, device="cuda").to(dt)
+        got = score(P, cfg_desc(P, cfg), q, k, v, w)[2]
+        for h in (0, H - 1):
+            ref = (v[0, h * Hkv // H].double() @ w[h * dh:(h + 1) * dh].double()).abs().sum(-1).cpu().numpy()
+            assert np.abs(got[0, h] / ref - 1).max() <= 2e-6, (n, h)
