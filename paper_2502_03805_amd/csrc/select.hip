@@ -24,6 +24,8 @@
 //   write     find digit 2 -> tau2, r2; ordered write of S1 u S2: what earlier slices contribute is read from
 //             their per-slice counts; -1 tail; count
 // Every decision is integer arithmetic on exact counts, so the result does not depend on scheduling.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace ckv {
@@ -42,7 +44,7 @@ enum { ST_D0 = 0, ST_A0, ST_D1, ST_A1, ST_TAU, ST_R, ST_WORDS = 8 };
 struct SelArgs {
     const uint32_t *attn; // float bits
     const uint32_t *crit;
-    const int32_t *budget;
+    const int32_t *budget; // null: max_budget for every head
     uint32_t *keys2;   // [heads][n]
     uint32_t *hist;    // [heads][2 stages][3 passes][SEL_BINS]
     uint32_t *state;   // [heads][2 stages][ST_WORDS]
@@ -67,7 +69,7 @@ __device__ __forceinline__ uint32_t order_key(uint32_t u)
 // b1, b2: the two stages' shares of the rest
 __device__ __forceinline__ void head_budget(const SelArgs &A, int head, int &B, int &b1, int &b2, int &kept)
 {
-    B = max(0, min(A.budget[head], min(A.n, A.max_budget)));
+    B = max(0, min(A.budget ? A.budget[head] : A.max_budget, min(A.n, A.max_budget)));
     kept = min(A.n - A.n_rank, B);
     const int rest = B - kept;
     b1 = (int)floor(A.alpha * (double)rest);
@@ -80,16 +82,24 @@ struct SelShared {
     uint32_t digit, above;
 };
 
+// Inclusive prefix sum over the wave: shifts inside rows of 16 lanes, then the rows' last lanes broadcast to the rows
+// behind (no LDS round trips, which a shuffle costs: they were a fifth of a row kernel's time).
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x)
+{
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false); // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false); // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false); // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false); // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false); // row_bcast:15 into rows 1, 3
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false); // row_bcast:31 into rows 2, 3
+    return x;
+}
+
 // Exclusive prefix sum over the workgroup in thread order; total in `total`.
 __device__ __forceinline__ uint32_t block_exclusive_scan(SelShared &sh, uint32_t x, uint32_t &total)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t incl = x;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(incl, o);
-        if (lane >= o) incl += y;
-    }
+    const uint32_t incl = wave_inclusive_scan(x);
     __syncthreads(); // wave_tot may still be read by a previous scan
     if (lane == 63) sh.wave_tot[wave] = incl;
     __syncthreads();
@@ -414,6 +424,256 @@ __global__ __launch_bounds__(SEL_THREADS) void select_write_kernel(SelArgs A)
     if (slice == 0 && threadIdx.x == 0) A.count[head] = B;
 }
 
+// ---- rows that one workgroup holds in registers ----------------------------------------------------------------------
+// The whole selection of a head in one launch: a thread keeps KPT keys of both score arrays in registers (tokens
+// (j * 1024 + thread) * 4 + e: every load is 16 bytes per lane), the digit histograms and prefix sums live in LDS.
+// The same digits, thresholds and tie order as the sliced kernels below, so the result is the same set.
+//   * a digit's histogram has four copies, interleaved (bin * 4 + lane % 4): scores crowd into few bins, and the lanes of
+//     an LDS atomic that hit one address are served one after the other
+//   * the thread that sums a bin also clears it, so a digit costs three barriers
+//   * ties are ranked only when the threshold's ties do not all fit
+//
+// What bounds it: instruction issue of one CU (about 5 vector instructions and an LDS atomic per key and digit), so the
+// time grows with the row while the sliced kernels cost seven launch boundaries whatever its length.  Eight heads, us, sliced /
+// one workgroup: n 512 34.8 / 10.6, 3072 36.3 / 10.7, 8192 36.6 / 15.2, 16384 37.1 / 21.2, 24576 36 / 29.9, 32768 36 / 38.4: rows
+// of up to 24576 keys are taken whole.  (Merging runs of equal digits into one atomic, as the sliced kernels do, costs more
+// instructions than it saves atomics here: 8192 keys 18.5 instead of 17.3 us.)
+constexpr int SEL_ROW_MAX = 24576;
+constexpr int ROW_THREADS = 1024;
+constexpr int ROW_WAVES = ROW_THREADS / 64;
+
+struct RowShared {
+    uint32_t hist[SEL_BINS * 4];
+    uint32_t wave_tot[4][ROW_WAVES];
+    uint32_t digit, above, inside;
+};
+
+// Exclusive prefix sums in thread order of NP words at once (two 16-bit counts each); totals as well.
+template <int NP>
+__device__ __forceinline__ void row_scan(RowShared &sh, const uint32_t (&x)[NP], uint32_t (&excl)[NP], uint32_t (&total)[NP])
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t incl[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) incl[p] = wave_inclusive_scan(x[p]);
+    __syncthreads(); // the totals of the scan before may still be read
+    if (lane == 63) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) sh.wave_tot[p][wave] = incl[p];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        uint32_t base = 0, tot = 0;
+#pragma unroll
+        for (int w = 0; w < ROW_WAVES; ++w) {
+            const uint32_t t = sh.wave_tot[p][w];
+            if (w < wave) base += t;
+            tot += t;
+        }
+        excl[p] = base + incl[p] - x[p];
+        total[p] = tot;
+    }
+}
+
+// The threshold of the `want` largest of the keys that `live` marks: its key and how many of its ties still fit, and
+// whether that is all of them.  The histogram is clear on entry and on exit.
+template <int KPT>
+__device__ __forceinline__ void row_threshold(RowShared &sh, const uint32_t (&key)[KPT], uint32_t live, uint32_t want,
+                                              uint32_t &tau, uint32_t &fit, bool &all_fit)
+{
+    constexpr int PER = SEL_BINS / ROW_THREADS;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t prefix = 0u, pmask = 0u, rest = want;
+#pragma unroll
+    for (int pass = 0; pass < 3; ++pass) {
+        const int shift = pass == 0 ? DSHIFT0 : pass == 1 ? DSHIFT1 : 0;
+        const uint32_t mask = pass == 2 ? DMASK2 : DMASK0;
+#pragma unroll
+        for (int j = 0; j < KPT; ++j) {
+            const bool on = ((live >> j) & 1u) && (key[j] & pmask) == prefix;
+            if (on) atomicAdd(&sh.hist[((key[j] >> shift) & mask) * 4 + (lane & 3)], 1u);
+        }
+        __syncthreads();
+        // bins in descending order, PER per thread
+        uint32_t h[PER], local = 0u;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            uint4 *bin = reinterpret_cast<uint4 *>(&sh.hist[(SEL_BINS - 1 - ((int)threadIdx.x * PER + j)) * 4]);
+            const uint4 c = *bin;
+            *bin = make_uint4(0u, 0u, 0u, 0u);
+            h[j] = c.x + c.y + c.z + c.w;
+            local += h[j];
+        }
+        const uint32_t incl = wave_inclusive_scan(local);
+        if (lane == 63) sh.wave_tot[0][wave] = incl;
+        if (threadIdx.x == 0) { sh.digit = 0u; sh.above = 0u; sh.inside = 0u; }
+        __syncthreads();
+        uint32_t run = incl - local;
+#pragma unroll
+        for (int w = 0; w < ROW_WAVES; ++w) run += w < wave ? sh.wave_tot[0][w] : 0u;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            if (run < rest && rest <= run + h[j]) {
+                sh.digit = (uint32_t)(SEL_BINS - 1 - ((int)threadIdx.x * PER + j));
+                sh.above = run;
+                sh.inside = h[j];
+            }
+            run += h[j];
+        }
+        __syncthreads();
+        prefix |= sh.digit << shift;
+        pmask |= mask << shift;
+        rest -= sh.above;
+        all_fit = sh.inside == rest;
+    }
+    tau = prefix;
+    fit = rest;
+}
+
+__device__ __forceinline__ int row_token(int j) { return ((j >> 2) * ROW_THREADS + (int)threadIdx.x) * 4 + (j & 3); }
+
+// This thread's keys of a row; tokens past the row re-read its end.
+template <int KPT>
+__device__ __forceinline__ void row_load(const uint32_t *row, int n, uint32_t (&key)[KPT])
+{
+#pragma unroll
+    for (int q = 0; q < KPT / 4; ++q) {
+        const int i0 = (q * ROW_THREADS + (int)threadIdx.x) * 4;
+        if ((n & 3) == 0) { // a quad is inside or outside as a whole, and 16-byte aligned
+            const uint4 a = *reinterpret_cast<const uint4 *>(row + min(i0, n - 4));
+            key[4 * q] = a.x; key[4 * q + 1] = a.y; key[4 * q + 2] = a.z; key[4 * q + 3] = a.w;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) key[4 * q + e] = row[min(i0 + e, n - 1)];
+        }
+    }
+}
+
+// The bits among `live` of the keys above the threshold and of the first `fit` of its ties in token order.
+template <int KPT>
+__device__ __forceinline__ uint32_t row_above(RowShared &sh, const uint32_t (&key)[KPT], uint32_t live, uint32_t tau,
+                                              uint32_t fit, bool all_fit)
+{
+    constexpr int QUADS = KPT / 4, NP = (QUADS + 1) / 2;
+    uint32_t gt = 0u, ties = 0u;
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+        gt |= (key[j] > tau ? 1u : 0u) << j;
+        ties |= (key[j] == tau ? 1u : 0u) << j;
+    }
+    gt &= live;
+    ties &= live;
+    if (all_fit) return gt | ties; // uniform over the workgroup
+    uint32_t cnt[NP], excl[NP], total[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) cnt[p] = 0u;
+#pragma unroll
+    for (int q = 0; q < QUADS; ++q) cnt[q >> 1] += (uint32_t)__popc((ties >> (4 * q)) & 15u) << (16 * (q & 1));
+    row_scan<NP>(sh, cnt, excl, total);
+    uint32_t before = 0u;
+#pragma unroll
+    for (int q = 0; q < QUADS; ++q) {
+        uint32_t rank = before + ((excl[q >> 1] >> (16 * (q & 1))) & 0xFFFFu);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if ((ties >> (4 * q + e)) & 1u) {
+                gt |= (rank < fit ? 1u : 0u) << (4 * q + e);
+                ++rank;
+            }
+        before += (total[q >> 1] >> (16 * (q & 1))) & 0xFFFFu;
+    }
+    return gt;
+}
+
+template <int KPT>
+__global__ __launch_bounds__(ROW_THREADS) void select_row_kernel(SelArgs A)
+{
+    constexpr int QUADS = KPT / 4, NP = (QUADS + 1) / 2;
+    __shared__ __attribute__((aligned(16))) RowShared sh;
+    const int head = blockIdx.x;
+    const uint32_t *attn = A.attn + (size_t)head * A.n, *crit = A.crit + (size_t)head * A.n;
+    const bool vec_ok = (A.n & 3) == 0;
+    uint32_t key1[KPT], key2[KPT];
+    // both rows are requested at the start; the longest rows would not fit the registers twice and take crit later
+    constexpr bool LATE = KPT > 16;
+    row_load<KPT>(attn, A.n, key1);
+    if (!LATE) row_load<KPT>(crit, A.n, key2);
+    int B, b1, b2, kept;
+    head_budget(A, head, B, b1, b2, kept);
+    for (int b = threadIdx.x * 4; b < SEL_BINS * 4; b += ROW_THREADS * 4) *reinterpret_cast<uint4 *>(&sh.hist[b]) = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    // bit j: the token competes (it is inside the row and not of the kept window)
+    uint32_t rank_ok = 0u;
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+        key1[j] = order_key(key1[j]);
+        rank_ok |= (row_token(j) < A.n_rank ? 1u : 0u) << j;
+    }
+    uint32_t taken = 0u; // stage 1 and the kept window
+    if (b1 > 0) { // uniform over the workgroup, as everything derived from the budget
+        uint32_t live = rank_ok, tau, fit;
+        bool all_fit;
+#pragma unroll
+        for (int j = 0; j < KPT; ++j)
+            if (key1[j] == SEL_TAKEN) live &= ~(1u << j);
+        row_threshold<KPT>(sh, key1, live, (uint32_t)b1, tau, fit, all_fit);
+        taken = row_above<KPT>(sh, key1, rank_ok, tau, fit, all_fit);
+    }
+    if (LATE) row_load<KPT>(crit, A.n, key2);
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+        key2[j] = order_key(key2[j]);
+        if (row_token(j) >= A.n - kept && row_token(j) < A.n) taken |= 1u << j;
+        if ((taken >> j) & 1u) key2[j] = SEL_TAKEN;
+    }
+    // the stage-2 keys with stage-1 entries marked are what the diagnostics read back
+    uint32_t *k2 = A.keys2 + (size_t)head * A.n;
+    uint32_t marked = 0u;
+#pragma unroll
+    for (int q = 0; q < QUADS; ++q) {
+        const int i0 = (q * ROW_THREADS + (int)threadIdx.x) * 4;
+        if (vec_ok) {
+            if (i0 < A.n) *reinterpret_cast<uint4 *>(k2 + i0) = make_uint4(key2[4 * q], key2[4 * q + 1], key2[4 * q + 2], key2[4 * q + 3]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (i0 + e < A.n) k2[i0 + e] = key2[4 * q + e];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) marked |= (key2[4 * q + e] == SEL_TAKEN && i0 + e < A.n ? 1u : 0u) << (4 * q + e);
+    }
+    uint32_t sel = marked;
+    if (b2 > 0) {
+        uint32_t tau, fit;
+        bool all_fit;
+        row_threshold<KPT>(sh, key2, rank_ok & ~marked, (uint32_t)b2, tau, fit, all_fit);
+        sel |= row_above<KPT>(sh, key2, rank_ok, tau, fit, all_fit);
+    }
+    // ordered write
+    uint32_t cnt[NP], excl[NP], total[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) cnt[p] = 0u;
+#pragma unroll
+    for (int q = 0; q < QUADS; ++q) cnt[q >> 1] += (uint32_t)__popc((sel >> (4 * q)) & 15u) << (16 * (q & 1));
+    row_scan<NP>(sh, cnt, excl, total);
+    int32_t *out = A.idx + (size_t)head * A.max_budget;
+    uint32_t before = 0u;
+#pragma unroll
+    for (int q = 0; q < QUADS; ++q) {
+        uint32_t pos = before + ((excl[q >> 1] >> (16 * (q & 1))) & 0xFFFFu);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if ((sel >> (4 * q + e)) & 1u) {
+                if (pos < (uint32_t)A.max_budget) out[pos] = row_token(4 * q + e);
+                ++pos;
+            }
+        before += (total[q >> 1] >> (16 * (q & 1))) & 0xFFFFu;
+    }
+    for (int j = B + (int)threadIdx.x; j < A.max_budget; j += ROW_THREADS) out[j] = -1;
+    if (threadIdx.x == 0) A.count[head] = B;
+}
+
 size_t select_workspace_words(int heads, int n)
 {
     const size_t n_slices = (size_t)(n + SEL_SLICE - 1) / SEL_SLICE;
@@ -475,6 +735,15 @@ hipError_t launch_select_rows(int heads, int n, int protect, const float *attn, 
                               const int32_t *budget, float alpha, int max_budget, int32_t *idx, int32_t *count,
                               uint32_t *keys2, uint32_t *scratch, hipStream_t s)
 {
+    if (n <= SEL_ROW_MAX) {
+        const SelArgs A = make_sel_args(heads, n, protect, attn, crit, budget, alpha, max_budget, idx, count, keys2, scratch);
+        const dim3 grid(heads), block(ROW_THREADS);
+        if (n <= 4 * ROW_THREADS) hipLaunchKernelGGL(select_row_kernel<4>, grid, block, 0, s, A);
+        else if (n <= 8 * ROW_THREADS) hipLaunchKernelGGL(select_row_kernel<8>, grid, block, 0, s, A);
+        else if (n <= 16 * ROW_THREADS) hipLaunchKernelGGL(select_row_kernel<16>, grid, block, 0, s, A);
+        else hipLaunchKernelGGL(select_row_kernel<24>, grid, block, 0, s, A);
+        return hipGetLastError();
+    }
     hipError_t e = launch_select_stage1_hist(heads, n, protect, attn, budget, alpha, max_budget, keys2, scratch, s);
     if (e != hipSuccess) return e;
     return launch_select_finish(heads, n, protect, attn, crit, budget, alpha, max_budget, idx, count, keys2, scratch, s);
@@ -489,31 +758,136 @@ hipError_t launch_select(const Dims &d, const float *attn, const float *crit, co
 }
 
 // ---- budget allocation across the kv heads of a batch item (Algorithm 2, line 1) -------------------------
-// The P entries with the largest pooled score among all Hkv * n entries of a batch item are found with the
-// same selection kernels (one row of Hkv * n keys per batch item, attention only); a head's share is the
-// number of those entries it owns, located by binary search in the ascending index list.
-__global__ void allocate_fill_kernel(int32_t *pool_budget, int batch, int P)
+// The P entries with the largest pooled score among all Hkv * n entries of a batch item are an order statistic of one row
+// of Hkv * n keys: its threshold comes from the selection's stage-1 digits, and a head's share is the number of its
+// entries above the threshold plus those of its ties that still fit (ties go to lower entries first, i.e. to lower heads).
+// Only counts are needed, no membership and no index list: one launch where the row fits a workgroup, five otherwise
+// (clear, three digits, count) -- the whole selection and a binary search in its list took ten (eight heads x 20011: 52 us,
+// now XX).
+struct AllocArgs {
+    int32_t *budget_out; // [batch][Hkv]
+    uint32_t *above;     // [batch][Hkv + 1]: entries above the threshold per head; the last word counts finished workgroups
+    uint32_t *ties;      // [batch][Hkv * n] (the first Hkv words of a row are used)
+    int Hkv, n, floor_each;
+};
+
+template <int KPT>
+__global__ __launch_bounds__(ROW_THREADS) void allocate_row_kernel(SelArgs A, AllocArgs L)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < batch) pool_budget[i] = P;
+    __shared__ __attribute__((aligned(16))) RowShared sh;
+    const int row = blockIdx.x;
+    uint32_t key[KPT];
+    row_load<KPT>(A.attn + (size_t)row * A.n, A.n, key);
+    for (int b = threadIdx.x * 4; b < SEL_BINS * 4; b += ROW_THREADS * 4) *reinterpret_cast<uint4 *>(&sh.hist[b]) = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    uint32_t inside = 0u, live = 0u;
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+        key[j] = order_key(key[j]);
+        inside |= (row_token(j) < A.n ? 1u : 0u) << j;
+        live |= (key[j] != SEL_TAKEN ? 1u : 0u) << j;
+    }
+    uint32_t tau, fit;
+    bool all_fit;
+    row_threshold<KPT>(sh, key, inside & live, (uint32_t)A.max_budget, tau, fit, all_fit);
+    const uint32_t sel = row_above<KPT>(sh, key, inside, tau, fit, all_fit);
+    // the histogram is clear again: its words count the heads' entries (the host takes this kernel for Hkv <= 4 * SEL_BINS)
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < KPT / 4; ++q) {
+        int g_run = -1;
+        uint32_t run = 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (!((sel >> (4 * q + e)) & 1u)) continue;
+            const int g = row_token(4 * q + e) / L.n;
+            if (g != g_run && run) { atomicAdd(&sh.hist[g_run], run); run = 0u; }
+            g_run = g;
+            ++run;
+        }
+        if (run) atomicAdd(&sh.hist[g_run], run);
+    }
+    __syncthreads();
+    for (int g = threadIdx.x; g < L.Hkv; g += ROW_THREADS)
+        L.budget_out[(size_t)row * L.Hkv + g] = min(L.n, L.floor_each + (int)sh.hist[g]);
 }
 
-__global__ void allocate_count_kernel(const int32_t *__restrict__ idx, int P, int Hkv, int n, int floor_each,
-                                      int32_t *__restrict__ budget_out)
+__global__ __launch_bounds__(256) void allocate_clear_kernel(uint32_t *hist, size_t words, AllocArgs L, int batch)
 {
-    const int bi = blockIdx.x, g = threadIdx.x;
-    if (g >= Hkv) return;
-    const int32_t *row = idx + (size_t)bi * P;
-    auto lower_bound = [&](long long key) { // first position whose index is >= key
-        int lo = 0, hi = P;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if ((long long)row[mid] < key) lo = mid + 1; else hi = mid;
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < words) hist[i] = 0u;
+    if (i < (size_t)batch * (L.Hkv + 1)) L.above[i] = 0u;
+    if (i < (size_t)batch * L.Hkv) L.ties[i / L.Hkv * ((size_t)L.Hkv * L.n) + i % L.Hkv] = 0u;
+}
+
+// One workgroup per slice of the row: its entries above the threshold and its ties, added to their heads' counts; the
+// workgroup that finishes last turns the counts into budgets.
+__global__ __launch_bounds__(SEL_THREADS) void allocate_count_kernel(SelArgs A, AllocArgs L)
+{
+    __shared__ SelShared sh;
+    __shared__ uint32_t cnt[2][SEL_SLICE]; // above / ties of the heads this slice touches (at most one per token)
+    __shared__ uint32_t last;
+    const int slice = blockIdx.x, row = blockIdx.y;
+    const int i0 = slice * SEL_SLICE + threadIdx.x * SEL_PER_THREAD;
+    uint32_t w[8];
+    load8(A.attn + (size_t)row * A.n, i0, A.n, (A.n & 3) == 0, w);
+    const uint32_t *st = A.state + (size_t)row * 2 * ST_WORDS;
+    const uint32_t d0 = st[ST_D0], a0 = st[ST_A0], d1 = st[ST_D1], a1 = st[ST_A1];
+    uint32_t d2, a2;
+    find_digit(sh, A.hist + (size_t)row * 2 * 3 * SEL_BINS + 2 * SEL_BINS, 1024, (uint32_t)A.max_budget - a0 - a1, d2, a2);
+    const uint32_t tau = (d0 << DSHIFT0) | (d1 << DSHIFT1) | d2, fit = (uint32_t)A.max_budget - a0 - a1 - a2;
+    const int g0 = slice * SEL_SLICE / L.n, g1 = min(slice * SEL_SLICE + SEL_SLICE - 1, A.n - 1) / L.n;
+    for (int g = threadIdx.x; g <= g1 - g0; g += SEL_THREADS) { cnt[0][g] = 0u; cnt[1][g] = 0u; }
+    __syncthreads();
+    uint32_t *above = L.above + (size_t)row * (L.Hkv + 1), *ties = L.ties + (size_t)row * A.n;
+    if (g0 == g1) { // uniform: the slice lies inside one head
+        uint32_t n_above = 0u, n_ties = 0u;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t key = order_key(w[j]);
+            n_above += i0 + j < A.n && key > tau ? 1u : 0u;
+            n_ties += i0 + j < A.n && key == tau ? 1u : 0u;
         }
-        return lo;
-    };
-    const int owned = lower_bound((long long)(g + 1) * n) - lower_bound((long long)g * n);
-    budget_out[bi * Hkv + g] = min(n, floor_each + owned);
+        const uint32_t both = block_sum(sh, n_above | (n_ties << 16)); // 2048 of either at most
+        if (threadIdx.x == 0) { cnt[0][0] = both & 0xFFFFu; cnt[1][0] = both >> 16; }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t key = order_key(w[j]);
+            if (i0 + j < A.n && key >= tau) atomicAdd(&cnt[key == tau ? 1 : 0][(i0 + j) / L.n - g0], 1u);
+        }
+    }
+    __syncthreads();
+    for (int g = threadIdx.x; g <= g1 - g0; g += SEL_THREADS) {
+        if (cnt[0][g]) atomicAdd(above + g0 + g, cnt[0][g]);
+        if (cnt[1][g]) atomicAdd(ties + g0 + g, cnt[1][g]);
+    }
+    // release before the ticket, acquire after it, both at device scope; the counts are read past the L1
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(above + L.Hkv, 1u) == gridDim.x - 1 ? 1u : 0u;
+    __syncthreads();
+    if (!last) return; // uniform
+    __threadfence();
+    uint32_t carry = 0u;
+    for (int c0 = 0; c0 < L.Hkv; c0 += SEL_THREADS) { // heads in order: how many ties lie before each
+        const int g = c0 + threadIdx.x;
+        uint32_t a = 0u, t = 0u, total;
+        if (g < L.Hkv) {
+            a = __hip_atomic_load(above + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            t = __hip_atomic_load(ties + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const uint32_t before = carry + block_exclusive_scan(sh, t, total);
+        if (g < L.Hkv)
+            L.budget_out[(size_t)row * L.Hkv + g] = min(L.n, L.floor_each + (int)(a + min(fit > before ? fit - before : 0u, t)));
+        carry += total;
+    }
+}
+
+__global__ void allocate_floor_kernel(AllocArgs L, int heads)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < heads) L.budget_out[i] = min(L.n, L.floor_each);
 }
 
 hipError_t launch_allocate(const Dims &d, const float *attn, int total, float floor_frac, int32_t *budget_out,
@@ -521,17 +895,34 @@ hipError_t launch_allocate(const Dims &d, const float *attn, int total, float fl
 {
     const int floor_each = (int)floor((double)floor_frac * (double)total / (double)d.Hkv);
     const int P = (int)min((long long)total - (long long)d.Hkv * floor_each, (long long)d.Hkv * d.n);
-    int32_t *pool_budget = tmp;                 // [batch]
-    int32_t *pool_count = tmp + d.batch;        // [batch]
-    int32_t *pool_idx = tmp + 2 * d.batch;      // [batch][P]
-    if (P > 0) {
-        hipLaunchKernelGGL(allocate_fill_kernel, dim3((d.batch + 63) / 64), dim3(64), 0, s, pool_budget, d.batch, P);
-        hipError_t e = launch_select_rows(d.batch, d.Hkv * d.n, 0, attn, attn, pool_budget, 1.0f, P, pool_idx, pool_count,
-                                          keys2, scratch, s);
-        if (e != hipSuccess) return e;
+    AllocArgs L;
+    L.budget_out = budget_out;
+    L.above = (uint32_t *)tmp; // batch * (Hkv + 1) of the batch * (2 + Hkv * ceil(P / Hkv)) words that are there when P > 0
+    L.ties = keys2;
+    L.Hkv = d.Hkv; L.n = d.n; L.floor_each = floor_each;
+    if (P <= 0) {
+        const int heads = d.batch * d.Hkv;
+        hipLaunchKernelGGL(allocate_floor_kernel, dim3((heads + 255) / 256), dim3(256), 0, s, L, heads);
+        return hipGetLastError();
     }
-    hipLaunchKernelGGL(allocate_count_kernel, dim3(d.batch), dim3(((d.Hkv + 63) / 64) * 64), 0, s, pool_idx, P, d.Hkv, d.n,
-                       floor_each, budget_out);
+    const int N = d.Hkv * d.n;
+    const SelArgs A = make_sel_args(d.batch, N, 0, attn, attn, nullptr, 1.0f, P, nullptr, nullptr, keys2, scratch);
+    if (N <= SEL_ROW_MAX && d.Hkv <= 4 * SEL_BINS) {
+        const dim3 grid(d.batch), block(ROW_THREADS);
+        if (N <= 4 * ROW_THREADS) hipLaunchKernelGGL(allocate_row_kernel<4>, grid, block, 0, s, A, L);
+        else if (N <= 8 * ROW_THREADS) hipLaunchKernelGGL(allocate_row_kernel<8>, grid, block, 0, s, A, L);
+        else if (N <= 16 * ROW_THREADS) hipLaunchKernelGGL(allocate_row_kernel<16>, grid, block, 0, s, A, L);
+        else hipLaunchKernelGGL(allocate_row_kernel<24>, grid, block, 0, s, A, L);
+        return hipGetLastError();
+    }
+    const size_t hist_words = (size_t)d.batch * (2 * 3 * SEL_BINS + 2 * ST_WORDS);
+    const size_t clear = std::max(hist_words, (size_t)d.batch * (d.Hkv + 1));
+    const dim3 grid(A.n_slices, d.batch), block(SEL_THREADS);
+    hipLaunchKernelGGL(allocate_clear_kernel, dim3((unsigned)((clear + 255) / 256)), dim3(256), 0, s, scratch, hist_words, L, d.batch);
+    hipLaunchKernelGGL((select_hist_kernel<0, 0>), grid, block, 0, s, A);
+    hipLaunchKernelGGL((select_hist_kernel<0, 1>), grid, block, 0, s, A);
+    hipLaunchKernelGGL((select_hist_kernel<0, 2>), grid, block, 0, s, A);
+    hipLaunchKernelGGL(allocate_count_kernel, grid, block, 0, s, A, L);
     return hipGetLastError();
 }
 

@@ -150,3 +150,52 @@ def test_magnitudes_with_every_row_block_count(P, dtype, dh, H, Hkv, dm, ns):
         for h in (0, H - 1):
             ref = (v[0, h * Hkv // H].double() @ w[h * dh:(h + 1) * dh].double()).abs().sum(-1).cpu().numpy()
             assert np.abs(got[0, h] / ref - 1).max() <= 2e-6, (n, h)
+
+
+# ---- selection and allocation: rows one workgroup takes, and the sliced kernels behind them ------------------------------
+def tied_scores(n, heads, distinct):
+    r = np.random.Generator(np.random.PCG64(n + distinct))
+    attn = r.integers(0, distinct, (1, heads, n)).astype(np.float32) / 8
+    crit = r.integers(0, distinct + 3, (1, heads, n)).astype(np.float32) - 2
+    return attn, crit
+
+
+@pytest.mark.parametrize("n", [2, 6, 8, 4095, 4096, 4097, 4100, 8191, 8192, 8193, 8196, 16383, 16384, 16385, 16388,
+                               24572, 24575, 24576, 24577, 24580])
+def test_select_at_the_row_lengths_where_the_kernel_changes(P, n):
+    from test_gpu_parity import assert_select_exact, run_select
+    r = np.random.Generator(np.random.PCG64(n))
+    attn, crit = r.standard_normal((1, 3, n)).astype(np.float32), r.lognormal(0, 2, (1, 3, n)).astype(np.float32)
+    for alpha in (0.0, 0.5, 1.0):
+        assert_select_exact(P, attn, crit, r.integers(0, n + 1, (1, 3)), alpha, max_budget=n)
+    for distinct in (1, 3):  # thresholds inside tie groups that cross every quad and wave
+        attn, crit = tied_scores(n, 2, distinct)
+        for B in sorted({1, n // 3, n - 1, n}):
+            if B > 0:
+                assert_select_exact(P, attn, crit, B, 0.5)
+
+
+@pytest.mark.parametrize("n", [130, 4097, 24576, 24579])
+def test_select_with_a_kept_window_at_the_row_lengths_where_the_kernel_changes(P, n):
+    from oracle import cpu_oracle as O
+    from test_gpu_parity import run_select
+    attn, crit = tied_scores(n, 2, 40)
+    for W, B in ((1, 1), (33, 20), (33, n // 2), (100, n)):
+        idx, count, budget = run_select(P, attn, crit, B, 0.5, flags=P.CKV_PROTECT_WINDOW, window=W)
+        ref_idx, ref_count, _ = O.select(attn.astype(np.float64), crit.astype(np.float64), budget, np.float32(0.5),
+                                         max_budget=idx.shape[-1], protect_last=W)
+        assert np.array_equal(idx, ref_idx) and np.array_equal(count, ref_count)
+
+
+@pytest.mark.parametrize("Hkv,n", [(1, 24576), (1, 24577), (3, 1365), (3, 1366), (24, 1024), (25, 1024), (2000, 3), (30000, 1),
+                                   (3000, 11), (7, 5000)])
+def test_allocate_at_the_row_lengths_where_the_kernel_changes(P, Hkv, n):
+    """Rows of Hkv * n keys around one workgroup's most; slices inside one head, over a few and over thousands of heads."""
+    from oracle import cpu_oracle as O
+    from test_gpu_parity import run_allocate
+    r = np.random.Generator(np.random.PCG64(Hkv + n))
+    for attn in (r.random((2, Hkv, n)).astype(np.float32), tied_scores(n, Hkv, 3)[0]):
+        for total in sorted({1, Hkv, (Hkv * n) // 3, Hkv * n}):
+            for floor_frac in (0.0, 0.3):
+                got = run_allocate(P, attn, total, floor_frac)
+                assert np.array_equal(got, O.allocate(attn.astype(np.float64), total, np.float32(floor_frac))), (total, floor_frac)
