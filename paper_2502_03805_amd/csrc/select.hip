@@ -121,14 +121,39 @@ __device__ __forceinline__ uint32_t block_sum(SelShared &sh, uint32_t x)
     return total;
 }
 
-// The thread's 8 consecutive words starting at token i0; words at or beyond n read as 0.
-__device__ __forceinline__ void load8(const uint32_t *base, int i0, int n, bool vec_ok, uint32_t (&out)[8])
+// How a row lies in its array: words from the last 16-byte boundary to its start, and words from its start to the
+// array's end (rows are packed, so a row of odd length shifts the next one's alignment).
+struct RowPlace {
+    int shift;
+    long long avail, total;
+};
+__device__ __forceinline__ RowPlace row_place(int row, int rows, int n)
 {
-    if (vec_ok && i0 + 7 < n) {
-        const uint4 a = *reinterpret_cast<const uint4 *>(base + i0);
-        const uint4 b = *reinterpret_cast<const uint4 *>(base + i0 + 4);
-        out[0] = a.x; out[1] = a.y; out[2] = a.z; out[3] = a.w;
-        out[4] = b.x; out[5] = b.y; out[6] = b.z; out[7] = b.w;
+    RowPlace p;
+    p.shift = (int)(((long long)row * n) & 3);
+    p.avail = (long long)(rows - row) * n;
+    p.total = (long long)rows * n;
+    return p;
+}
+
+// The thread's 8 consecutive words starting at token i0 (a multiple of 8); the caller masks those at or beyond n.  A
+// shifted row is read as the three aligned 16-byte pieces around the eight words (they lie inside the array: in this row
+// or its neighbours); single words only where a piece would cross the array's end.  (n 20011 against 20000, all eight
+// kernels: 44.5 / 38 us when a shifted row was read word by word.)
+__device__ __forceinline__ void load8(const uint32_t *base, int i0, int n, RowPlace at, uint32_t (&out)[8])
+{
+    if (i0 + 7 < n && i0 + 11 - at.shift < at.avail) {
+        const uint4 *p = reinterpret_cast<const uint4 *>(base + i0 - at.shift);
+        const uint4 a = p[0], b = p[1];
+        uint4 c = make_uint4(0u, 0u, 0u, 0u);
+        if (at.shift) c = p[2]; // uniform
+        const uint32_t w[12] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, c.x, c.y, c.z, c.w};
+        const uint32_t odd = (at.shift & 1) ? 0xFFFFFFFFu : 0u, two = (at.shift & 2) ? 0xFFFFFFFFu : 0u;
+        uint32_t x[10];
+#pragma unroll
+        for (int j = 0; j < 10; ++j) x[j] = (w[j] & ~odd) | (w[j + 1] & odd);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) out[j] = (x[j] & ~two) | (x[j + 2] & two);
     } else {
 #pragma unroll
         for (int j = 0; j < 8; ++j) out[j] = (i0 + j < n) ? base[i0 + j] : 0u;
@@ -203,10 +228,9 @@ __global__ __launch_bounds__(SEL_THREADS) void select_hist_kernel(SelArgs A)
     for (int b = threadIdx.x; b < SEL_BINS; b += SEL_THREADS) sh.hist[b] = 0u;
     __syncthreads();
     const uint32_t *src = (STAGE == 0 ? A.attn : A.keys2) + (size_t)head * A.n;
-    const bool vec_ok = (A.n & 3) == 0;
     const int i0 = slice * SEL_SLICE + threadIdx.x * SEL_PER_THREAD;
     uint32_t w[8];
-    load8(src, i0, A.n, vec_ok, w);
+    load8(src, i0, A.n, row_place(head, gridDim.y, A.n), w);
     // runs of equal digits inside a thread's 8 tokens are merged into one atomic
     uint32_t run_digit = 0u, run_len = 0u, n_above = 0u;
 #pragma unroll
@@ -289,8 +313,9 @@ __global__ __launch_bounds__(SEL_THREADS) void select_mark_kernel(SelArgs A)
     const bool vec_ok = (A.n & 3) == 0;
     const int i0 = slice * SEL_SLICE + threadIdx.x * SEL_PER_THREAD;
     uint32_t a[8], c[8];
-    load8(A.attn + (size_t)head * A.n, i0, A.n, vec_ok, a);
-    load8(A.crit + (size_t)head * A.n, i0, A.n, vec_ok, c);
+    const RowPlace at = row_place(head, gridDim.y, A.n);
+    load8(A.attn + (size_t)head * A.n, i0, A.n, at, a);
+    load8(A.crit + (size_t)head * A.n, i0, A.n, at, c);
     bool gt[8], tie[8];
     uint32_t n_tie = 0u;
 #pragma unroll
@@ -389,10 +414,9 @@ __global__ __launch_bounds__(SEL_THREADS) void select_write_kernel(SelArgs A)
     }
     tie_base = carry;
 
-    const bool vec_ok = (A.n & 3) == 0;
     const int i0 = slice * SEL_SLICE + threadIdx.x * SEL_PER_THREAD;
     uint32_t key[8];
-    load8(A.keys2 + (size_t)head * A.n, i0, A.n, vec_ok, key);
+    load8(A.keys2 + (size_t)head * A.n, i0, A.n, row_place(head, gridDim.y, A.n), key);
     bool sel[8], tie[8];
     uint32_t n_tie = 0u;
 #pragma unroll
@@ -531,22 +555,42 @@ __device__ __forceinline__ void row_threshold(RowShared &sh, const uint32_t (&ke
     fit = rest;
 }
 
+// Keys a workgroup's quads have to cover: a row of odd length may begin up to three words into its first quad.
+static int row_span(int n) { return n + (n & 3 ? 3 : 0); }
+
 __device__ __forceinline__ int row_token(int j) { return ((j >> 2) * ROW_THREADS + (int)threadIdx.x) * 4 + (j & 3); }
 
-// This thread's keys of a row; tokens past the row re-read its end.
+// This thread's keys of a row: key j is token row_token(j) - at.shift, so that every quad is 16-byte aligned (the first may
+// begin in the row before, the last end in the row behind: the caller masks tokens outside 0 .. n-1).  Every load is
+// unconditional; quads behind the row's last, or behind the array's last whole one, re-read that.  Up to three words at
+// the array's end are outside its whole quads and are read one by one.
 template <int KPT>
-__device__ __forceinline__ void row_load(const uint32_t *row, int n, uint32_t (&key)[KPT])
+__device__ __forceinline__ void row_load(const uint32_t *row, int n, RowPlace at, uint32_t (&key)[KPT])
 {
+    if (at.total < 4) { // (uniform) no whole quad
+#pragma unroll
+        for (int j = 0; j < KPT; ++j) {
+            const int i = row_token(j) - at.shift;
+            key[j] = i >= 0 && i < n ? row[i] : 0u;
+        }
+        return;
+    }
+    const int row_last = ((n - 1 + at.shift) & ~3) - at.shift;                       // start of the quad that ends the row
+    const long long whole_end = ((at.avail + at.shift) & ~3ll) - at.shift;           // end of the array's last whole quad
+    const int last = (int)min((long long)row_last, whole_end - 4);
 #pragma unroll
     for (int q = 0; q < KPT / 4; ++q) {
-        const int i0 = (q * ROW_THREADS + (int)threadIdx.x) * 4;
-        if ((n & 3) == 0) { // a quad is inside or outside as a whole, and 16-byte aligned
-            const uint4 a = *reinterpret_cast<const uint4 *>(row + min(i0, n - 4));
-            key[4 * q] = a.x; key[4 * q + 1] = a.y; key[4 * q + 2] = a.z; key[4 * q + 3] = a.w;
-        } else {
+        const uint4 a = *reinterpret_cast<const uint4 *>(row + min(row_token(4 * q) - at.shift, last));
+        key[4 * q] = a.x; key[4 * q + 1] = a.y; key[4 * q + 2] = a.z; key[4 * q + 3] = a.w;
+    }
+    if (whole_end < n) { // uniform: the array's last row
 #pragma unroll
-            for (int e = 0; e < 4; ++e) key[4 * q + e] = row[min(i0 + e, n - 1)];
-        }
+        for (int q = 0; q < KPT / 4; ++q)
+            if (row_token(4 * q) - at.shift == (int)whole_end) {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if ((int)whole_end + e < n) key[4 * q + e] = row[(int)whole_end + e];
+            }
     }
 }
 
@@ -593,12 +637,13 @@ __global__ __launch_bounds__(ROW_THREADS) void select_row_kernel(SelArgs A)
     __shared__ __attribute__((aligned(16))) RowShared sh;
     const int head = blockIdx.x;
     const uint32_t *attn = A.attn + (size_t)head * A.n, *crit = A.crit + (size_t)head * A.n;
-    const bool vec_ok = (A.n & 3) == 0;
+    const RowPlace at = row_place(head, gridDim.x, A.n);
+    auto token = [&](int j) { return row_token(j) - at.shift; };
     uint32_t key1[KPT], key2[KPT];
     // both rows are requested at the start; the longest rows would not fit the registers twice and take crit later
     constexpr bool LATE = KPT > 16;
-    row_load<KPT>(attn, A.n, key1);
-    if (!LATE) row_load<KPT>(crit, A.n, key2);
+    row_load<KPT>(attn, A.n, at, key1);
+    if (!LATE) row_load<KPT>(crit, A.n, at, key2);
     int B, b1, b2, kept;
     head_budget(A, head, B, b1, b2, kept);
     for (int b = threadIdx.x * 4; b < SEL_BINS * 4; b += ROW_THREADS * 4) *reinterpret_cast<uint4 *>(&sh.hist[b]) = make_uint4(0u, 0u, 0u, 0u);
@@ -608,7 +653,7 @@ __global__ __launch_bounds__(ROW_THREADS) void select_row_kernel(SelArgs A)
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
         key1[j] = order_key(key1[j]);
-        rank_ok |= (row_token(j) < A.n_rank ? 1u : 0u) << j;
+        rank_ok |= (token(j) >= 0 && token(j) < A.n_rank ? 1u : 0u) << j;
     }
     uint32_t taken = 0u; // stage 1 and the kept window
     if (b1 > 0) { // uniform over the workgroup, as everything derived from the budget
@@ -620,11 +665,11 @@ __global__ __launch_bounds__(ROW_THREADS) void select_row_kernel(SelArgs A)
         row_threshold<KPT>(sh, key1, live, (uint32_t)b1, tau, fit, all_fit);
         taken = row_above<KPT>(sh, key1, rank_ok, tau, fit, all_fit);
     }
-    if (LATE) row_load<KPT>(crit, A.n, key2);
+    if (LATE) row_load<KPT>(crit, A.n, at, key2);
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
         key2[j] = order_key(key2[j]);
-        if (row_token(j) >= A.n - kept && row_token(j) < A.n) taken |= 1u << j;
+        if (token(j) >= A.n - kept && token(j) < A.n) taken |= 1u << j;
         if ((taken >> j) & 1u) key2[j] = SEL_TAKEN;
     }
     // the stage-2 keys with stage-1 entries marked are what the diagnostics read back
@@ -632,16 +677,17 @@ __global__ __launch_bounds__(ROW_THREADS) void select_row_kernel(SelArgs A)
     uint32_t marked = 0u;
 #pragma unroll
     for (int q = 0; q < QUADS; ++q) {
-        const int i0 = (q * ROW_THREADS + (int)threadIdx.x) * 4;
-        if (vec_ok) {
-            if (i0 < A.n) *reinterpret_cast<uint4 *>(k2 + i0) = make_uint4(key2[4 * q], key2[4 * q + 1], key2[4 * q + 2], key2[4 * q + 3]);
+        const int i0 = token(4 * q); // keys2 starts on a 16-byte boundary as the scores do: its rows are shifted alike
+        if (i0 >= 0 && i0 + 3 < A.n) {
+            *reinterpret_cast<uint4 *>(k2 + i0) = make_uint4(key2[4 * q], key2[4 * q + 1], key2[4 * q + 2], key2[4 * q + 3]);
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (i0 + e < A.n) k2[i0 + e] = key2[4 * q + e];
+                if (i0 + e >= 0 && i0 + e < A.n) k2[i0 + e] = key2[4 * q + e];
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) marked |= (key2[4 * q + e] == SEL_TAKEN && i0 + e < A.n ? 1u : 0u) << (4 * q + e);
+        for (int e = 0; e < 4; ++e)
+            marked |= (key2[4 * q + e] == SEL_TAKEN && i0 + e >= 0 && i0 + e < A.n ? 1u : 0u) << (4 * q + e);
     }
     uint32_t sel = marked;
     if (b2 > 0) {
@@ -665,7 +711,7 @@ __global__ __launch_bounds__(ROW_THREADS) void select_row_kernel(SelArgs A)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             if ((sel >> (4 * q + e)) & 1u) {
-                if (pos < (uint32_t)A.max_budget) out[pos] = row_token(4 * q + e);
+                if (pos < (uint32_t)A.max_budget) out[pos] = token(4 * q + e);
                 ++pos;
             }
         before += (total[q >> 1] >> (16 * (q & 1))) & 0xFFFFu;
@@ -735,12 +781,13 @@ hipError_t launch_select_rows(int heads, int n, int protect, const float *attn, 
                               const int32_t *budget, float alpha, int max_budget, int32_t *idx, int32_t *count,
                               uint32_t *keys2, uint32_t *scratch, hipStream_t s)
 {
-    if (n <= SEL_ROW_MAX) {
+    const int span = row_span(n);
+    if (span <= SEL_ROW_MAX) {
         const SelArgs A = make_sel_args(heads, n, protect, attn, crit, budget, alpha, max_budget, idx, count, keys2, scratch);
         const dim3 grid(heads), block(ROW_THREADS);
-        if (n <= 4 * ROW_THREADS) hipLaunchKernelGGL(select_row_kernel<4>, grid, block, 0, s, A);
-        else if (n <= 8 * ROW_THREADS) hipLaunchKernelGGL(select_row_kernel<8>, grid, block, 0, s, A);
-        else if (n <= 16 * ROW_THREADS) hipLaunchKernelGGL(select_row_kernel<16>, grid, block, 0, s, A);
+        if (span <= 4 * ROW_THREADS) hipLaunchKernelGGL(select_row_kernel<4>, grid, block, 0, s, A);
+        else if (span <= 8 * ROW_THREADS) hipLaunchKernelGGL(select_row_kernel<8>, grid, block, 0, s, A);
+        else if (span <= 16 * ROW_THREADS) hipLaunchKernelGGL(select_row_kernel<16>, grid, block, 0, s, A);
         else hipLaunchKernelGGL(select_row_kernel<24>, grid, block, 0, s, A);
         return hipGetLastError();
     }
@@ -762,8 +809,8 @@ hipError_t launch_select(const Dims &d, const float *attn, const float *crit, co
 // of Hkv * n keys: its threshold comes from the selection's stage-1 digits, and a head's share is the number of its
 // entries above the threshold plus those of its ties that still fit (ties go to lower entries first, i.e. to lower heads).
 // Only counts are needed, no membership and no index list: one launch where the row fits a workgroup, five otherwise
-// (clear, three digits, count) -- the whole selection and a binary search in its list took ten (eight heads x 20011: 52 us,
-// now XX).
+// (clear, three digits, count) -- the whole selection and a binary search in its list took ten (two rows of eight heads x 20011: 52 us
+// of kernels, now 27).
 struct AllocArgs {
     int32_t *budget_out; // [batch][Hkv]
     uint32_t *above;     // [batch][Hkv + 1]: entries above the threshold per head; the last word counts finished workgroups
@@ -777,14 +824,16 @@ __global__ __launch_bounds__(ROW_THREADS) void allocate_row_kernel(SelArgs A, Al
     __shared__ __attribute__((aligned(16))) RowShared sh;
     const int row = blockIdx.x;
     uint32_t key[KPT];
-    row_load<KPT>(A.attn + (size_t)row * A.n, A.n, key);
+    const RowPlace at = row_place(row, gridDim.x, A.n);
+    row_load<KPT>(A.attn + (size_t)row * A.n, A.n, at, key);
     for (int b = threadIdx.x * 4; b < SEL_BINS * 4; b += ROW_THREADS * 4) *reinterpret_cast<uint4 *>(&sh.hist[b]) = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     uint32_t inside = 0u, live = 0u;
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
         key[j] = order_key(key[j]);
-        inside |= (row_token(j) < A.n ? 1u : 0u) << j;
+        const int i = row_token(j) - at.shift;
+        inside |= (i >= 0 && i < A.n ? 1u : 0u) << j;
         live |= (key[j] != SEL_TAKEN ? 1u : 0u) << j;
     }
     uint32_t tau, fit;
@@ -800,7 +849,7 @@ __global__ __launch_bounds__(ROW_THREADS) void allocate_row_kernel(SelArgs A, Al
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             if (!((sel >> (4 * q + e)) & 1u)) continue;
-            const int g = row_token(4 * q + e) / L.n;
+            const int g = (row_token(4 * q + e) - at.shift) / L.n;
             if (g != g_run && run) { atomicAdd(&sh.hist[g_run], run); run = 0u; }
             g_run = g;
             ++run;
@@ -830,7 +879,7 @@ __global__ __launch_bounds__(SEL_THREADS) void allocate_count_kernel(SelArgs A, 
     const int slice = blockIdx.x, row = blockIdx.y;
     const int i0 = slice * SEL_SLICE + threadIdx.x * SEL_PER_THREAD;
     uint32_t w[8];
-    load8(A.attn + (size_t)row * A.n, i0, A.n, (A.n & 3) == 0, w);
+    load8(A.attn + (size_t)row * A.n, i0, A.n, row_place(row, gridDim.y, A.n), w);
     const uint32_t *st = A.state + (size_t)row * 2 * ST_WORDS;
     const uint32_t d0 = st[ST_D0], a0 = st[ST_A0], d1 = st[ST_D1], a1 = st[ST_A1];
     uint32_t d2, a2;
@@ -862,13 +911,16 @@ __global__ __launch_bounds__(SEL_THREADS) void allocate_count_kernel(SelArgs A, 
         if (cnt[0][g]) atomicAdd(above + g0 + g, cnt[0][g]);
         if (cnt[1][g]) atomicAdd(ties + g0 + g, cnt[1][g]);
     }
-    // release before the ticket, acquire after it, both at device scope; the counts are read past the L1
-    __threadfence();
+    // The workgroup's counts are in (the barrier), one thread releases them and draws the ticket at device scope; the last
+    // workgroup acquires and reads past the L1.
     __syncthreads();
-    if (threadIdx.x == 0) last = atomicAdd(above + L.Hkv, 1u) == gridDim.x - 1 ? 1u : 0u;
+    if (threadIdx.x == 0) {
+        __threadfence();
+        last = atomicAdd(above + L.Hkv, 1u) == gridDim.x - 1 ? 1u : 0u;
+        __threadfence();
+    }
     __syncthreads();
     if (!last) return; // uniform
-    __threadfence();
     uint32_t carry = 0u;
     for (int c0 = 0; c0 < L.Hkv; c0 += SEL_THREADS) { // heads in order: how many ties lie before each
         const int g = c0 + threadIdx.x;
@@ -907,11 +959,12 @@ hipError_t launch_allocate(const Dims &d, const float *attn, int total, float fl
     }
     const int N = d.Hkv * d.n;
     const SelArgs A = make_sel_args(d.batch, N, 0, attn, attn, nullptr, 1.0f, P, nullptr, nullptr, keys2, scratch);
-    if (N <= SEL_ROW_MAX && d.Hkv <= 4 * SEL_BINS) {
+    const int span = row_span(N);
+    if (span <= SEL_ROW_MAX && d.Hkv <= 4 * SEL_BINS) {
         const dim3 grid(d.batch), block(ROW_THREADS);
-        if (N <= 4 * ROW_THREADS) hipLaunchKernelGGL(allocate_row_kernel<4>, grid, block, 0, s, A, L);
-        else if (N <= 8 * ROW_THREADS) hipLaunchKernelGGL(allocate_row_kernel<8>, grid, block, 0, s, A, L);
-        else if (N <= 16 * ROW_THREADS) hipLaunchKernelGGL(allocate_row_kernel<16>, grid, block, 0, s, A, L);
+        if (span <= 4 * ROW_THREADS) hipLaunchKernelGGL(allocate_row_kernel<4>, grid, block, 0, s, A, L);
+        else if (span <= 8 * ROW_THREADS) hipLaunchKernelGGL(allocate_row_kernel<8>, grid, block, 0, s, A, L);
+        else if (span <= 16 * ROW_THREADS) hipLaunchKernelGGL(allocate_row_kernel<16>, grid, block, 0, s, A, L);
         else hipLaunchKernelGGL(allocate_row_kernel<24>, grid, block, 0, s, A, L);
         return hipGetLastError();
     }
