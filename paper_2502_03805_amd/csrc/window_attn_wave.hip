@@ -51,7 +51,8 @@ struct AttnArgs {
     int qbs;      // 32-row blocks of the window
     int hpw;      // query heads per wave (hpw * qbs <= AM_MAX_QB)
     int groups;   // ceil(G / hpw): workgroups over the same keys
-    int xc8;      // ceil(workgroups along the keys / 8)
+    int chunks;   // workgroups along the keys
+    int pairs;    // batch * kv heads * chunks
     int causal;   // window row w sees keys <= n - W + w only
     float c;      // scale * log2(e)
     int64_t ks0, ks1, ks2;
@@ -143,13 +144,12 @@ struct WaveJob {
 };
 __device__ __forceinline__ bool wave_job(const AttnArgs &A, int wave, WaveJob &J)
 {
-    // workgroups that read the same keys (the groups of heads) sit on one XCD, next to each other in launch order
+    // workgroups that read the same keys (the groups of heads) sit on one XCD, next to each other in launch order; the
+    // (kv head, chunk of ranges) pairs are dealt to the XCDs in turn, whatever their number
     const int L = blockIdx.x, xcd = L & 7;
-    int r = L >> 3;
-    const int group = r % A.groups;
-    r /= A.groups;
-    const int wg_chunk = (r % A.xc8) * 8 + xcd;
-    const int bh = r / A.xc8, Hkv = A.H / A.G;
+    const int group = (L >> 3) % A.groups, pair = (L >> 3) / A.groups * 8 + xcd;
+    const int bh = pair / A.chunks, wg_chunk = pair % A.chunks, Hkv = A.H / A.G;
+    if (pair >= A.pairs) return false;
     J.bi = bh / Hkv;
     J.g = bh % Hkv;
     // wave `range` of the head takes key blocks range, range + ranges, range + 2 * ranges, ...: at any time the
@@ -370,16 +370,24 @@ bool attn_wave_supported(const Dims &d)
            ((int64_t)(d.n - 1) * d.ks[2] + d.dh) * 2 < ((int64_t)1 << 31);
 }
 
-// Keys per wave (it sets the number of waves per head).  Many keys spread a wave's fixed cost (its query fragments:
-// up to 32 KiB) over more key blocks; few give the chip enough waves (it holds 8 per CU, 2048 in all).  Measured
-// on the 5:1 group with a 64-row window at a 128K context: 1024 keys per wave is the best (512 and 2048 are 4-7 %
-// slower, 256 is 14 % slower), so: 1024, halved while that leaves less than one full round of waves.
-static int attn_kpw(const Dims &d, int groups)
+// Keys per wave (they set the number of waves).  Many keys spread a wave's fixed cost (its query fragments, up to 32 KiB,
+// worth c keys) over more key blocks, few fill the chip: it has 1024 SIMDs, and a round's time goes with the waves of
+// the fullest one -- a little over one, two or three waves' time while it holds fewer than four, which do not cover each
+// other's waits.  The choice is the cheapest by that count (measured within 3 % of the best of the seven everywhere: 5:1 group
+// with a 64-row window, 2000 .. 131072 tokens; 4:1 group at d_h 64, 1500 .. 4 x 32768).
+static int attn_kpw(const Dims &d, int groups, int row_blocks)
 {
     const long long per_range = (long long)d.batch * d.Hkv * groups;
-    int kpw = 1024;
-    while (kpw > AM_MIN_KPW && per_range * ((d.n + kpw - 1) / kpw) < 2048) kpw >>= 1;
-    return kpw;
+    const int choices[] = {1024, 768, 512, 384, 256, 192, AM_MIN_KPW};
+    const double c = 35.0 + 35.0 * row_blocks;
+    int best = AM_MIN_KPW;
+    double least = 0.0;
+    for (int kpw : choices) {
+        const long long r = (per_range * ((d.n + kpw - 1) / kpw) + 1023) / 1024;
+        const double cost = (r == 1 ? 1.35 : r == 2 ? 2.2 : r == 3 ? 3.1 : (double)r) * (kpw + c);
+        if (least == 0.0 || cost < least) { least = cost; best = kpw; }
+    }
+    return best;
 }
 
 static AttnArgs make_args(const Dims &d, const void *q, const void *k)
@@ -388,23 +396,18 @@ static AttnArgs make_args(const Dims &d, const void *q, const void *k)
     A.q = (const bf16_t *)q; A.k = (const bf16_t *)k;
     A.H = d.H; A.G = d.G; A.n = d.n; A.W = d.W; A.causal = d.causal;
     A.qbs = (d.W + 31) / 32;
-    // Heads per wave: every wave runs all of its hpw * qbs row blocks (a last group with fewer heads works on zero
-    // queries for the rest), so hpw is the choice with the least wave work in all, a key block's own cost (its
-    // loads and fragment reads) counted like one row block's; ties go to the larger hpw (measured on the 5:1 group
-    // with a 64-row window: two heads per wave 1.5 % faster than one).
-    A.hpw = 1;
-    {
-        const int most = AM_MAX_QB / A.qbs < d.G ? AM_MAX_QB / A.qbs : d.G;
-        int best = 1 << 30;
-        for (int h = 1; h <= (most > 0 ? most : 1); ++h) {
-            const int cost = ((d.G + h - 1) / h) * (1 + h * A.qbs);
-            if (cost <= best) { best = cost; A.hpw = h; }
-        }
-    }
-    A.groups = (d.G + A.hpw - 1) / A.hpw;
-    const int kpw = attn_kpw(d, A.groups);
+    // Heads per wave: one (few registers, four waves per SIMD, the most waves for a short launch); two where a group's heads
+    // pair up and the launch is long enough to fill the chip anyway (half the key traffic).  Both sweeps, us, most heads
+    // that fit / one / two: 4:1 group, d_h 64: 8192 tokens 26.5 / 20.2 / 20.7, 4 x 8192 38.8 / 33.9 / 34.7, 4 x 32768 84.3 /
+    // 86.0 / 80.4; 5:1 group with a 64-row window (two fit, the sixth slot idle): 8192 tokens 45.7 / 37.3, 20000 80.2 / 64.6,
+    // 131072 242.6 / 241.8.
+    const bool pairs_up = d.G % 2 == 0 && 2 * A.qbs <= AM_MAX_QB;
+    A.hpw = pairs_up && (long long)d.batch * d.H * ((d.n + 511) / 512) >= 8192 ? 2 : 1;
+    A.groups = d.G / A.hpw;
+    const int kpw = attn_kpw(d, A.groups, A.hpw * A.qbs);
     A.ranges = (d.n + kpw - 1) / kpw;
-    A.xc8 = ((A.ranges + AM_WAVES - 1) / AM_WAVES + 7) / 8;
+    A.chunks = (A.ranges + AM_WAVES - 1) / AM_WAVES;
+    A.pairs = d.batch * d.Hkv * A.chunks;
     A.c = d.scale * AM_LOG2E;
     A.ks0 = d.ks[0]; A.ks1 = d.ks[1]; A.ks2 = d.ks[2];
     return A;
@@ -415,7 +418,7 @@ template <int DH>
 static void launch_sweep(const AttnArgs &A, const Dims &d, bool stats_pass, float *part, const float *stats, float *a_raw,
                          hipStream_t s)
 {
-    const dim3 grid((unsigned)(8 * A.groups * A.xc8 * d.batch * d.Hkv)), block(64 * AM_WAVES);
+    const dim3 grid((unsigned)(8 * A.groups * ((A.pairs + 7) / 8))), block(64 * AM_WAVES);
     const int qb = A.hpw * A.qbs;
 #define CKV_SWEEP(QB)                                                                                             \
     if (stats_pass) hipLaunchKernelGGL((attn_stats_wave_kernel<DH, QB>), grid, block, 0, s, A, part);              \

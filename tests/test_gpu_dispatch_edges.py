@@ -228,3 +228,27 @@ def test_fp32_window_attention_against_float64(P, dh, H, Hkv, n, W, causal):
         err[name] = np.linalg.norm(got - ref) / np.linalg.norm(ref)
         assert np.abs(got - ref).max() <= 4e-6 * ref.max()
     assert err["matrix"] <= max(1.2 * err["vector"], 3e-7), err
+
+
+# ---- wave-private attention sweeps: heads and keys per wave ----------------------------------------------------------------------
+@pytest.mark.parametrize("dh,H,Hkv,W,b,ns", [
+    (64, 32, 8, 32, 1, (127, 129, 1000, 3000, 8193)), (64, 32, 8, 32, 4, (3001, 32768)), (128, 40, 8, 64, 1, (65, 2000, 8192, 20000)),
+    (64, 3, 3, 100, 3, (129, 2600)), (128, 14, 2, 33, 2, (511, 4100)),
+])
+def test_wave_sweeps_over_the_choices_of_heads_and_keys_per_wave(P, dh, H, Hkv, W, b, ns):
+    """fp32 logits of exact products and fp32 sums over the window: 4e-6 of the largest score."""
+    import torch
+    for n in ns:
+        g = torch.Generator(device="cuda").manual_seed(n)
+        q, k = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((b, H, W, dh), (b, Hkv, n, dh)))
+        cfg = CONFIGS["llama32k"].with_(n_q_heads=H, n_kv_heads=Hkv, head_dim=dh, d_model=32, window=W, n_ctx=n, batch=b, pool_kernel=1)
+        desc = cfg_desc(P, cfg, flags=P.CKV_ATTN_ONLY)
+        attn = torch.empty((b, Hkv, n), dtype=torch.float32, device="cuda")
+        crit = torch.empty_like(attn)
+        ws = torch.empty(P.workspace_bytes(desc, 1), dtype=torch.uint8, device="cuda")
+        P.criticalkv_score(desc, q, k, None, None, attn, crit, None, workspace=ws)
+        for bi, gi in ((0, 0), (b - 1, Hkv - 1)):
+            ref = 0
+            for h in range(gi * H // Hkv, (gi + 1) * H // Hkv):
+                ref = ref + torch.softmax(q[bi, h].double() @ k[bi, gi].double().t() / dh ** 0.5, -1).mean(0) * Hkv / H
+            assert (attn[bi, gi].double() - ref).abs().max() <= 4e-6 * ref.max(), (n, bi, gi)
