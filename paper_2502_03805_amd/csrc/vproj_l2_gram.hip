@@ -47,19 +47,28 @@ __device__ __forceinline__ bf16_t f32_to_bf16_rne(float x)
 // lies near a tie of G_hi's rounding would then move between the two parts of the stored constant.
 //
 // Work split: a chain runs over a whole slice, so the blocks are what is dealt out: 40 blocks of 16 x 16 per (head,
-// slice), 20 per workgroup, two per wave (one accumulator chain each; five per wave leave a SIMD with one wave, which
-// does not cover its own waits: 47 us instead of 38).  The workgroup's tile, 128 rows x 64 columns of the
-// canonical W_O (rows contiguous along d_model), sits in LDS with each row's even words before its odd ones, so that a
-// lane's values of 16 columns are one 16-byte read (single words: 56 us instead of 47, both with five blocks per wave), at a pitch of 36 words (the 16 rows
-// of a read start on 16 different bank groups); the next two tiles are in registers meanwhile.  Bound by the fp32 matrix rate (157 TFLOP/s nominal;
-// 2.7 GFLOP at 32 heads and d_model 4096 are 17 us; measured 38 us).  With fp32 products on the vector ALUs from the output-major layout it
-// took 229 us, and a layout change of 21 us before it.
+// slice), 20 per workgroup, runs of two or three per wave (one accumulator chain each).  The workgroup's tile, 128 rows x 64
+// columns of the canonical W_O (rows contiguous along d_model), sits in LDS with each row's even words before its odd ones,
+// so that a lane's values of 16 columns are one 16-byte read, at a pitch of 36 words (the 16 rows of a read start on 16
+// different bank groups); the next two tiles are in registers meanwhile.
+// Bound by the fp32 matrix rate (157 TFLOP/s nominal; 2.7 GFLOP at 32 heads and d_model 4096 are 17 us) and the operand
+// reads under it: 28 us.  Before, on the way here: fp32 products on the vector ALUs from the output-major layout 229 us
+// and a layout change of 21 us before it; single words instead of 16-byte reads 56; five blocks per wave, one wave per
+// SIMD, 47; two per wave, ten waves (six blocks on the fullest SIMD, an A read per block) 34.
 constexpr int GP_CHUNK = 64;                   // columns per LDS tile
 constexpr int GP_HALF = GP_CHUNK / 4;          // words of a row that lanes with k = 0, 1 read (the others read the rest)
 constexpr int GP_PITCH = 2 * GP_HALF + 4;      // words per row
-constexpr int GP_WAVES = 10;                   // waves per workgroup
-constexpr int GP_BLOCKS = 2;                   // 16 x 16 blocks per wave
-constexpr int GP_STAGERS = 512;                // threads that move the tile, two 16-byte pieces each
+constexpr int GP_WAVES = 8;                    // waves per workgroup; the threads move two 16-byte pieces of a tile each
+constexpr int GP_BLOCKS = 3;                   // 16 x 16 blocks per wave at most
+
+// Runs of blocks in one block row i (16 rows of G; it has (i | 1) + 1 blocks, up to the end of its 32 x 32 diagonal block):
+// eight runs of three and eight of two make up the 40.  A workgroup takes four of each, its waves 0-3 the runs of three
+// and 4-7 those of two: waves w and w + 4 share a SIMD, which so gets five blocks.  A run reads its A operand once.
+struct GramRun { int8_t i, j; };
+__device__ constexpr GramRun GP_RUNS[2][GP_WAVES] = {
+    {{4, 0}, {4, 3}, {5, 0}, {5, 3}, {0, 0}, {1, 0}, {2, 0}, {2, 2}},
+    {{6, 0}, {6, 3}, {7, 0}, {7, 3}, {3, 0}, {3, 2}, {6, 6}, {7, 6}},
+};
 
 __global__ __launch_bounds__(64 * GP_WAVES) void gram_partial_kernel(const bf16_t *__restrict__ w_o, float *__restrict__ partial, int dm)
 {
@@ -68,39 +77,24 @@ __global__ __launch_bounds__(64 * GP_WAVES) void gram_partial_kernel(const bf16_
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
     const int cols = dm / GL_SLICES; // host guarantees dm % (GL_SLICES * GP_CHUNK) == 0
-    // blocks in row order: block row i (16 rows of G) has (i | 1) + 1 blocks, up to the end of its 32 x 32 diagonal block
-    int bi[GP_BLOCKS], bj[GP_BLOCKS];
-    {
-        int at = (blockIdx.z * GP_WAVES + wave) * GP_BLOCKS, i = 0;
-#pragma unroll
-        for (int x = 0; x < GP_BLOCKS; ++x) {
-            int left = x == 0 ? at : bj[x - 1] + 1;
-            while (left > (i | 1)) { left -= (i | 1) + 1; ++i; }
-            bi[x] = i;
-            bj[x] = left;
-        }
-    }
-    int aoff[GP_BLOCKS], boff[GP_BLOCKS]; // word of this lane's row inside the tile, for k = lane / 16 of the first four columns
-#pragma unroll
-    for (int x = 0; x < GP_BLOCKS; ++x) {
-        aoff[x] = (bi[x] * 16 + l16) * GP_PITCH + (kg >> 1) * GP_HALF;
-        boff[x] = (bj[x] * 16 + l16) * GP_PITCH + (kg >> 1) * GP_HALF;
-    }
+    const int bi = GP_RUNS[blockIdx.z][wave].i, bj = GP_RUNS[blockIdx.z][wave].j;
+    const bool three = wave < GP_WAVES / 2; // uniform over the wave
+    // word of this lane's row inside the tile, for k = lane / 16 of the first four columns; the run's blocks follow each other
+    const int aoff = (bi * 16 + l16) * GP_PITCH + (kg >> 1) * GP_HALF;
+    const int boff = (bj * 16 + l16) * GP_PITCH + (kg >> 1) * GP_HALF;
     // odd columns are the upper halves of their words; a bf16 value is the upper half of its fp32
     const uint32_t pick = (kg & 1) ? 0x07060C0Cu : 0x05040C0Cu;
     auto value = [&](uint32_t w) { return __uint_as_float(__builtin_amdgcn_perm(w, 0u, pick)); };
 
     // staging: 8 pieces per row; two tiles are in flight in registers while a third is worked on
-    const bool stager = wave < GP_STAGERS / 64; // uniform over the wave
-    const bf16_t *src = w_o + ((size_t)h * GL_DH + (threadIdx.x >> 3) % (GL_DH / 2)) * dm + slice * cols + (threadIdx.x & 7) * 8;
+    const bf16_t *src = w_o + ((size_t)h * GL_DH + (threadIdx.x >> 3)) * dm + slice * cols + (threadIdx.x & 7) * 8;
     const int tiles = cols / GP_CHUNK; // even: d_model is a multiple of 512
-    auto fetch = [&](int t, uint4 (&piece)[2]) {
+    auto fetch = [&](int t, uint4 (&piece)[2]) __attribute__((always_inline)) {
         const int c0 = min(t, tiles - 1) * GP_CHUNK;
 #pragma unroll
         for (int j = 0; j < 2; ++j) piece[j] = *reinterpret_cast<const uint4 *>(src + (size_t)j * (GL_DH / 2) * dm + c0);
     };
-    auto stash = [&](uint32_t *to, const uint4 (&piece)[2]) {
-        if (!stager) return;
+    auto stash = [&](uint32_t *to, const uint4 (&piece)[2]) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             uint32_t *p = to + (j * (GL_DH / 2) + (threadIdx.x >> 3)) * GP_PITCH + (threadIdx.x & 7) * 2;
@@ -111,24 +105,28 @@ __global__ __launch_bounds__(64 * GP_WAVES) void gram_partial_kernel(const bf16_
     f32x4 acc[GP_BLOCKS];
 #pragma unroll
     for (int x = 0; x < GP_BLOCKS; ++x) acc[x] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto work = [&](const uint32_t *cur) {
+    auto run = [&](auto blocks_c, const uint32_t *cur) __attribute__((always_inline)) {
+        constexpr int BLOCKS = decltype(blocks_c)::value;
 #pragma unroll
         for (int q = 0; q < GP_HALF / 4; ++q) { // 16 columns: four words per lane and operand, four steps of the chains
-            uint4 a[GP_BLOCKS], b[GP_BLOCKS];
+            const uint4 a = *reinterpret_cast<const uint4 *>(cur + aoff + 4 * q);
+            uint4 b[BLOCKS];
 #pragma unroll
-            for (int x = 0; x < GP_BLOCKS; ++x) {
-                a[x] = *reinterpret_cast<const uint4 *>(cur + aoff[x] + 4 * q);
-                b[x] = *reinterpret_cast<const uint4 *>(cur + boff[x] + 4 * q);
-            }
+            for (int x = 0; x < BLOCKS; ++x) b[x] = *reinterpret_cast<const uint4 *>(cur + boff + x * 16 * GP_PITCH + 4 * q);
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
+            for (int k = 0; k < 4; ++k) {
+                const float av = value(k == 0 ? a.x : k == 1 ? a.y : k == 2 ? a.z : a.w);
 #pragma unroll
-                for (int x = 0; x < GP_BLOCKS; ++x) {
-                    const uint32_t wa = k == 0 ? a[x].x : k == 1 ? a[x].y : k == 2 ? a[x].z : a[x].w;
+                for (int x = 0; x < BLOCKS; ++x) {
                     const uint32_t wb = k == 0 ? b[x].x : k == 1 ? b[x].y : k == 2 ? b[x].z : b[x].w;
-                    acc[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(value(wa), value(wb), acc[x], 0, 0, 0);
+                    acc[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, value(wb), acc[x], 0, 0, 0);
                 }
+            }
         }
+    };
+    auto work = [&](const uint32_t *cur) __attribute__((always_inline)) {
+        if (three) run(std::integral_constant<int, 3>{}, cur);
+        else run(std::integral_constant<int, 2>{}, cur);
     };
     uint4 even[2], odd[2]; // pieces of the next even and odd tile
     fetch(0, even);
@@ -147,9 +145,11 @@ __global__ __launch_bounds__(64 * GP_WAVES) void gram_partial_kernel(const bf16_
     }
     float *dst = partial + ((size_t)h * GL_SLICES + slice) * GL_DH * GL_DH;
 #pragma unroll
-    for (int x = 0; x < GP_BLOCKS; ++x)
+    for (int x = 0; x < GP_BLOCKS; ++x) {
+        if (x < 2 || three)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) dst[(bi[x] * 16 + 4 * kg + v) * GL_DH + bj[x] * 16 + l16] = acc[x][v];
+            for (int v = 0; v < 4; ++v) dst[(bi * 16 + 4 * kg + v) * GL_DH + (bj + x) * 16 + l16] = acc[x][v];
+    }
 }
 
 // G = sum of the slices (fixed order), folded onto its lower block triangle, split into hi + lo bf16;
