@@ -452,25 +452,45 @@ __global__ __launch_bounds__(SEL_THREADS) void select_write_kernel(SelArgs A)
 // The whole selection of a head in one launch: a thread keeps KPT keys of both score arrays in registers (tokens
 // (j * 1024 + thread) * 4 + e: every load is 16 bytes per lane), the digit histograms and prefix sums live in LDS.
 // The same digits, thresholds and tie order as the sliced kernels below, so the result is the same set.
-//   * a digit's histogram has four copies, interleaved (bin * 4 + lane % 4): scores crowd into few bins, and the lanes of
-//     an LDS atomic that hit one address are served one after the other
+//   * a digit's histogram has several copies, interleaved (bin * copies + lane % copies): scores crowd into few bins, and
+//     the lanes of an LDS atomic that hit one address are served one after the other.  Summing and clearing them costs too:
+//     two copies for rows of up to 8192 keys, four for longer ones (1024 / 8192 / 24576 keys, us: two 9.9 / 13.5 / 27.6, four
+//     10.9 / 14.3 / 27.0, eight 17 / 20 / 32)
 //   * the thread that sums a bin also clears it, so a digit costs three barriers
 //   * ties are ranked only when the threshold's ties do not all fit
 //
-// What bounds it: instruction issue of one CU (about 5 vector instructions and an LDS atomic per key and digit), so the
-// time grows with the row while the sliced kernels cost seven launch boundaries whatever its length.  Eight heads, us, sliced /
-// one workgroup: n 512 34.8 / 10.6, 3072 36.3 / 10.7, 8192 36.6 / 15.2, 16384 37.1 / 21.2, 24576 36 / 29.9, 32768 36 / 38.4: rows
-// of up to 24576 keys are taken whole.  (Merging runs of equal digits into one atomic, as the sliced kernels do, costs more
-// instructions than it saves atomics here: 8192 keys 18.5 instead of 17.3 us.)
+// What bounds it: at short rows the six digits' barriers (about 0.9 us each, and 3 us for a launch that only loads and
+// stores); at long ones instruction issue of one CU (about 5 vector instructions and an LDS atomic per key and digit), so
+// the time grows with the row while the sliced kernels cost eight launches whatever its length.  Eight heads, us, sliced / one
+// workgroup: n 512 34.8 / 8.9, 3072 36.3 / 9.4, 8192 36.6 / 12.7, 16384 37.1 / 19.4, 24576 36 / 25.2, 32768 36 / 38 (before the
+// waves' totals were summed by row shifts, which took 1.5 - 2 us off): rows of up to 24576 keys are taken whole.  (Merging
+// runs of equal digits into one atomic, as the sliced kernels do, costs more instructions than it saves atomics here: 8192
+// keys 18.5 instead of 17.3 us.)
 constexpr int SEL_ROW_MAX = 24576;
 constexpr int ROW_THREADS = 1024;
 constexpr int ROW_WAVES = ROW_THREADS / 64;
 
 struct RowShared {
-    uint32_t hist[SEL_BINS * 4];
+    uint32_t hist[SEL_BINS * 4]; // row_copies(KPT) of the four interleaved
     uint32_t wave_tot[4][ROW_WAVES];
     uint32_t digit, above, inside;
 };
+
+constexpr int row_copies(int kpt) { return kpt <= 8 ? 2 : 4; }
+
+// Sum of the totals of the waves before this one, and of all: lanes 0-15 of every row of lanes hold one total each.
+__device__ __forceinline__ uint32_t waves_before(const uint32_t (&wave_tot)[ROW_WAVES], uint32_t &total)
+{
+    static_assert(ROW_WAVES == 16, "one total per lane of a DPP row");
+    uint32_t x = wave_tot[threadIdx.x & 15];
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false); // row_shr:1, 2, 4, 8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    total = (uint32_t)__builtin_amdgcn_readlane((int)x, ROW_WAVES - 1);
+    return wave ? (uint32_t)__builtin_amdgcn_readlane((int)x, wave - 1) : 0u;
+}
 
 // Exclusive prefix sums in thread order of NP words at once (two 16-bit counts each); totals as well.
 template <int NP>
@@ -488,15 +508,8 @@ __device__ __forceinline__ void row_scan(RowShared &sh, const uint32_t (&x)[NP],
     __syncthreads();
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        uint32_t base = 0, tot = 0;
-#pragma unroll
-        for (int w = 0; w < ROW_WAVES; ++w) {
-            const uint32_t t = sh.wave_tot[p][w];
-            if (w < wave) base += t;
-            tot += t;
-        }
+        const uint32_t base = waves_before(sh.wave_tot[p], total[p]);
         excl[p] = base + incl[p] - x[p];
-        total[p] = tot;
     }
 }
 
@@ -506,7 +519,7 @@ template <int KPT>
 __device__ __forceinline__ void row_threshold(RowShared &sh, const uint32_t (&key)[KPT], uint32_t live, uint32_t want,
                                               uint32_t &tau, uint32_t &fit, bool &all_fit)
 {
-    constexpr int PER = SEL_BINS / ROW_THREADS;
+    constexpr int PER = SEL_BINS / ROW_THREADS, COPIES = row_copies(KPT);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint32_t prefix = 0u, pmask = 0u, rest = want;
 #pragma unroll
@@ -516,26 +529,30 @@ __device__ __forceinline__ void row_threshold(RowShared &sh, const uint32_t (&ke
 #pragma unroll
         for (int j = 0; j < KPT; ++j) {
             const bool on = ((live >> j) & 1u) && (key[j] & pmask) == prefix;
-            if (on) atomicAdd(&sh.hist[((key[j] >> shift) & mask) * 4 + (lane & 3)], 1u);
+            if (on) atomicAdd(&sh.hist[((key[j] >> shift) & mask) * COPIES + (lane & (COPIES - 1))], 1u);
         }
         __syncthreads();
         // bins in descending order, PER per thread
         uint32_t h[PER], local = 0u;
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
-            uint4 *bin = reinterpret_cast<uint4 *>(&sh.hist[(SEL_BINS - 1 - ((int)threadIdx.x * PER + j)) * 4]);
-            const uint4 c = *bin;
-            *bin = make_uint4(0u, 0u, 0u, 0u);
-            h[j] = c.x + c.y + c.z + c.w;
+            uint32_t *bin = &sh.hist[(SEL_BINS - 1 - ((int)threadIdx.x * PER + j)) * COPIES];
+            if constexpr (COPIES == 2) {
+                const uint2 c = *reinterpret_cast<const uint2 *>(bin);
+                *reinterpret_cast<uint2 *>(bin) = make_uint2(0u, 0u);
+                h[j] = c.x + c.y;
+            } else {
+                const uint4 c = *reinterpret_cast<const uint4 *>(bin);
+                *reinterpret_cast<uint4 *>(bin) = make_uint4(0u, 0u, 0u, 0u);
+                h[j] = c.x + c.y + c.z + c.w;
+            }
             local += h[j];
         }
         const uint32_t incl = wave_inclusive_scan(local);
         if (lane == 63) sh.wave_tot[0][wave] = incl;
         if (threadIdx.x == 0) { sh.digit = 0u; sh.above = 0u; sh.inside = 0u; }
         __syncthreads();
-        uint32_t run = incl - local;
-#pragma unroll
-        for (int w = 0; w < ROW_WAVES; ++w) run += w < wave ? sh.wave_tot[0][w] : 0u;
+        uint32_t all, run = waves_before(sh.wave_tot[0], all) + incl - local;
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             if (run < rest && rest <= run + h[j]) {
