@@ -63,21 +63,22 @@ __global__ __launch_bounds__(VM_THREADS, 2) void vproj_mfma_kernel(const bf16_t 
     static_assert(VM_LOADS * 2 == VM_CB * geo::LPC, "the next tile's loads go out during the first half of a tile");
     __shared__ __attribute__((aligned(1024))) char lds[2 * VM_TILE_BYTES];
     // XCD-aware work mapping.  Workgroups of a 1-D grid are handed to the 8 XCDs round-robin (workgroup L
-    // runs on XCD L % 8) and every XCD has its own 4 MiB L2.  An XCD gets consecutive (batch item, query head)
-    // pairs, i.e. heads of one kv group, and walks them two at a time: the two heads take turns on every row
-    // tile, so the second one finds the tile's V rows in that L2, and the workgroups resident on the XCD stream
+    // runs on XCD L % 8) and every XCD has its own 4 MiB L2.  An XCD gets an eighth of the (query head, row tile) items in
+    // head order, i.e. consecutive heads of one kv group, and walks the heads two at a time: the two take turns on every
+    // row tile, so the second one finds the tile's V rows in that L2, and the workgroups resident on the XCD stream
     // the same two 1 MiB W_O slices, which stay in L2 as well.  (Four heads in turn were measured slower: their
     // four slices evict each other.  Measured against one head at a time: same speed, half the L2 misses -- as
     // long as two slices leave room in L2: at d_model 5120 (2 x 1.25 MiB) pairing was 13 % slower, so the host
-    // pairs heads only up to d_model 4096.)
-    const int xcd = blockIdx.x & 7, k_in_xcd = blockIdx.x >> 3;
-    const int hpx = (heads + 7) >> 3;                    // heads per XCD
-    // pair = 1: two heads take turns on a row tile; pair = 0: one head at a time (its slice alone in L2)
-    const int member = pair ? (k_in_xcd & 1) : 0, pt = pair ? (k_in_xcd >> 1) : k_in_xcd;
-    const int in_xcd = (pair ? 2 : 1) * (pt / row_tiles) + member;
-    const int hb = xcd * hpx + in_xcd;                   // batch * H + head
-    if (in_xcd >= hpx || hb >= heads) return;
-    const int tile_x = pt % row_tiles;
+    // pairs heads only up to d_model 4096.  Dealing out whole heads left an XCD idle with 28 of them and half idle with 12:
+    // 32768 tokens 592 / 140 us, now 532 / 107.)
+    const int total = heads * row_tiles, per_xcd = (total + 7) >> 3;
+    const int k_in_xcd = blockIdx.x >> 3, item = (blockIdx.x & 7) * per_xcd + k_in_xcd;
+    if (k_in_xcd >= per_xcd || item >= total) return; // uniform over the workgroup
+    // pair = 1: heads 2p and 2p + 1 alternate over their row tiles (a last head without a partner runs alone)
+    const int first = pair ? item / (2 * row_tiles) * 2 : item / row_tiles, in_head = item - first * row_tiles;
+    const bool turns = pair && first + 1 < heads;
+    const int hb = first + (turns ? in_head & 1 : 0);    // batch * H + head
+    const int tile_x = turns ? in_head >> 1 : in_head;
     const int h = hb % H, bi = hb / H, g = h / G;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); // wave-uniform, kept in a scalar register
@@ -211,20 +212,19 @@ static void launch_rb(const Dims &d, const void *v, const void *w_t, float *vnor
     const int row_tiles = (d.n + rows_per_wg - 1) / rows_per_wg;
     const int heads = d.batch * d.H;
     const int pair = (size_t)2 * DH * d.dm * 2 <= ((size_t)2 << 20) ? 1 : 0; // two slices within 2 MiB
-    const int hpx = (heads + 7) / 8;
-    const long long wgs = 8ll * (pair ? 2 * ((hpx + 1) / 2) : hpx) * row_tiles; // 8 XCDs x heads (in pairs) x row tiles
+    const long long wgs = 8ll * (((long long)heads * row_tiles + 7) / 8); // an eighth of the (head, row tile) items per XCD
     hipLaunchKernelGGL((vproj_mfma_kernel<DH, RB>), dim3((unsigned)wgs), dim3(VM_THREADS), 0, s, (const bf16_t *)v,
                        (const bf16_t *)w_t, vnorm, d.H, d.G, d.n, d.dm, d.vs[0], d.vs[1], d.vs[2], row_tiles, heads, pair);
 }
 
 int cheapest_rounds(const Dims &d, int rows_per_block, double c2, double c1, const int *choices, int count)
 {
-    const long long heads_per_xcd = ((long long)d.batch * d.H + 7) / 8;
+    const long long heads = (long long)d.batch * d.H;
     int best = choices[0];
     double least = 0.0;
     for (int i = 0; i < count; ++i) {
         const int rb = choices[i], rows = rows_per_block * rb;
-        const long long wgs = heads_per_xcd * ((d.n + rows - 1) / rows), rest = wgs % 64;
+        const long long wgs = (heads * ((d.n + rows - 1) / rows) + 7) / 8, rest = wgs % 64;
         const double cost = (double)(wgs / 64) * (rb + c2) + (rest > 32 ? rb + c2 : rest > 0 ? 0.48 * rb + c1 : 0.0);
         if (i == 0 || cost < least) { least = cost; best = rb; }
     }

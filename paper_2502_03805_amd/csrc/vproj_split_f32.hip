@@ -131,13 +131,12 @@ __global__ __launch_bounds__(VS_THREADS, 2) void vproj_split_kernel(const float 
     using geo = SGeo<DH>;
     constexpr int KS = geo::KS, CB = VS_TN / 16;
     __shared__ __attribute__((aligned(1024))) char lds[2 * geo::TILE_BYTES];
-    // workgroup L runs on XCD L % 8; an XCD takes consecutive query heads one after the other, so that the workgroups
-    // resident on it stream the same head's parts out of its L2
-    const int xcd = blockIdx.x & 7, k_in_xcd = blockIdx.x >> 3;
-    const int hpx = (heads + 7) >> 3;
-    const int in_xcd = k_in_xcd / row_tiles, hb = xcd * hpx + in_xcd; // batch * H + head
-    if (in_xcd >= hpx || hb >= heads) return;                         // uniform over the workgroup
-    const int tile_x = k_in_xcd % row_tiles;
+    // workgroup L runs on XCD L % 8; an XCD takes an eighth of the (head, row tile) pairs in head order, so that the
+    // workgroups resident on it stream the same head's parts out of its L2, whatever the number of heads
+    const int total = heads * row_tiles, per_xcd = (total + 7) >> 3;
+    const int k_in_xcd = blockIdx.x >> 3, item = (blockIdx.x & 7) * per_xcd + k_in_xcd;
+    if (k_in_xcd >= per_xcd || item >= total) return;                 // uniform over the workgroup
+    const int hb = item / row_tiles, tile_x = item % row_tiles;       // batch * H + head
     const int h = hb % H, bi = hb / H, g = h / G;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -263,7 +262,7 @@ static void launch_project(const Dims &d, const void *v, const bf16_t *w3, float
 {
     const int rows_per_wg = VS_WAVES * RB * 16, row_tiles = (d.n + rows_per_wg - 1) / rows_per_wg;
     const int heads = d.batch * d.H;
-    const dim3 grid((unsigned)(8ll * ((heads + 7) / 8) * row_tiles)), block(VS_THREADS);
+    const dim3 grid((unsigned)(8ll * (((long long)heads * row_tiles + 7) / 8))), block(VS_THREADS);
     if (d.norm == CKV_NORM_L2)
         hipLaunchKernelGGL((vproj_split_kernel<DH, RB, true>), grid, block, 0, s, (const float *)v, w3, vnorm, d.H, d.G, d.n,
                            d.dm, d.vs[0], d.vs[1], d.vs[2], row_tiles, heads);

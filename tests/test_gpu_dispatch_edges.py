@@ -252,3 +252,38 @@ def test_wave_sweeps_over_the_choices_of_heads_and_keys_per_wave(P, dh, H, Hkv, 
             for h in range(gi * H // Hkv, (gi + 1) * H // Hkv):
                 ref = ref + torch.softmax(q[bi, h].double() @ k[bi, gi].double().t() / dh ** 0.5, -1).mean(0) * Hkv / H
             assert (attn[bi, gi].double() - ref).abs().max() <= 4e-6 * ref.max(), (n, bi, gi)
+
+
+# ---- work dealt to the XCDs: head counts that eight does not divide ---------------------------------------------------------
+@pytest.mark.parametrize("dtype,dh,H,Hkv,dm,b,n", [
+    ("bf16", 128, 28, 4, 128, 1, 1500), ("bf16", 128, 1, 1, 256, 1, 700), ("bf16", 128, 12, 2, 5120, 1, 450),
+    ("bf16", 64, 7, 7, 256, 3, 900), ("f32", 128, 20, 4, 64, 1, 600), ("f32", 64, 5, 1, 32, 1, 5000),
+])
+def test_magnitudes_over_head_counts(P, dtype, dh, H, Hkv, dm, b, n):
+    """L1 magnitudes of every head and row; fp32 sums: 2e-6 of the result."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(H * n)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    cfg = CONFIGS["llama32k"].with_(n_q_heads=H, n_kv_heads=Hkv, head_dim=dh, d_model=dm, n_ctx=n, dtype=dtype, window=8, batch=b)
+    q, k, v = (torch.randn(s, generator=g, device="cuda").to(dt) for s in ((b, H, 8, dh), (b, Hkv, n, dh), (b, Hkv, n, dh)))
+    w = torch.randn((H * dh, dm), generator=g, device="cuda").to(dt)
+    got = torch.from_numpy(score(P, cfg_desc(P, cfg), q, k, v, w)[2]).cuda()
+    for bi in range(b):
+        for h in range(H):
+            ref = (v[bi, h * Hkv // H].double() @ w[h * dh:(h + 1) * dh].double()).abs().sum(-1)
+            assert (got[bi, h].double() / ref - 1).abs().max() <= 2e-6, (bi, h)
+
+
+@pytest.mark.parametrize("H,Hkv,b,n", [(28, 4, 1, 3000), (2, 1, 1, 70), (12, 2, 3, 1111), (5, 5, 2, 9000)])
+def test_l2_magnitudes_over_head_counts(P, H, Hkv, b, n):
+    """The Gram form's split constant has a relative error of 2^-17 per entry: 2e-5 of a row's norm."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(H + n)
+    cfg = CONFIGS["llama32k"].with_(n_q_heads=H, n_kv_heads=Hkv, d_model=512, n_ctx=n, window=8, batch=b)
+    q, k, v = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((b, H, 8, 128), (b, Hkv, n, 128), (b, Hkv, n, 128)))
+    w = (0.02 * torch.randn((H * 128, 512), generator=g, device="cuda")).to(torch.bfloat16)
+    got = torch.from_numpy(score(P, cfg_desc(P, cfg, norm=2), q, k, v, w)[2]).cuda()
+    for bi in range(b):
+        for h in range(H):
+            ref = (v[bi, h * Hkv // H].double() @ w[h * 128:(h + 1) * 128].double()).square().sum(-1).sqrt()
+            assert (got[bi, h].double() / ref - 1).abs().max() <= 2e-5, (bi, h)
