@@ -197,13 +197,13 @@ __global__ __launch_bounds__(HEADS * 256, HEADS == 1 ? 2 : 1) void vproj_l2_resi
     constexpr int GR_HEADS = HEADS, GR_WAVES = 4 * HEADS;
     __shared__ __attribute__((aligned(1024))) char lds[GR_HEADS * 2 * GL_G_BYTES]; // per head: G_hi | G_lo, XOR-swizzled
     const int Hkv = H / G, hgroups = G / GR_HEADS; // (the launcher takes HEADS = 2 for even G only)
-    const int L = blockIdx.x, xcd = L & 7;
-    int r = L >> 3;
-    const int hl = (r % hgroups) * GR_HEADS;                 // first head of this workgroup inside its kv group
-    r /= hgroups;
-    const int range = r % ranges;
-    const int pair = (r / ranges) * 8 + xcd;
-    if (pair >= pairs) return; // uniform over the workgroup
+    // an XCD takes an eighth of the (kv head, range of rows) items; the workgroups of a kv group that share one are
+    // neighbours in launch order
+    const int items = pairs * ranges, per_xcd = (items + 7) >> 3;
+    const int hl = ((int)blockIdx.x >> 3) % hgroups * GR_HEADS; // first head of this workgroup inside its kv group
+    const int k_in_xcd = ((int)blockIdx.x >> 3) / hgroups, item = ((int)blockIdx.x & 7) * per_xcd + k_in_xcd;
+    if (k_in_xcd >= per_xcd || item >= items) return; // uniform over the workgroup
+    const int range = item % ranges, pair = item / ranges;
     const int bi = pair / Hkv, g = pair % Hkv, h = g * G + hl;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -364,14 +364,15 @@ hipError_t launch_vproj_l2_mfma(const Dims &d, const void *v, const void *gram, 
     // ranges of rows per workgroup of heads: eight waves per CU over the whole launch where the context allows it,
     // so that every workgroup is resident from the start (a kv group's workgroups then walk the same rows side by side)
     const int pairs = d.batch * d.Hkv;
-    const int per_range = 8 * ((pairs + 7) / 8) * (d.G / heads);
+    // (dealing whole kv heads to the XCDs used four of the eight with 4 kv heads: 28 query heads, 32768 tokens 75 us, now 42)
+    const int per_range = pairs * (d.G / heads);
     int ranges = (512 / heads) / per_range;
     const int most = (d.n + waves * GR_BLOCK_ROWS - 1) / (waves * GR_BLOCK_ROWS); // a block per wave at least
     ranges = ranges > most ? most : ranges;
     ranges = ranges < 1 ? 1 : ranges;
     int rows_per_range = (d.n + ranges - 1) / ranges;
     rows_per_range = (rows_per_range + GR_BLOCK_ROWS - 1) / GR_BLOCK_ROWS * GR_BLOCK_ROWS;
-    const dim3 grid((unsigned)(per_range * ranges)), block(waves * 64);
+    const dim3 grid((unsigned)(8 * ((pairs * ranges + 7) / 8) * (d.G / heads))), block(waves * 64);
     if (heads == 2)
         hipLaunchKernelGGL(vproj_l2_resident_kernel<2>, grid, block, 0, s, (const bf16_t *)v, (const bf16_t *)gram, vnorm,
                            d.H, d.G, d.n, d.vs[0], d.vs[1], d.vs[2], pairs, ranges, rows_per_range);
