@@ -52,7 +52,7 @@ __device__ __forceinline__ bf16_t f32_to_bf16_rne(float x)
 // so that a lane's values of 16 columns are one 16-byte read, at a pitch of 36 words (the 16 rows of a read start on 16
 // different bank groups); the next two tiles are in registers meanwhile.
 // Bound by the fp32 matrix rate (157 TFLOP/s nominal; 2.7 GFLOP at 32 heads and d_model 4096 are 17 us) and the operand
-// reads under it: 28 us.  Before, on the way here: fp32 products on the vector ALUs from the output-major layout 229 us
+// reads under it: 28 us in a chain of calls, 33 under the kernel trace.  Before, on the way here: fp32 products on the vector ALUs from the output-major layout 229 us
 // and a layout change of 21 us before it; single words instead of 16-byte reads 56; five blocks per wave, one wave per
 // SIMD, 47; two per wave, ten waves (six blocks on the fullest SIMD, an A read per block) 34.
 constexpr int GP_CHUNK = 64;                   // columns per LDS tile
