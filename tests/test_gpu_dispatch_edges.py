@@ -287,3 +287,16 @@ def test_l2_magnitudes_over_head_counts(P, H, Hkv, b, n):
         for h in range(H):
             ref = (v[bi, h * Hkv // H].double() @ w[h * 128:(h + 1) * 128].double()).square().sum(-1).sqrt()
             assert (got[bi, h].double() / ref - 1).abs().max() <= 2e-5, (bi, h)
+
+
+@pytest.mark.parametrize("heads,n", [(1, 1), (1, 2), (1, 3), (3, 1), (2, 2), (5, 1), (1, 5), (3, 3)])
+def test_select_and_allocate_on_a_few_keys_in_all(P, heads, n):
+    """Arrays with no whole 16-byte piece, and with one that crosses rows."""
+    from oracle import cpu_oracle as O
+    from test_gpu_parity import assert_select_exact, run_allocate
+    r = np.random.Generator(np.random.PCG64(10 * heads + n))
+    attn, crit = r.random((1, heads, n)).astype(np.float32), r.random((1, heads, n)).astype(np.float32)
+    for B in range(1, n + 1):
+        assert_select_exact(P, attn, crit, B, 0.5)
+    for total in range(0, heads * n + 1):
+        assert np.array_equal(run_allocate(P, attn, total, 0.25), O.allocate(attn.astype(np.float64), total, np.float32(0.25)))
