@@ -12,7 +12,8 @@
 //   project   the tiling of the bf16 kernel: a wave keeps RB blocks of 16 token rows (all three parts) as MFMA
 //             fragments, the head's parts stream through LDS in tiles of 32 columns (24 KiB at d_h 128, double
 //             buffered, direct buffer->LDS loads, 16-byte chunks swizzled), six MFMAs per (k-step, row block), the
-//             previous column block's |acc| drained under them.
+//             previous column block's |acc| drained under them.  Rows that meet an infinity or NaN are computed again
+//             from the fp32 operands (exact_rows), so that they get what fp32 products give.
 //
 // What bounds it: the matrix cores; six bf16 MFMAs per fp32 product still leave 2.7 times the rate of the fp32 MFMA
 // (157 TFLOP/s nominal).  Measured at 16 query heads over 4 kv heads, d_h 128, d_model 2048, 8192 tokens: the score call
@@ -36,15 +37,15 @@ constexpr int VS_PARTS = 3;
 #define LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
 // The three bf16 parts of x.  A value whose nearest bf16 is infinite (the last half step below FLT_MAX) takes the
-// truncated first part, and an infinity or NaN is its own first part with zeros behind it.
+// truncated first part.  An infinity or NaN has no such parts (its products with the other operand's parts would cancel or
+// meet zeros): it becomes a NaN, and the project kernel computes the rows that come out as NaN again, in fp32.
 __device__ __forceinline__ void split3(float x, uint32_t &p0, uint32_t &p1, uint32_t &p2)
 {
     const uint32_t u = __float_as_uint(x);
-    uint32_t h = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-    if ((h & 0x7F80u) == 0x7F80u || (u & 0x7F800000u) == 0x7F800000u)
-        h = (u >> 16) | ((u & 0x7FFFFFFFu) > 0x7F800000u ? 0x40u : 0u);
-    p0 = h & 0xFFFFu;
     const bool finite = (u & 0x7F800000u) != 0x7F800000u;
+    uint32_t h = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+    if ((h & 0x7F80u) == 0x7F80u) h = u >> 16;
+    p0 = finite ? h & 0xFFFFu : 0x7FC0u;
     const float r = finite ? x - __uint_as_float(p0 << 16) : 0.f;
     const uint32_t ur = __float_as_uint(r);
     p1 = (ur + 0x7FFFu + ((ur >> 16) & 1u)) >> 16;
@@ -122,8 +123,55 @@ struct SGeo {
     __host__ __device__ static constexpr int swz(int c) { return DH == 128 ? (c & 15) : ((c >> 1) & 7); }
 };
 
+template <bool L2> __device__ __forceinline__ void drain(float &to, float x) { to = L2 ? fmaf(x, x, to) : to + fabsf(x); }
+
+// The magnitudes of VS_EXACT neighbouring rows from the fp32 operands themselves, by one wave: a lane takes every 64th
+// column, one fma chain over d_h per row.  For rows with an operand that has no three parts: rare, so all that is asked of
+// it is the rate of the vector kernel.  The score call at 16 heads over 4 kv heads, d_model 2048, 8192 tokens: 2.55 ms with
+// the vector kernel; 0.30 here, 0.44 - 0.51 with one such row, 2.05 with one in every row.
+constexpr int VS_EXACT = 8;
+template <int DH, bool L2, bool OUT_IN>
+__device__ __forceinline__ void exact_rows(const float *vbase, int64_t vs2, int row, int n, const float *w, int64_t ldw, int dm,
+                                           float (&out)[VS_EXACT])
+{
+    const int lane = threadIdx.x & 63;
+    const float *v[VS_EXACT];
+#pragma unroll
+    for (int j = 0; j < VS_EXACT; ++j) {
+        v[j] = vbase + (int64_t)min(row + j, n - 1) * vs2;
+        out[j] = 0.f;
+    }
+    for (int c = lane; c < dm; c += 64) { // (d_model is a multiple of 32: half of the lanes may skip the last round)
+        float p[VS_EXACT];
+#pragma unroll
+        for (int j = 0; j < VS_EXACT; ++j) p[j] = 0.f;
+#pragma unroll 2
+        for (int t = 0; t < DH; t += 4) {
+            float x[4];
+            if (OUT_IN) { // [d_model][H * d_h]: this lane's column is contiguous
+                const float4 four = *reinterpret_cast<const float4 *>(w + c * ldw + t);
+                x[0] = four.x; x[1] = four.y; x[2] = four.z; x[3] = four.w;
+            } else {      // [H * d_h][d_model]: the lanes' columns are
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = w[(t + e) * ldw + c];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int j = 0; j < VS_EXACT; ++j) p[j] = fmaf(v[j][t + e], x[e], p[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < VS_EXACT; ++j) drain<L2>(out[j], p[j]);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int j = 0; j < VS_EXACT; ++j) out[j] += __shfl_xor(out[j], o);
+}
+
 template <int DH, int RB, bool L2>
-__global__ __launch_bounds__(VS_THREADS, 2) void vproj_split_kernel(const float *__restrict__ v, const bf16_t *__restrict__ w3,
+__global__ __launch_bounds__(VS_THREADS, 2) void vproj_split_kernel(const float *__restrict__ v, const float *__restrict__ w_o,
+                                                                    int out_in, const bf16_t *__restrict__ w3,
                                                                     float *__restrict__ vnorm, int H, int G, int n, int dm,
                                                                     int64_t vs0, int64_t vs1, int64_t vs2, int row_tiles,
                                                                     int heads)
@@ -198,7 +246,6 @@ __global__ __launch_bounds__(VS_THREADS, 2) void vproj_split_kernel(const float 
         for (int p = 0; p < VS_PARTS; ++p) read_b(lds, s, p);
 
     const int tiles = dm / VS_TN;
-    auto drain = [&](float &to, float x) { to = L2 ? fmaf(x, x, to) : to + fabsf(x); };
     auto tile_step = [&](auto buf_c, int t) {
         constexpr int BUF = decltype(buf_c)::value;
         const char *cur = lds + BUF * geo::TILE_BYTES;
@@ -227,7 +274,7 @@ __global__ __launch_bounds__(VS_THREADS, 2) void vproj_split_kernel(const float 
                     // the previous column block's products, spread over the k-steps
                     if (q < RB) {
 #pragma unroll
-                        for (int e = 0; e < 4 / KS; ++e) drain(sum[q][s * (4 / KS) + e], acc[pp ^ 1][q][s * (4 / KS) + e]);
+                        for (int e = 0; e < 4 / KS; ++e) drain<L2>(sum[q][s * (4 / KS) + e], acc[pp ^ 1][q][s * (4 / KS) + e]);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -248,27 +295,41 @@ __global__ __launch_bounds__(VS_THREADS, 2) void vproj_split_kernel(const float 
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) drain(sum[rb][j], acc[(CB - 1) & 1][rb][j]);
+        for (int j = 0; j < 4; ++j) drain<L2>(sum[rb][j], acc[(CB - 1) & 1][rb][j]);
         float x = (sum[rb][0] + sum[rb][1]) + (sum[rb][2] + sum[rb][3]);
         x += __shfl_xor(x, 16);
         x += __shfl_xor(x, 32);
         const int row = row0 + rb * 16 + l16;
-        if (kc == 0 && row < n) out[row] = L2 ? sqrtf(x) : x;
+        const bool lost = x != x; // an operand without three parts
+        if (kc == 0 && row < n && !lost) out[row] = L2 ? sqrtf(x) : x;
+        const uint32_t again = (uint32_t)__ballot(kc == 0 && row < n && lost); // (rows are the lanes 0 .. 15)
+#pragma unroll 1
+        for (int r8 = 0; r8 < 16; r8 += VS_EXACT) {
+            if (!((again >> r8) & ((1u << VS_EXACT) - 1u))) continue; // uniform over the wave
+            float exact[VS_EXACT];
+            const int first = row0 + rb * 16 + r8;
+            if (out_in) exact_rows<DH, L2, true>(vbase, vs2, first, n, w_o + h * DH, (int64_t)H * DH, dm, exact);
+            else exact_rows<DH, L2, false>(vbase, vs2, first, n, w_o + (int64_t)h * DH * dm, dm, dm, exact);
+#pragma unroll
+            for (int j = 0; j < VS_EXACT; ++j)
+                if (lane == 0 && ((again >> (r8 + j)) & 1u)) out[first + j] = L2 ? sqrtf(exact[j]) : exact[j];
+        }
     }
 }
 
 template <int DH, int RB>
-static void launch_project(const Dims &d, const void *v, const bf16_t *w3, float *vnorm, hipStream_t s)
+static void launch_project(const Dims &d, int out_in, const void *v, const void *w_o, const void *w3, float *vnorm,
+                           hipStream_t s)
 {
     const int rows_per_wg = VS_WAVES * RB * 16, row_tiles = (d.n + rows_per_wg - 1) / rows_per_wg;
     const int heads = d.batch * d.H;
     const dim3 grid((unsigned)(8ll * (((long long)heads * row_tiles + 7) / 8))), block(VS_THREADS);
     if (d.norm == CKV_NORM_L2)
-        hipLaunchKernelGGL((vproj_split_kernel<DH, RB, true>), grid, block, 0, s, (const float *)v, w3, vnorm, d.H, d.G, d.n,
-                           d.dm, d.vs[0], d.vs[1], d.vs[2], row_tiles, heads);
+        hipLaunchKernelGGL((vproj_split_kernel<DH, RB, true>), grid, block, 0, s, (const float *)v, (const float *)w_o, out_in,
+                           (const bf16_t *)w3, vnorm, d.H, d.G, d.n, d.dm, d.vs[0], d.vs[1], d.vs[2], row_tiles, heads);
     else
-        hipLaunchKernelGGL((vproj_split_kernel<DH, RB, false>), grid, block, 0, s, (const float *)v, w3, vnorm, d.H, d.G, d.n,
-                           d.dm, d.vs[0], d.vs[1], d.vs[2], row_tiles, heads);
+        hipLaunchKernelGGL((vproj_split_kernel<DH, RB, false>), grid, block, 0, s, (const float *)v, (const float *)w_o, out_in,
+                           (const bf16_t *)w3, vnorm, d.H, d.G, d.n, d.dm, d.vs[0], d.vs[1], d.vs[2], row_tiles, heads);
 }
 
 size_t vproj_split_bytes(const Dims &d) { return (size_t)d.H * d.dh * d.dm * VS_PARTS * 2; }
@@ -302,17 +363,17 @@ hipError_t launch_vproj_split(const Dims &d, int out_in, const void *v, const vo
     if (d.dh == 64) { // (six blocks spill, and five are nowhere the best)
         const int choices[] = {4, 3, 2, 1};
         switch (pick_row_blocks(d, choices, 4)) {
-        case 4: launch_project<64, 4>(d, v, (const bf16_t *)w3, vnorm, s); break;
-        case 3: launch_project<64, 3>(d, v, (const bf16_t *)w3, vnorm, s); break;
-        case 2: launch_project<64, 2>(d, v, (const bf16_t *)w3, vnorm, s); break;
-        default: launch_project<64, 1>(d, v, (const bf16_t *)w3, vnorm, s); break;
+        case 4: launch_project<64, 4>(d, out_in, v, w_o, w3, vnorm, s); break;
+        case 3: launch_project<64, 3>(d, out_in, v, w_o, w3, vnorm, s); break;
+        case 2: launch_project<64, 2>(d, out_in, v, w_o, w3, vnorm, s); break;
+        default: launch_project<64, 1>(d, out_in, v, w_o, w3, vnorm, s); break;
         }
     } else { // (the registers hold three)
         const int choices[] = {3, 2, 1};
         switch (pick_row_blocks(d, choices, 3)) {
-        case 3: launch_project<128, 3>(d, v, (const bf16_t *)w3, vnorm, s); break;
-        case 2: launch_project<128, 2>(d, v, (const bf16_t *)w3, vnorm, s); break;
-        default: launch_project<128, 1>(d, v, (const bf16_t *)w3, vnorm, s); break;
+        case 3: launch_project<128, 3>(d, out_in, v, w_o, w3, vnorm, s); break;
+        case 2: launch_project<128, 2>(d, out_in, v, w_o, w3, vnorm, s); break;
+        default: launch_project<128, 1>(d, out_in, v, w_o, w3, vnorm, s); break;
         }
     }
     return hipGetLastError();

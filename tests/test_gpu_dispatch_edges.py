@@ -80,6 +80,32 @@ def test_fp32_magnitudes_over_the_exponent_range(P, v_scale, w_scale):
     assert np.abs(got / ref - 1).max() <= 2e-6
 
 
+@pytest.mark.parametrize("norm", [1, 2])
+@pytest.mark.parametrize("wo_out_in", [False, True])
+@pytest.mark.parametrize("dh,H,Hkv,n,dm", [(64, 4, 2, 130, 96), (128, 4, 1, 515, 32), (128, 32, 8, 1217, 64)])
+def test_fp32_magnitudes_with_infinities(P, dh, H, Hkv, n, dm, wo_out_in, norm):
+    """An infinite entry of V or W_O gives the infinite magnitude that the fp32 products give (the entry ranks first), and a
+    NaN only where a product is one; every other row is as without it."""
+    import torch
+    cfg = CONFIGS["tiny"].with_(head_dim=dh, n_q_heads=H, n_kv_heads=Hkv, n_ctx=n, d_model=dm)
+    t = make_layer(cfg)
+    v, w = t["v"], t["w_o"]
+    v[0, 0, 0, 1], v[0, 0, 17, dh - 1], v[0, -1, n - 1, 3] = np.inf, -np.inf, np.inf
+    v[0, 0, 40, :2] = np.inf, -np.inf          # both signs in one row: NaN where their products differ in sign
+    v[0, 0, 41, 5], v[0, 0, 63, 0] = np.nan, 0.0
+    w[0] = np.abs(w[0]) + 1e-3                 # (one sign: the first entry's row has no cancelling infinities)
+    w[(H - 1) * dh + 2, dm - 1] = -np.inf      # the last head's rows are all infinite
+    with np.errstate(invalid="ignore"):
+        ref = magnitudes64(v, w, H, norm)
+    dev = [torch.from_numpy(a).cuda() for a in (t["q_win"], t["k"], v, np.ascontiguousarray(w.T) if wo_out_in else w)]
+    for extra in (P.CKV_NO_MFMA, 0):
+        got = score(P, cfg_desc(P, cfg, flags=(P.CKV_WO_OUT_IN if wo_out_in else 0) | extra, norm=norm), *dev)[2]
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref)), extra
+        fin = np.isfinite(ref)
+        assert np.abs(got[fin] - ref[fin]).max() <= 2e-6 * np.abs(ref[fin]).max()
+    assert np.isinf(ref[0, H - 1]).sum() > n // 2 and np.isinf(ref[0, 0, 0]) and np.isinf(ref[0, 0, 17])
+
+
 def test_fp32_score_accepts_a_workspace_without_room_for_the_split(P):
     """A workspace that ends before the split's scratch is accepted and gives the vector kernel's magnitudes,
     bit by bit."""
