@@ -1,7 +1,7 @@
 // Per-entry L1 (or L2) magnitude of the projected value for fp32 layers, on the bf16 matrix cores
 // (Theorem 3.3; Algorithm 1, lines 2-3):  N^h_i = sum_c | sum_t V^g[i,t] * W_O^h[t,c] |.
 //
-// An fp32 number is the sum of three bf16 numbers (3 x 8 significant bits, the same exponent range):
+// An fp32 number (of magnitude 2^-60 to 2^60, or zero) is the sum of three bf16 numbers (3 x 8 significant bits):
 //   x = x0 + x1 + x2,  x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1), both differences exact.
 // With round-to-nearest |x1| <= 2^-9 |x0| and |x2| <= 2^-18 |x0|, so of the nine products of v * w the three that are
 // left out (v1 w2, v2 w1, v2 w2) are below 2^-26 of it, under half an ulp of the fp32 product; the six others are exact
@@ -12,14 +12,15 @@
 //   project   the tiling of the bf16 kernel: a wave keeps RB blocks of 16 token rows (all three parts) as MFMA
 //             fragments, the head's parts stream through LDS in tiles of 32 columns (24 KiB at d_h 128, double
 //             buffered, direct buffer->LDS loads, 16-byte chunks swizzled), six MFMAs per (k-step, row block), the
-//             previous column block's |acc| drained under them.  Rows that meet an infinity or NaN are computed again
-//             from the fp32 operands (exact_rows), so that they get what fp32 products give.
+//             previous column block's |acc| drained under them.  Rows that meet an entry outside that range are computed
+//             again from the fp32 operands (exact_rows), so that they get what fp32 products give.
 //
 // What bounds it: the matrix cores; six bf16 MFMAs per fp32 product still leave 2.7 times the rate of the fp32 MFMA
 // (157 TFLOP/s nominal).  Measured at 16 query heads over 4 kv heads, d_h 128, d_model 2048, 8192 tokens: the score call
-// 2.63 ms with the vector kernel (27 TFLOP/s), 0.388 ms with this one; 4 heads, d_h 64, d_model 256, 1024 tokens: the
-// vector kernel's 84 us become 10.  Relative error of the magnitudes against 64 bits: 6.6e-7 before, 2.1e-7 now (the
-// d_model sum runs in 16 accumulators instead of one).
+// 2.57 ms with the vector kernel (27 TFLOP/s), 0.293 ms with this one; 4 heads, d_h 64, d_model 256, 1024 tokens: 119 and
+// 21 us.  One product may be off by 9.8e-8 of itself (an fp32 fma: 6.0e-8; rms 2.60e-8 and 2.53e-8), but the sums run in
+// 16 accumulators instead of one: the magnitudes' error against 64 bits (2-norm) is 5.7e-8 where the vector kernel has
+// 6.7e-7 (d_model 2048), and 4.2e-8 where it has 2.4e-7 (d_model 256).
 #include <type_traits>
 
 #include "common.hpp"
@@ -36,17 +37,16 @@ constexpr int VS_PARTS = 3;
 
 #define LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
-// The three bf16 parts of x.  A value whose nearest bf16 is infinite (the last half step below FLT_MAX) takes the
-// truncated first part.  An infinity or NaN has no such parts (its products with the other operand's parts would cancel or
-// meet zeros): it becomes a NaN, and the project kernel computes the rows that come out as NaN again, in fp32.
+// The three bf16 parts of x.  They are x itself, and every product of two parts is exact, for zero and for magnitudes from
+// 2^-60 up to 2^60: no part and no product lies below fp32's smallest subnormal (below 2^-110 the third part would fall
+// under bf16's), no sum of products overflows.  Any other x (infinity and NaN among them) becomes a NaN, and the project
+// kernel computes the rows that come out as NaN again, in fp32.  Random values of order one or 1e-2 are never that small.
 __device__ __forceinline__ void split3(float x, uint32_t &p0, uint32_t &p1, uint32_t &p2)
 {
     const uint32_t u = __float_as_uint(x);
-    const bool finite = (u & 0x7F800000u) != 0x7F800000u;
-    uint32_t h = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-    if ((h & 0x7F80u) == 0x7F80u) h = u >> 16;
-    p0 = finite ? h & 0xFFFFu : 0x7FC0u;
-    const float r = finite ? x - __uint_as_float(p0 << 16) : 0.f;
+    const bool has_parts = ((u >> 23) & 0xFFu) - (127u - 60u) < 120u || (u << 1) == 0u;
+    p0 = has_parts ? (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16 : 0x7FC0u;
+    const float r = x - __uint_as_float(p0 << 16);
     const uint32_t ur = __float_as_uint(r);
     p1 = (ur + 0x7FFFu + ((ur >> 16) & 1u)) >> 16;
     const float r2 = r - __uint_as_float(p1 << 16);

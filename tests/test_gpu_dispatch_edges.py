@@ -64,9 +64,11 @@ def test_fp32_magnitudes_against_float64(P, dh, H, Hkv, n, dm, wo_out_in, norm):
     assert err["split"] <= max(1.05 * err["vector"], 2e-7), err
 
 
-@pytest.mark.parametrize("v_scale,w_scale", [(1e30, 1e-30), (1e-25, 1e25), (3.0e38, 1e-20), (1e-30, 1e-3)])
+@pytest.mark.parametrize("v_scale,w_scale", [(1e30, 1e-30), (1e-25, 1e25), (3.0e38, 1e-20), (1e-30, 1e-3), (1e-35, 1.0), (1e-37, 1.0),
+                                             (1.0, 1e-36), (1e-37, 1e30), (2.0 ** -59, 2.0 ** -56), (2.0 ** 59, 2.0 ** 55)])
 def test_fp32_magnitudes_over_the_exponent_range(P, v_scale, w_scale):
-    """Entries up to the last half step below FLT_MAX (whose nearest bf16 is infinite) and down to 1e-30."""
+    """Entries from the last half step below FLT_MAX (whose nearest bf16 is infinite) down to where a third bf16 part would
+    be subnormal, and around the ends of the range that the split takes."""
     import torch
     cfg = CONFIGS["tiny"].with_(n_ctx=130, d_model=64)
     t = make_layer(cfg)
@@ -75,9 +77,15 @@ def test_fp32_magnitudes_over_the_exponent_range(P, v_scale, w_scale):
         v[0, 0, 5, 3], v[0, 1, 7, 0] = np.finfo(np.float32).max, -np.finfo(np.float32).max
     w = (t["w_o"] * np.float32(w_scale)).astype(np.float32)
     ref = magnitudes64(v, w, cfg.n_q_heads, 1)
-    got = score(P, cfg_desc(P, cfg), *(torch.from_numpy(a).cuda() for a in (t["q_win"], t["k"], v, w)))[2]
-    assert np.isfinite(got).all()
-    assert np.abs(got / ref - 1).max() <= 2e-6
+    dev = [torch.from_numpy(a).cuda() for a in (t["q_win"], t["k"], v, w)]
+    err = []
+    for flags in (0, P.CKV_NO_MFMA):
+        got = score(P, cfg_desc(P, cfg, flags=flags), *dev)[2]
+        assert np.isfinite(got).all()
+        # fp32 sums: 2e-6; where they are subnormal each of the d_h * d_model steps rounds by up to 2^-150 in either kernel
+        assert (np.abs(got - ref) <= 2e-6 * ref + cfg.head_dim * cfg.d_model * 2.0 ** -150).all()
+        err.append(np.abs(got / ref - 1).max())
+    assert err[0] <= 1.2 * err[1] + 1.2e-7, err # a few ulp beyond the vector kernel's at most
 
 
 @pytest.mark.parametrize("norm", [1, 2])
