@@ -825,12 +825,12 @@ hipError_t launch_select(const Dims &d, const float *attn, const float *crit, co
 // The P entries with the largest pooled score among all Hkv * n entries of a batch item are an order statistic of one row
 // of Hkv * n keys: its threshold comes from the selection's stage-1 digits, and a head's share is the number of its
 // entries above the threshold plus those of its ties that still fit (ties go to lower entries first, i.e. to lower heads).
-// Only counts are needed, no membership and no index list: one launch where the row fits a workgroup, five otherwise
-// (clear, three digits, count) -- the whole selection and a binary search in its list took ten (two rows of eight heads x 20011: 52 us
-// of kernels, now 27).
+// Only counts are needed, no membership and no index list: one launch where the row fits a workgroup, six otherwise
+// (clear, three digits, count, finish) -- the whole selection and a binary search in its list took ten (two rows of eight
+// heads x 20011: 39.5 us in a chain of calls, now 23).
 struct AllocArgs {
     int32_t *budget_out; // [batch][Hkv]
-    uint32_t *above;     // [batch][Hkv + 1]: entries above the threshold per head; the last word counts finished workgroups
+    uint32_t *above;     // [batch][Hkv]: entries above the threshold per head
     uint32_t *ties;      // [batch][Hkv * n] (the first Hkv words of a row are used)
     int Hkv, n, floor_each;
 };
@@ -882,17 +882,17 @@ __global__ __launch_bounds__(256) void allocate_clear_kernel(uint32_t *hist, siz
 {
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (i < words) hist[i] = 0u;
-    if (i < (size_t)batch * (L.Hkv + 1)) L.above[i] = 0u;
-    if (i < (size_t)batch * L.Hkv) L.ties[i / L.Hkv * ((size_t)L.Hkv * L.n) + i % L.Hkv] = 0u;
+    if (i < (size_t)batch * L.Hkv) {
+        L.above[i] = 0u;
+        L.ties[i / L.Hkv * ((size_t)L.Hkv * L.n) + i % L.Hkv] = 0u;
+    }
 }
 
-// One workgroup per slice of the row: its entries above the threshold and its ties, added to their heads' counts; the
-// workgroup that finishes last turns the counts into budgets.
+// One workgroup per slice of the row: its entries above the threshold and its ties, added to their heads' counts.
 __global__ __launch_bounds__(SEL_THREADS) void allocate_count_kernel(SelArgs A, AllocArgs L)
 {
     __shared__ SelShared sh;
     __shared__ uint32_t cnt[2][SEL_SLICE]; // above / ties of the heads this slice touches (at most one per token)
-    __shared__ uint32_t last;
     const int slice = blockIdx.x, row = blockIdx.y;
     const int i0 = slice * SEL_SLICE + threadIdx.x * SEL_PER_THREAD;
     uint32_t w[8];
@@ -905,7 +905,7 @@ __global__ __launch_bounds__(SEL_THREADS) void allocate_count_kernel(SelArgs A, 
     const int g0 = slice * SEL_SLICE / L.n, g1 = min(slice * SEL_SLICE + SEL_SLICE - 1, A.n - 1) / L.n;
     for (int g = threadIdx.x; g <= g1 - g0; g += SEL_THREADS) { cnt[0][g] = 0u; cnt[1][g] = 0u; }
     __syncthreads();
-    uint32_t *above = L.above + (size_t)row * (L.Hkv + 1), *ties = L.ties + (size_t)row * A.n;
+    uint32_t *above = L.above + (size_t)row * L.Hkv, *ties = L.ties + (size_t)row * A.n;
     if (g0 == g1) { // uniform: the slice lies inside one head
         uint32_t n_above = 0u, n_ties = 0u;
 #pragma unroll
@@ -928,24 +928,24 @@ __global__ __launch_bounds__(SEL_THREADS) void allocate_count_kernel(SelArgs A, 
         if (cnt[0][g]) atomicAdd(above + g0 + g, cnt[0][g]);
         if (cnt[1][g]) atomicAdd(ties + g0 + g, cnt[1][g]);
     }
-    // The workgroup's counts are in (the barrier), one thread releases them and draws the ticket at device scope; the last
-    // workgroup acquires and reads past the L1.
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();
-        last = atomicAdd(above + L.Hkv, 1u) == gridDim.x - 1 ? 1u : 0u;
-        __threadfence();
-    }
-    __syncthreads();
-    if (!last) return; // uniform
+    if (slice == 0 && threadIdx.x == 0) A.state[(size_t)row * 2 * ST_WORDS + ST_R] = fit;
+}
+
+// One workgroup per row: the heads' counts become budgets.  A launch of its own, and no ticket that lets the last workgroup
+// of the count kernel do it: that needs a release by every wave that counted, and the write-backs of L2 these cost grow with
+// the launch (the whole allocation, us, with one release per workgroup / like this: 64 rows of 8 heads x 8000 110 / 56, one
+// of 8 x 131072 55 / 45, two of 8 x 20011 24.9 / 23.2).
+__global__ __launch_bounds__(SEL_THREADS) void allocate_finish_kernel(SelArgs A, AllocArgs L)
+{
+    __shared__ SelShared sh;
+    const int row = blockIdx.x;
+    const uint32_t *above = L.above + (size_t)row * L.Hkv, *ties = L.ties + (size_t)row * A.n;
+    const uint32_t fit = A.state[(size_t)row * 2 * ST_WORDS + ST_R];
     uint32_t carry = 0u;
     for (int c0 = 0; c0 < L.Hkv; c0 += SEL_THREADS) { // heads in order: how many ties lie before each
         const int g = c0 + threadIdx.x;
-        uint32_t a = 0u, t = 0u, total;
-        if (g < L.Hkv) {
-            a = __hip_atomic_load(above + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            t = __hip_atomic_load(ties + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        const uint32_t a = g < L.Hkv ? above[g] : 0u, t = g < L.Hkv ? ties[g] : 0u;
+        uint32_t total;
         const uint32_t before = carry + block_exclusive_scan(sh, t, total);
         if (g < L.Hkv)
             L.budget_out[(size_t)row * L.Hkv + g] = min(L.n, L.floor_each + (int)(a + min(fit > before ? fit - before : 0u, t)));
@@ -966,7 +966,7 @@ hipError_t launch_allocate(const Dims &d, const float *attn, int total, float fl
     const int P = (int)min((long long)total - (long long)d.Hkv * floor_each, (long long)d.Hkv * d.n);
     AllocArgs L;
     L.budget_out = budget_out;
-    L.above = (uint32_t *)tmp; // batch * (Hkv + 1) of the batch * (2 + Hkv * ceil(P / Hkv)) words that are there when P > 0
+    L.above = (uint32_t *)tmp; // batch * Hkv of the batch * (2 + Hkv * ceil(P / Hkv)) words that are there when P > 0
     L.ties = keys2;
     L.Hkv = d.Hkv; L.n = d.n; L.floor_each = floor_each;
     if (P <= 0) {
@@ -986,13 +986,14 @@ hipError_t launch_allocate(const Dims &d, const float *attn, int total, float fl
         return hipGetLastError();
     }
     const size_t hist_words = (size_t)d.batch * (2 * 3 * SEL_BINS + 2 * ST_WORDS);
-    const size_t clear = std::max(hist_words, (size_t)d.batch * (d.Hkv + 1));
+    const size_t clear = std::max(hist_words, (size_t)d.batch * d.Hkv);
     const dim3 grid(A.n_slices, d.batch), block(SEL_THREADS);
     hipLaunchKernelGGL(allocate_clear_kernel, dim3((unsigned)((clear + 255) / 256)), dim3(256), 0, s, scratch, hist_words, L, d.batch);
     hipLaunchKernelGGL((select_hist_kernel<0, 0>), grid, block, 0, s, A);
     hipLaunchKernelGGL((select_hist_kernel<0, 1>), grid, block, 0, s, A);
     hipLaunchKernelGGL((select_hist_kernel<0, 2>), grid, block, 0, s, A);
     hipLaunchKernelGGL(allocate_count_kernel, grid, block, 0, s, A, L);
+    hipLaunchKernelGGL(allocate_finish_kernel, dim3(d.batch), block, 0, s, A, L);
     return hipGetLastError();
 }
 

@@ -235,6 +235,23 @@ def test_allocate_at_the_row_lengths_where_the_kernel_changes(P, Hkv, n):
                 assert np.array_equal(got, O.allocate(attn.astype(np.float64), total, np.float32(floor_frac))), (total, floor_frac)
 
 
+@pytest.mark.parametrize("b,Hkv,n", [(5, 3000, 11), (3, 700, 36), (4, 900, 31), (2, 820, 30), (2, 30000, 1), (33, 8, 3100)])
+def test_allocate_counts_of_every_wave_arrive(P, b, Hkv, n):
+    """Slices over 64 heads and more (every wave of a workgroup adds counts of its own) and launches of many rows: whole
+    numbers, each call on a workspace that an earlier one has filled."""
+    import torch
+    from oracle import cpu_oracle as O
+    cfg = CONFIGS["tiny"].with_(n_q_heads=Hkv, n_kv_heads=Hkv, n_ctx=n, window=1, batch=b)
+    desc = cfg_desc(P, cfg)
+    r = np.random.Generator(np.random.PCG64(Hkv * n))
+    attn = np.concatenate([r.random((b - 1, Hkv, n)).astype(np.float32), tied_scores(n, Hkv, 3)[0]])
+    dev, budget = torch.from_numpy(attn).cuda(), torch.empty((b, Hkv), dtype=torch.int32, device="cuda")
+    ws = torch.full((P.workspace_bytes(desc, n),), 255, dtype=torch.uint8, device="cuda")
+    for total in (Hkv * n // 3, Hkv * n // 2, Hkv * n // 3):
+        P.criticalkv_allocate(desc, dev, total, 0.2, budget, workspace=ws)
+        assert np.array_equal(budget.cpu().numpy(), O.allocate(attn.astype(np.float64), total, np.float32(0.2)))
+
+
 # ---- fp32 window attention on the matrix cores -----------------------------------------------------------------------------
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("dh,H,Hkv,n,W", [(64, 4, 4, 33, 1), (64, 3, 1, 32, 32), (128, 8, 2, 31, 31), (128, 8, 8, 2049, 33),
