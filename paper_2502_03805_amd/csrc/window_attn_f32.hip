@@ -5,9 +5,11 @@
 //            ranges' pairs by every wave that needs them (there are at most 64 ranges: cheaper than a launch between)
 //
 // v_mfma_f32_32x32x2_f32: a lane holds row (A) / column (B) lane % 32 at k = lane / 32; accumulator j is row
-// 8*(j/4) + 4*(lane/32) + j%4, column lane%32.  It adds its two products one after the other in fp32, exactly as a scalar
-// fmaf chain does, so nothing is rounded that the vector kernel did not round.  Which k an instruction takes is free as
-// long as both operands agree: instruction 4i + e takes k = 8i + 4 * (lane / 32) + e, so that a lane's operands of four
+// 8*(j/4) + 4*(lane/32) + j%4, column lane%32.  It adds its two products one after the other in fp32, as a scalar fmaf
+// chain does.  A logit is the sum of four chains of a quarter of d_h each: its rounding, which all of a heavy entry's weights
+// share, is most of the result's error.  Against 64 bits (2-norm, means over 100 layers of the tiny shape and 30 of the
+// larger one below): the vector kernel 3.6e-7 / 2.4e-7, one chain 3.6e-7 / 2.3e-7, two 2.0e-7 / 1.5e-7, four 1.6e-7 /
+// 1.1e-7, for 0.1 - 0.7 us of both sweeps.  Which k an instruction takes is free as long as both operands agree: instruction 4i + e takes k = 8i + 4 * (lane / 32) + e, so that a lane's operands of four
 // instructions are one 16-byte load from global memory; no LDS.
 //
 // Work split: a wave owns one block of 32 window rows of one query head (its queries in registers for its whole life)
@@ -29,6 +31,7 @@ constexpr int AF_WAVES = 4;
 constexpr int AF_KEYS = 32;       // keys per block
 constexpr int AF_ROWS = 32;       // window rows per block
 constexpr int AF_MAX_RANGES = 64; // key ranges per head
+constexpr int AF_CHAINS = 4;      // accumulators per block of logits
 constexpr double AF_LOG2E = 1.4426950408889634;
 constexpr float AF_NEG = -1.0e30f;
 
@@ -82,19 +85,27 @@ __device__ __forceinline__ float weight(float logit, float m, const AttnF32Args 
 template <int DH, bool KEYS_ARE_ROWS>
 __device__ __forceinline__ f32x16 logits(float4 (&key)[DH / 8], const float4 (&query)[DH / 8], const float *next, int half)
 {
-    f32x16 acc;
+    f32x16 acc[AF_CHAINS];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) acc[j] = 0.f;
+    for (int c = 0; c < AF_CHAINS; ++c)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) acc[c][j] = 0.f;
 #pragma unroll
     for (int i = 0; i < DH / 8; ++i) {
         const float kx[4] = {key[i].x, key[i].y, key[i].z, key[i].w}, qx[4] = {query[i].x, query[i].y, query[i].z, query[i].w};
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            acc = KEYS_ARE_ROWS ? __builtin_amdgcn_mfma_f32_32x32x2f32(kx[e], qx[e], acc, 0, 0, 0)
-                                : __builtin_amdgcn_mfma_f32_32x32x2f32(qx[e], kx[e], acc, 0, 0, 0);
+            acc[e % AF_CHAINS] = KEYS_ARE_ROWS ? __builtin_amdgcn_mfma_f32_32x32x2f32(kx[e], qx[e], acc[e % AF_CHAINS], 0, 0, 0)
+                                               : __builtin_amdgcn_mfma_f32_32x32x2f32(qx[e], kx[e], acc[e % AF_CHAINS], 0, 0, 0);
         key[i] = *reinterpret_cast<const float4 *>(next + 8 * i + 4 * half);
     }
-    return acc;
+#pragma unroll
+    for (int c = AF_CHAINS / 2; c > 0; c >>= 1)
+#pragma unroll
+        for (int x = 0; x < c; ++x)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc[x][j] += acc[x + c][j];
+    return acc[0];
 }
 
 template <int DH>

@@ -281,6 +281,24 @@ def test_fp32_window_attention_against_float64(P, dh, H, Hkv, n, W, causal):
     assert err["matrix"] <= max(1.2 * err["vector"], 3e-7), err
 
 
+@pytest.mark.parametrize("dh,H,Hkv,n,W", [(64, 4, 4, 512, 8), (64, 4, 4, 4096, 8), (128, 16, 4, 1500, 32)])
+def test_fp32_window_attention_loses_no_precision(P, dh, H, Hkv, n, W):
+    """Scores with heavy entries, over several layers: no further from 64 bits than the vector kernel's.  A logit's error is
+    the rounding of its chain over d_h; four chains of a quarter each halve it (0.45 of the vector kernel's measured)."""
+    import torch
+    err = {0: 0.0, P.CKV_NO_MFMA: 0.0}
+    for seed in range(8):
+        cfg = CONFIGS["tiny"].with_(head_dim=dh, n_q_heads=H, n_kv_heads=Hkv, n_ctx=n, d_model=32, window=W, pool_kernel=1)
+        t = make_layer(cfg, seed_offset=seed)
+        dev = [torch.from_numpy(t[name]).cuda() for name in ("q_win", "k", "v", "w_o")]
+        s = dev[0].double().view(1, Hkv, H // Hkv, W, dh) @ dev[1].double()[:, :, None].transpose(-1, -2).contiguous() / dh ** 0.5
+        ref = torch.softmax(s, -1).mean((2, 3)).cpu().numpy()
+        for flags in err:
+            got = score(P, cfg_desc(P, cfg, flags=flags), *dev)[0]
+            err[flags] += np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    assert err[0] <= 0.8 * err[P.CKV_NO_MFMA], err
+
+
 # ---- wave-private attention sweeps: heads and keys per wave ----------------------------------------------------------------------
 @pytest.mark.parametrize("dh,H,Hkv,W,b,ns", [
     (64, 32, 8, 32, 1, (127, 129, 1000, 3000, 8193)), (64, 32, 8, 32, 4, (3001, 32768)), (128, 40, 8, 64, 1, (65, 2000, 8192, 20000)),
