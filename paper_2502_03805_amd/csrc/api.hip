@@ -199,7 +199,7 @@ static int score_plan(const ckv_layer_desc *desc, const void *q_win, const void 
     const size_t part_cap = (size_t)d.batch * d.H * d.W * p.ws.max_chunks * 2;
     const size_t sel_cap = select_workspace_words(d.batch * d.Hkv, d.n);
     p.part_floats = std::max(part_cap, sel_cap);
-    p.f32_a = desc->dtype == CKV_F32 && !(desc->flags & CKV_NO_MFMA) && attn_f32_supported(d, p.part_floats);
+    p.f32_a = desc->dtype == CKV_F32 && !(desc->flags & CKV_NO_MFMA) && attn_f32_taken(d, p.part_floats);
     if (p.f32_a && sel_cap > part_cap) p.part = (float *)(p.base + p.ws.sel_scratch);
     p.chunks = p.tile_a ? mfma_attn_chunks(d) : p.wave_a ? wave_attn_chunks(d) : generic_attn_chunks(d);
     if (p.chunks > p.ws.max_chunks) return CKV_E_WORKSPACE;
@@ -226,13 +226,13 @@ static int score_attention(const ScorePlan &p, const ckv_layer_desc *desc, const
     const Dims &d = p.d;
     hipStream_t s = p.s;
     hipError_t e;
-    if (p.f32_a) { // (pass 2 merges the ranges' pairs itself)
+    if (p.f32_a) { // (pass 2 merges the ranges' pairs itself, or a launch of pass 1 does)
         mark(ev, 2 * CKV_STAGE_ATTN_STATS, s);
-        e = launch_attn_f32(d, q_win, k, p.part, p.part_floats, p.a_raw, true, s);
+        e = launch_attn_f32(d, q_win, k, p.part, p.part_floats, p.stats, p.a_raw, true, s);
         mark(ev, 2 * CKV_STAGE_ATTN_STATS + 1, s);
         if (e != hipSuccess) return CKV_E_HIP;
         mark(ev, 2 * CKV_STAGE_ATTN_COLSUM, s);
-        e = launch_attn_f32(d, q_win, k, p.part, p.part_floats, p.a_raw, false, s);
+        e = launch_attn_f32(d, q_win, k, p.part, p.part_floats, p.stats, p.a_raw, false, s);
         mark(ev, 2 * CKV_STAGE_ATTN_COLSUM + 1, s);
         return e == hipSuccess ? CKV_OK : CKV_E_HIP;
     }

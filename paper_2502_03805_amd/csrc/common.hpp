@@ -74,10 +74,11 @@ hipError_t launch_attn_colsum_mfma(const Dims &d, const void *q, const void *k, 
 hipError_t launch_attn_stats_wave(const Dims &d, const void *q, const void *k, float *part, int chunks, hipStream_t s);
 hipError_t launch_attn_colsum_wave(const Dims &d, const void *q, const void *k, const float *stats, float *a_raw,
                                    hipStream_t s);
-// both sweeps for fp32 layers on the fp32 matrix instruction (stats: pass 1, else pass 2); part holds part_floats floats
-bool attn_f32_supported(const Dims &d, size_t part_floats);
-hipError_t launch_attn_f32(const Dims &d, const void *q, const void *k, float *part, size_t part_floats, float *a_raw,
-                           bool stats, hipStream_t s);
+// both sweeps for fp32 layers on the fp32 matrix instruction (pass 1, with the rows' (M, weight) left in part or stats, else
+// pass 2); part holds part_floats floats
+bool attn_f32_taken(const Dims &d, size_t part_floats);
+hipError_t launch_attn_f32(const Dims &d, const void *q, const void *k, float *part, size_t part_floats, float *stats,
+                           float *a_raw, bool pass1, hipStream_t s);
 // projected-value L1 norm; w_t is [d_model, H*dh]
 hipError_t launch_vproj_generic(const Dims &d, int dtype, const void *v, const void *w_t, float *vnorm,
                                 hipStream_t s);

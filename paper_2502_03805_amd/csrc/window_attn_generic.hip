@@ -1,7 +1,7 @@
 // Observation-window attention on the vector ALUs (Algorithm 2, lines 2-3; eq. (2)).
 //
 // These kernels serve what the matrix-core kernels do not cover (bf16 with windows past 128 rows or token strides past
-// 2 GiB, CKV_NO_MFMA).
+// 2 GiB, fp32 with windows of a few rows, CKV_NO_MFMA).
 // The softmax over all n keys needs each window row's max and sum before any weight can
 // be summed over the window, so the keys are swept twice:
 //   pass 1  per (query head, key chunk): row-wise max and sum of exp over the chunk
