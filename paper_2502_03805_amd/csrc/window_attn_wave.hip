@@ -370,23 +370,26 @@ bool attn_wave_supported(const Dims &d)
            ((int64_t)(d.n - 1) * d.ks[2] + d.dh) * 2 < ((int64_t)1 << 31);
 }
 
-// Keys per wave (they set the number of waves).  Many keys spread a wave's fixed cost (its query fragments, up to 32 KiB,
-// worth c keys) over more key blocks, few fill the chip: it has 1024 SIMDs, and a round's time goes with the waves of
-// the fullest one -- a little over one, two or three waves' time while it holds fewer than four, which do not cover each
-// other's waits.  The choice is the cheapest by that count (measured within 3 % of the best of the seven everywhere: 5:1 group
-// with a 64-row window, 2000 .. 131072 tokens; 4:1 group at d_h 64, 1500 .. 4 x 32768).
-static int attn_kpw(const Dims &d, int groups, int row_blocks)
+// Keys per wave (they set the number of waves) and the cost of the launch with them.  Many keys spread a wave's fixed cost
+// (its query fragments, up to 32 KiB, worth c keys) over more key blocks, few fill the chip: it has 1024 SIMDs, and a
+// round's time goes with the waves of the fullest one -- a little over one, two or three waves' time while it holds fewer
+// than four, which do not cover each other's waits.  The choice is the cheapest by that count (measured within 3 % of the
+// best of the seven: 5:1 group with a 64-row window, 2000 .. 131072 tokens; 4:1 group at d_h 64, 1500 .. 4 x 32768).
+static int attn_kpw(const Dims &d, int groups, int row_blocks, double *cost)
 {
-    const long long per_range = (long long)d.batch * d.Hkv * groups;
+    const long long heads = (long long)d.batch * d.Hkv;
     const int choices[] = {1024, 768, 512, 384, 256, 192, AM_MIN_KPW};
     const double c = 35.0 + 35.0 * row_blocks;
     int best = AM_MIN_KPW;
     double least = 0.0;
     for (int kpw : choices) {
-        const long long r = (per_range * ((d.n + kpw - 1) / kpw) + 1023) / 1024;
-        const double cost = (r == 1 ? 1.35 : r == 2 ? 2.2 : r == 3 ? 3.1 : (double)r) * (kpw + c);
-        if (least == 0.0 || cost < least) { least = cost; best = kpw; }
+        const long long chunks = ((d.n + kpw - 1) / kpw + AM_WAVES - 1) / AM_WAVES;
+        const long long r = (groups * ((heads * chunks + 7) / 8) + 31) / 32; // (wave_job's dealing: 32 CUs in each of 8 XCDs)
+        const double all = (r == 1 ? 1.35 : r == 2 ? 2.2 : r == 3 ? 3.1 : (double)r) * (kpw + c);
+        if (least == 0.0 || all < least) { least = all; best = kpw; }
     }
+    // a key block costs its row blocks and what is paid once for all of them (its loads, its fragments' reads)
+    *cost = least * (row_blocks + (d.dh == 128 ? 2.0 : 1.0));
     return best;
 }
 
@@ -396,15 +399,22 @@ static AttnArgs make_args(const Dims &d, const void *q, const void *k)
     A.q = (const bf16_t *)q; A.k = (const bf16_t *)k;
     A.H = d.H; A.G = d.G; A.n = d.n; A.W = d.W; A.causal = d.causal;
     A.qbs = (d.W + 31) / 32;
-    // Heads per wave: one (few registers, four waves per SIMD, the most waves for a short launch); two where a group's heads
-    // pair up and the launch is long enough to fill the chip anyway (half the key traffic).  Both sweeps, us, most heads
-    // that fit / one / two: 4:1 group, d_h 64: 8192 tokens 26.5 / 20.2 / 20.7, 4 x 8192 38.8 / 33.9 / 34.7, 4 x 32768 84.3 /
-    // 86.0 / 80.4; 5:1 group with a 64-row window (two fit, the sixth slot idle): 8192 tokens 45.7 / 37.3, 20000 80.2 / 64.6,
-    // 131072 242.6 / 241.8.
-    const bool pairs_up = d.G % 2 == 0 && 2 * A.qbs <= AM_MAX_QB;
-    A.hpw = pairs_up && (long long)d.batch * d.H * ((d.n + 511) / 512) >= 8192 ? 2 : 1;
-    A.groups = d.G / A.hpw;
-    const int kpw = attn_kpw(d, A.groups, A.hpw * A.qbs);
+    // Heads per wave: few fill the chip in a short launch (and take few registers), many read a key block less often, and
+    // a last group with fewer heads works on zero queries for the rest.  The choice is the cheapest launch by the count
+    // above; over 2048 .. 131072 tokens, groups of 2 to 16, windows of 16 to 64 it is within 0.3 % of the best on average and
+    // 7 % at worst.  Both sweeps and the combine, us, one / two / three / four heads, d_h 128, W 32: 40 heads over 8 kv heads,
+    // 131072 tokens 195 / 178 / 160 / 184; 56 over 8: 259 / 224 / 224 / 198, 32768 tokens 86 / 67 / 77 / 71; 14 over 2, 32768
+    // tokens 32 / 33 / 39 / 36.  d_h 64 differs less: 64 over 8, 32768 tokens 52 / 50 / 55 / 58.
+    A.hpw = 1;
+    int kpw = 0;
+    double least = 0.0;
+    for (int h = 1; h * A.qbs <= AM_MAX_QB && h <= d.G; ++h) {
+        double cost;
+        const int k = attn_kpw(d, (d.G + h - 1) / h, h * A.qbs, &cost);
+        if (h > 1 && h * A.qbs == AM_MAX_QB) cost *= 1.04; // (the registers of four row blocks leave two waves per SIMD)
+        if (h == 1 || cost < least) { least = cost; A.hpw = h; kpw = k; }
+    }
+    A.groups = (d.G + A.hpw - 1) / A.hpw;
     A.ranges = (d.n + kpw - 1) / kpw;
     A.chunks = (A.ranges + AM_WAVES - 1) / AM_WAVES;
     A.pairs = d.batch * d.Hkv * A.chunks;

@@ -328,6 +328,48 @@ def test_wave_sweeps_over_the_choices_of_heads_and_keys_per_wave(P, dh, H, Hkv, 
             assert (attn[bi, gi].double() - ref).abs().max() <= 4e-6 * ref.max(), (n, bi, gi)
 
 
+def wave_heads(dh, G, kv_heads, W, n):
+    """Query heads per wave as the launcher chooses them (the cheapest launch; kv_heads over the whole batch)."""
+    blocks = (W + 31) // 32
+
+    def cost(h):
+        groups, least = -(-G // h), []
+        for kpw in (1024, 768, 512, 384, 256, 192, 128):
+            chunks = (-(-n // kpw) + 3) // 4
+            rounds = (groups * ((kv_heads * chunks + 7) // 8) + 31) // 32
+            least.append({1: 1.35, 2: 2.2, 3: 3.1}.get(rounds, rounds) * (kpw + 35 + 35 * h * blocks))
+        return min(least) * (h * blocks + (2 if dh == 128 else 1)) * (1.04 if h > 1 and h * blocks == 4 else 1)
+
+    return min(range(1, min(G, 4 // blocks) + 1), key=cost)
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dh,G,W,b,n,heads", [
+    # every number of heads a wave takes, with a last group of fewer heads where one is possible, and heads of two row blocks
+    (64, 4, 32, 8, 4101, 2), (64, 7, 32, 8, 2049, 2), (64, 6, 32, 8, 4101, 3), (64, 5, 20, 16, 4101, 3), (64, 7, 32, 8, 16390, 4),
+    (64, 8, 33, 16, 4101, 2), (128, 7, 32, 4, 4101, 2), (128, 6, 32, 8, 2049, 3), (128, 5, 7, 8, 4101, 3), (128, 8, 32, 16, 4101, 4),
+    (128, 7, 32, 16, 4101, 4), (128, 8, 64, 8, 2049, 2), (128, 7, 33, 8, 2049, 2)])
+def test_wave_sweeps_with_several_heads_per_wave(P, dh, G, W, b, n, heads, causal):
+    """fp32 logits of exact products and fp32 sums over the window: 4e-6 of the largest score."""
+    import torch
+    Hkv, H = 8, 8 * G
+    assert wave_heads(dh, G, b * Hkv, W, n) == heads
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q, k = (torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16) for s in ((b, H, W, dh), (b, Hkv, n, dh)))
+    cfg = CONFIGS["llama32k"].with_(n_q_heads=H, n_kv_heads=Hkv, head_dim=dh, d_model=32, window=W, n_ctx=n, batch=b, pool_kernel=1)
+    desc = cfg_desc(P, cfg, flags=P.CKV_ATTN_ONLY | (P.CKV_CAUSAL_TAIL if causal else 0))
+    attn = torch.empty((b, Hkv, n), dtype=torch.float32, device="cuda")
+    ws = torch.empty(P.workspace_bytes(desc, 1), dtype=torch.uint8, device="cuda")
+    P.criticalkv_score(desc, q, k, None, None, attn, torch.empty_like(attn), None, workspace=ws)
+    hidden = torch.arange(n, device="cuda")[None, :] > n - W + torch.arange(W, device="cuda")[:, None]
+    for bi, gi in ((0, 0), (b // 2, 3), (b - 1, Hkv - 1)):
+        ref = 0
+        for h in range(gi * G, (gi + 1) * G):
+            s = q[bi, h].double() @ k[bi, gi].double().t().contiguous() / dh ** 0.5
+            ref = ref + torch.softmax(s.masked_fill(hidden, -torch.inf) if causal else s, -1).mean(0) / G
+        assert (attn[bi, gi].double() - ref).abs().max() <= 4e-6 * ref.max(), (bi, gi)
+
+
 # ---- work dealt to the XCDs: head counts that eight does not divide ---------------------------------------------------------
 @pytest.mark.parametrize("dtype,dh,H,Hkv,dm,b,n", [
     ("bf16", 128, 28, 4, 128, 1, 1500), ("bf16", 128, 1, 1, 256, 1, 700), ("bf16", 128, 12, 2, 5120, 1, 450),
