@@ -164,16 +164,31 @@ def test_gram_constant_against_float64(P, H, dm, wo_out_in):
 
 
 # ---- row blocks per wave of the projection ----------------------------------------------------------------------------
+def row_blocks(dtype, dh, heads, n):
+    """Row blocks per wave as the launcher chooses them: the cheapest rounds of workgroups."""
+    choices, c2, c1 = {("bf16", 128): ((7, 6, 5, 4, 3, 2), 1.07, 0.90), ("bf16", 64): ((10, 8, 6, 4, 3, 2), 1.84, 1.83),
+                       ("f32", 128): ((3, 2, 1), 0.40, 0.38), ("f32", 64): ((4, 3, 2, 1), 0.50, 0.55)}[dtype, dh]
+
+    def cost(rb):
+        wgs = (heads * -(-n // (64 * rb)) + 7) // 8
+        rest = wgs % 64
+        return wgs // 64 * (rb + c2) + (rb + c2 if rest > 32 else 0.48 * rb + c1 if rest else 0.0)
+
+    return min(choices, key=cost), set(choices)
+
+
 @pytest.mark.parametrize("dtype,dh,H,Hkv,dm,ns", [
-    # 8 * 64 = 512 workgroups are one full round: n on both sides of every change of the choice
     ("bf16", 128, 32, 8, 128, (511, 1025, 1537, 2049, 3073, 4097, 6145, 8193)),
-    ("bf16", 64, 32, 8, 256, (511, 1025, 3073, 4097, 8193, 10241)),
-    ("f32", 128, 16, 4, 32, (1025, 2049, 6145)),
-    ("f32", 64, 16, 4, 32, (1025, 2049, 3073, 8193)),
+    ("bf16", 64, 32, 8, 256, (511, 1025, 1600, 2048, 2816, 3073, 4097, 8193, 10241)),
+    ("f32", 128, 16, 4, 32, (1000, 1025, 2049, 6145)),
+    ("f32", 64, 16, 4, 32, (1025, 2049, 3073, 8193, 9300)),
 ])
 def test_magnitudes_with_every_row_block_count(P, dtype, dh, H, Hkv, dm, ns):
-    """fp32 sums of exact products (bf16: d_h of them, then d_model magnitudes): 2e-6 of the result."""
+    """fp32 sums of exact products (bf16: d_h of them, then d_model magnitudes): 2e-6 of the result.  The lengths make the
+    launcher take every number of row blocks it has."""
     import torch
+    picked, choices = {row_blocks(dtype, dh, H, n)[0] for n in ns}, row_blocks(dtype, dh, H, ns[0])[1]
+    assert picked == choices
     for n in ns:
         cfg = CONFIGS["llama32k"].with_(n_q_heads=H, n_kv_heads=Hkv, head_dim=dh, d_model=dm, n_ctx=n, dtype=dtype, window=8)
         g = torch.Generator(device="cuda").manual_seed(n)
