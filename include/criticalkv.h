@@ -111,7 +111,10 @@ typedef struct ckv_layer_desc {
 
 /*
  * Bytes of workspace that criticalkv_score, criticalkv_select and criticalkv_allocate need for this
- * layer, criticalkv_diagnostics included (the largest of them; compact needs none).  max_budget only sizes criticalkv_allocate's list.  Returns 0 if the descriptor is invalid.
+ * layer, criticalkv_diagnostics included (the largest of them; compact needs none).  max_budget counts for
+ * criticalkv_allocate only.  fp32 layers: includes 6 bytes per entry of w_o for the copy from which criticalkv_score
+ * computes the magnitudes on the matrix cores (in the space that max_budget adds, if that is larger); a workspace
+ * without room for it is accepted and the score runs the vector kernel.  Returns 0 if the descriptor is invalid.
  * Host-only computation.
  */
 CKV_API size_t criticalkv_workspace_bytes(const ckv_layer_desc *desc, int32_t max_budget);
@@ -160,7 +163,9 @@ CKV_API int criticalkv_prepare_gram(const ckv_layer_desc *desc, const void *w_o,
  * order layout, projection, first sweep, second sweep, combine (the projection hardly touches HBM, so a previous
  * kernel's pending write-backs drain under it and not under the bandwidth-bound sweeps).
  */
-#define CKV_STAGE_WO_LAYOUT 0   /* layout change of a canonical w_o (empty with CKV_WO_OUT_IN) */
+#define CKV_STAGE_WO_LAYOUT 0   /* layout change of w_o: of a canonical one, for CKV_NORM_L2 without a prepared constant
+                                   (bf16, d_h 128) of an output-major one; empty where none is needed and for fp32
+                                   layers, whose copy of w_o is made in the projection stage */
 #define CKV_STAGE_ATTN_STATS 1  /* first key sweep: row max and sum of exp                      */
 #define CKV_STAGE_ATTN_COLSUM 2 /* second key sweep: window-reduced softmax weights             */
 #define CKV_STAGE_VPROJ 3       /* ||V W^O||_1 per entry                                        */
@@ -235,7 +240,7 @@ CKV_API int criticalkv_prepare_wo(const ckv_layer_desc *desc, const void *w_o, v
  *      total_budget in [0, Hkv * n], floor_frac in [0, 1]
  * out: budget [batch, Hkv] int32, DEVICE; feed it to criticalkv_select
  * workspace: criticalkv_workspace_bytes(desc, max_budget) bytes with Hkv * max_budget >= P always
- *      suffice; too few bytes give CKV_E_WORKSPACE.  Hkv * n must fit an int32 (CKV_E_UNSUPPORTED).
+ *      suffice and are asked for, though less is used; too few bytes give CKV_E_WORKSPACE.  Hkv * n must fit an int32 (CKV_E_UNSUPPORTED).
  */
 CKV_API int criticalkv_allocate(const ckv_layer_desc *desc, const float *attn, int32_t total_budget,
                                 float floor_frac, int32_t *budget, void *workspace, size_t workspace_bytes,

@@ -79,7 +79,7 @@ Workspace carve_workspace(const Dims &d, int dtype, int max_budget)
     // last, so that the offsets above do not depend on max_budget
     w.alloc_tmp = off; off = align256(off + ((size_t)2 * d.batch + (size_t)d.batch * d.Hkv * (max_budget > 0 ? max_budget : 0)) * 4);
     w.total = off;
-    // fp32 layers: scratch of one score call, over the allocation's list (never live in the same call).  A workspace that
+    // fp32 layers: scratch of one score call, over the allocation's counts (never live in the same call).  A workspace that
     // ends at `total` is still accepted by every call; the score then takes the vector kernel.
     w.w_split = w.alloc_tmp;
     w.total_split = w.total;

@@ -37,7 +37,7 @@ struct Workspace {
     size_t sel_keys;   // [batch*Hkv, n] u32: stage-2 keys with stage-1 entries marked
     size_t l2_scratch; // Gram partial sums and the split bf16 Gram matrices (L2 norm only)
     size_t diag_part;  // per-chunk partial sums of the perturbation diagnostics
-    size_t alloc_tmp;  // budget allocation: pool budgets, counts and the pooled index list
+    size_t alloc_tmp;  // budget allocation: counts per head (batch * Hkv words of what max_budget reserves)
     size_t sel_scratch; // digit histograms, per-head state, per-slice counts of the selection kernels
     size_t total;
     size_t w_split;    // fp32 layers: the three-part copy of W_O; lies behind what every call needs (see carve_workspace)
@@ -108,14 +108,8 @@ size_t select_workspace_words(int heads, int n); // u32 words of histogram / sta
 hipError_t launch_select(const Dims &d, const float *attn, const float *crit, const int32_t *budget, float alpha,
                          int max_budget, int32_t *idx, int32_t *count, uint32_t *keys2, uint32_t *scratch,
                          hipStream_t s);
-// the selection in two halves: stage 1's digit histograms need attn only (they can run beside the projection),
-// the rest needs crit as well
-hipError_t launch_select_stage1_hist(int heads, int n, int protect, const float *attn, const int32_t *budget, float alpha,
-                                     int max_budget, uint32_t *keys2, uint32_t *scratch, hipStream_t s);
-hipError_t launch_select_finish(int heads, int n, int protect, const float *attn, const float *crit, const int32_t *budget,
-                                float alpha, int max_budget, int32_t *idx, int32_t *count, uint32_t *keys2,
-                                uint32_t *scratch, hipStream_t s);
-// per-head budgets from a per-batch-item total; tmp holds 2 * batch + batch * total int32
+// per-head budgets from a per-batch-item total; tmp holds batch * Hkv words, keys2 and scratch what a selection of these
+// rows needs
 hipError_t launch_allocate(const Dims &d, const float *attn, int total, float floor_frac, int32_t *budget_out,
                            uint32_t *keys2, uint32_t *scratch, int32_t *tmp, hipStream_t s);
 // perturbation quantities of a finished selection; part holds diagnostics_workspace_floats(d) floats

@@ -451,7 +451,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_write_kernel(SelArgs A)
 // ---- rows that one workgroup holds in registers ----------------------------------------------------------------------
 // The whole selection of a head in one launch: a thread keeps KPT keys of both score arrays in registers (tokens
 // (j * 1024 + thread) * 4 + e: every load is 16 bytes per lane), the digit histograms and prefix sums live in LDS.
-// The same digits, thresholds and tie order as the sliced kernels below, so the result is the same set.
+// The same digits, thresholds and tie order as the sliced kernels above, so the result is the same set.
 //   * a digit's histogram has several copies, interleaved (bin * copies + lane % copies): scores crowd into few bins, and
 //     the lanes of an LDS atomic that hit one address are served one after the other.  Summing and clearing them costs too:
 //     two copies for rows of up to 8192 keys, four for longer ones (1024 / 8192 / 24576 keys, us: two 9.9 / 13.5 / 27.6, four
@@ -764,43 +764,14 @@ static SelArgs make_sel_args(int heads, int n, int protect, const float *attn, c
     return A;
 }
 
-// First half of the selection: the three digit histograms of stage 1.  It reads attn only (not crit), so it can
-// run while the projected-value magnitudes are still being computed.
-hipError_t launch_select_stage1_hist(int heads, int n, int protect, const float *attn, const int32_t *budget, float alpha,
-                                     int max_budget, uint32_t *keys2, uint32_t *scratch, hipStream_t s)
-{
-    const SelArgs A = make_sel_args(heads, n, protect, attn, attn, budget, alpha, max_budget, nullptr, nullptr, keys2, scratch);
-    const size_t zero_words = (size_t)heads * (2 * 3 * SEL_BINS + 2 * ST_WORDS);
-    dim3 grid(A.n_slices, heads), block(SEL_THREADS);
-    hipLaunchKernelGGL(select_zero_kernel, dim3((unsigned)((zero_words + 255) / 256)), dim3(256), 0, s, scratch, zero_words);
-    hipLaunchKernelGGL((select_hist_kernel<0, 0>), grid, block, 0, s, A);
-    hipLaunchKernelGGL((select_hist_kernel<0, 1>), grid, block, 0, s, A);
-    hipLaunchKernelGGL((select_hist_kernel<0, 2>), grid, block, 0, s, A);
-    return hipGetLastError();
-}
-
-// Second half: stage-1 membership and stage-2 keys, the two remaining histograms of stage 2, the ordered write.
-hipError_t launch_select_finish(int heads, int n, int protect, const float *attn, const float *crit, const int32_t *budget,
-                                float alpha, int max_budget, int32_t *idx, int32_t *count, uint32_t *keys2,
-                                uint32_t *scratch, hipStream_t s)
-{
-    const SelArgs A = make_sel_args(heads, n, protect, attn, crit, budget, alpha, max_budget, idx, count, keys2, scratch);
-    dim3 grid(A.n_slices, heads), block(SEL_THREADS);
-    hipLaunchKernelGGL(select_mark_kernel, grid, block, 0, s, A);
-    hipLaunchKernelGGL((select_hist_kernel<1, 1>), grid, block, 0, s, A);
-    hipLaunchKernelGGL((select_hist_kernel<1, 2>), grid, block, 0, s, A);
-    hipLaunchKernelGGL(select_write_kernel, grid, block, 0, s, A);
-    return hipGetLastError();
-}
-
 // heads rows of n keys each (a row is one (batch item, kv head), or one whole batch item for the allocation)
 hipError_t launch_select_rows(int heads, int n, int protect, const float *attn, const float *crit,
                               const int32_t *budget, float alpha, int max_budget, int32_t *idx, int32_t *count,
                               uint32_t *keys2, uint32_t *scratch, hipStream_t s)
 {
     const int span = row_span(n);
+    const SelArgs A = make_sel_args(heads, n, protect, attn, crit, budget, alpha, max_budget, idx, count, keys2, scratch);
     if (span <= SEL_ROW_MAX) {
-        const SelArgs A = make_sel_args(heads, n, protect, attn, crit, budget, alpha, max_budget, idx, count, keys2, scratch);
         const dim3 grid(heads), block(ROW_THREADS);
         if (span <= 4 * ROW_THREADS) hipLaunchKernelGGL(select_row_kernel<4>, grid, block, 0, s, A);
         else if (span <= 8 * ROW_THREADS) hipLaunchKernelGGL(select_row_kernel<8>, grid, block, 0, s, A);
@@ -808,9 +779,17 @@ hipError_t launch_select_rows(int heads, int n, int protect, const float *attn, 
         else hipLaunchKernelGGL(select_row_kernel<24>, grid, block, 0, s, A);
         return hipGetLastError();
     }
-    hipError_t e = launch_select_stage1_hist(heads, n, protect, attn, budget, alpha, max_budget, keys2, scratch, s);
-    if (e != hipSuccess) return e;
-    return launch_select_finish(heads, n, protect, attn, crit, budget, alpha, max_budget, idx, count, keys2, scratch, s);
+    const size_t zero_words = (size_t)heads * (2 * 3 * SEL_BINS + 2 * ST_WORDS);
+    const dim3 grid(A.n_slices, heads), block(SEL_THREADS);
+    hipLaunchKernelGGL(select_zero_kernel, dim3((unsigned)((zero_words + 255) / 256)), dim3(256), 0, s, scratch, zero_words);
+    hipLaunchKernelGGL((select_hist_kernel<0, 0>), grid, block, 0, s, A);
+    hipLaunchKernelGGL((select_hist_kernel<0, 1>), grid, block, 0, s, A);
+    hipLaunchKernelGGL((select_hist_kernel<0, 2>), grid, block, 0, s, A);
+    hipLaunchKernelGGL(select_mark_kernel, grid, block, 0, s, A);
+    hipLaunchKernelGGL((select_hist_kernel<1, 1>), grid, block, 0, s, A);
+    hipLaunchKernelGGL((select_hist_kernel<1, 2>), grid, block, 0, s, A);
+    hipLaunchKernelGGL(select_write_kernel, grid, block, 0, s, A);
+    return hipGetLastError();
 }
 
 hipError_t launch_select(const Dims &d, const float *attn, const float *crit, const int32_t *budget, float alpha,
