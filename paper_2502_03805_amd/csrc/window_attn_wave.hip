@@ -374,12 +374,12 @@ bool attn_wave_supported(const Dims &d)
 // (its query fragments, up to 32 KiB, worth c keys) over more key blocks, few fill the chip: it has 1024 SIMDs, and a
 // round's time goes with the waves of the fullest one -- a little over one, two or three waves' time while it holds fewer
 // than four, which do not cover each other's waits.  The choice is the cheapest by that count (measured within 3 % of the
-// best of the seven: 5:1 group with a 64-row window, 2000 .. 131072 tokens; 4:1 group at d_h 64, 1500 .. 4 x 32768).
+// best of the seven: 5:1 group with a 64-row window, 2000 .. 131072 tokens; groups of 2 to 16 at d_h 64, 2048 .. 131072).
 static int attn_kpw(const Dims &d, int groups, int row_blocks, double *cost)
 {
     const long long heads = (long long)d.batch * d.Hkv;
     const int choices[] = {1024, 768, 512, 384, 256, 192, AM_MIN_KPW};
-    const double c = 35.0 + 35.0 * row_blocks;
+    const double c = (d.dh == 128 ? 35.0 : 20.0) * (1 + row_blocks);
     int best = AM_MIN_KPW;
     double least = 0.0;
     for (int kpw : choices) {
@@ -389,7 +389,7 @@ static int attn_kpw(const Dims &d, int groups, int row_blocks, double *cost)
         if (least == 0.0 || all < least) { least = all; best = kpw; }
     }
     // a key block costs its row blocks and what is paid once for all of them (its loads, its fragments' reads)
-    *cost = least * (row_blocks + (d.dh == 128 ? 2.0 : 1.0));
+    *cost = least * (row_blocks + (d.dh == 128 ? 2.0 : 0.7));
     return best;
 }
 

@@ -352,8 +352,8 @@ def wave_heads(dh, G, kv_heads, W, n):
         for kpw in (1024, 768, 512, 384, 256, 192, 128):
             chunks = (-(-n // kpw) + 3) // 4
             rounds = (groups * ((kv_heads * chunks + 7) // 8) + 31) // 32
-            least.append({1: 1.35, 2: 2.2, 3: 3.1}.get(rounds, rounds) * (kpw + 35 + 35 * h * blocks))
-        return min(least) * (h * blocks + (2 if dh == 128 else 1)) * (1.04 if h > 1 and h * blocks == 4 else 1)
+            least.append({1: 1.35, 2: 2.2, 3: 3.1}.get(rounds, rounds) * (kpw + (35 if dh == 128 else 20) * (1 + h * blocks)))
+        return min(least) * (h * blocks + (2 if dh == 128 else 0.7)) * (1.04 if h > 1 and h * blocks == 4 else 1)
 
     return min(range(1, min(G, 4 // blocks) + 1), key=cost)
 
