@@ -40,7 +40,7 @@ struct Workspace {
     size_t alloc_tmp;  // budget allocation: counts per head (batch * Hkv words of what max_budget reserves)
     size_t sel_scratch; // digit histograms, per-head state, per-slice counts of the selection kernels
     size_t total;
-    size_t w_split;    // fp32 layers: the three-part copy of W_O; lies behind what every call needs (see carve_workspace)
+    size_t w_split;    // fp32 layers: the two-part copy of W_O; lies behind what every call needs (see carve_workspace)
     size_t total_split;
     int max_chunks;    // capacity of stats_part per window row
 };
@@ -86,11 +86,11 @@ hipError_t launch_vproj_mfma(const Dims &d, const void *v, const void *w_t, floa
 // Row blocks per wave of a projection launch: of `choices`, the one whose rounds of workgroups cost least (the first of
 // equals).  An XCD runs 64 workgroups at a time; a round costs RB + c2 with more than 32 of them, 0.48 RB + c1 with fewer.
 int cheapest_rounds(const Dims &d, int rows_per_block, double c2, double c1, const int *choices, int count);
-// the same (either norm) for fp32 layers, on the bf16 matrix cores with every operand split into three parts; w_o in
-// either layout, w3 holds vproj_split_bytes(d) of scratch
+// the same (either norm) for fp32 layers, on the f16 matrix cores with every operand split into two parts; w_o in
+// either layout, scratch holds vproj_split_bytes(d)
 bool vproj_split_supported(const Dims &d);
 size_t vproj_split_bytes(const Dims &d);
-hipError_t launch_vproj_split(const Dims &d, int out_in, const void *v, const void *w_o, void *w3, float *vnorm,
+hipError_t launch_vproj_split(const Dims &d, int out_in, const void *v, const void *w_o, void *scratch, float *vnorm,
                               hipStream_t s);
 // L2 norm through the Gram matrix W_O^h W_O^h^T (bf16, d_h = 128)
 bool vproj_l2_mfma_supported(const Dims &d);

@@ -1,134 +1,164 @@
-// Per-entry L1 (or L2) magnitude of the projected value for fp32 layers, on the bf16 matrix cores
+// Per-entry L1 (or L2) magnitude of the projected value for fp32 layers, on the f16 matrix cores
 // (Theorem 3.3; Algorithm 1, lines 2-3):  N^h_i = sum_c | sum_t V^g[i,t] * W_O^h[t,c] |.
 //
-// An fp32 number (of magnitude 2^-60 to 2^60, or zero) is the sum of three bf16 numbers (3 x 8 significant bits):
-//   x = x0 + x1 + x2,  x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1), both differences exact.
-// With round-to-nearest |x1| <= 2^-9 |x0| and |x2| <= 2^-18 |x0|, so of the nine products of v * w the three that are
-// left out (v1 w2, v2 w1, v2 w2) are below 2^-26 of it, under half an ulp of the fp32 product; the six others are exact
-// in the MFMA's fp32 accumulators and are added smallest first.  Nothing is held in 16 bits that was held in 32: the
-// three parts together are the number.
+// An fp32 number is the sum of two f16 numbers once a power of two has brought it into f16's range:
+//   x * s = hi + lo,  hi = f16(x * s), lo = f16(x * s - hi), the difference exact.
+// A token's row of V and a tile of W_O (d_h rows by 32 columns of a head) have a scale each that takes their largest
+// entry to [2^14, 2^15).  lo rounds by at most 2^-24 of x (rms 2^-26), and by 2^-40 of the row's or tile's largest entry
+// where it is subnormal (the instruction takes subnormal operands as they are).  Of the four products of v * w the one that
+// is left out, lo * lo, is at most 2^-24 of it (rms 2^-27); the three others are exact in the MFMA's fp32 accumulators and
+// are added smallest first.  Nothing is held in 16 bits that was held in 32: the two parts together are the number.
 //
-//   split     W_O once per call into [head][d_model][3 parts][d_h] (and from the canonical layout to output-major)
-//   project   the tiling of the bf16 kernel: a wave keeps RB blocks of 16 token rows (all three parts) as MFMA
-//             fragments, the head's parts stream through LDS in tiles of 32 columns (24 KiB at d_h 128, double
-//             buffered, direct buffer->LDS loads, 16-byte chunks swizzled), six MFMAs per (k-step, row block), the
-//             previous column block's |acc| drained under them.  Rows that meet an entry outside that range are computed
-//             again from the fp32 operands (exact_rows), so that they get what fp32 products give.
+//   split     W_O once per call into [head][d_model][2 parts][d_h] (and from the canonical layout to output-major), with
+//             a factor per tile that undoes its scale
+//   project   the tiling of the bf16 kernel: a wave keeps RB blocks of 16 token rows (both parts) as MFMA fragments, the
+//             head's parts stream through LDS in tiles of 32 columns (16 KiB at d_h 128, double buffered, direct
+//             buffer->LDS loads, 16-byte chunks swizzled), three MFMAs per (k-step, row block), the previous column
+//             block's |acc| times the tile's factor added up under them.  Rows whose operands do not fit the scheme are
+//             computed again from the fp32 operands (exact_rows): those that meet an infinity, a NaN or a row or tile
+//             whose largest entry lies outside 2^-60 .. 2^60 (they come out as NaN), and those whose result is so small
+//             against their operands' largest entries that the error of the small entries might show (VS_SMALL).
 //
-// What bounds it: the matrix cores; six bf16 MFMAs per fp32 product still leave 2.7 times the rate of the fp32 MFMA
-// (157 TFLOP/s nominal).  Measured at 16 query heads over 4 kv heads, d_h 128, d_model 2048, 8192 tokens: the score call
-// 2.57 ms with the vector kernel (27 TFLOP/s), 0.293 ms with this one; 4 heads, d_h 64, d_model 256, 1024 tokens: 119 and
-// 21 us.  One product may be off by 9.8e-8 of itself (an fp32 fma: 6.0e-8; rms 2.60e-8 and 2.53e-8), but the sums run in
-// 16 accumulators instead of one: the magnitudes' error against 64 bits (2-norm) is 5.7e-8 where the vector kernel has
-// 6.7e-7 (d_model 2048), and 4.2e-8 where it has 2.4e-7 (d_model 256).
+// What bounds it: the matrix cores, at three f16 MFMAs per fp32 product, 5 times the rate of the fp32 MFMA (157 TFLOP/s
+// nominal).  (Three bf16 parts per operand and six products, which need no scales, took twice the matrix work.)
+// Measured, score call at 16 query heads over 4 kv heads, d_h 128, d_model 2048, 8192 tokens: 2.57 ms on the vector ALUs
+// (27 TFLOP/s), 0.287 with the six bf16 products, 0.174 like this (the project kernel 240 -> 139 us).  The magnitudes' error
+// against 64 bits (2-norm, means over 9 and 30 layers): d_model 2048 6.7e-7 / 5.7e-8 / 4.9e-8, d_model 256 and d_h 64
+// 2.4e-7 / 4.2e-8 / 3.3e-8 (vector / six bf16 products / this, whose last additions are in 64 bits).
 #include <type_traits>
 
 #include "common.hpp"
 
 namespace ckv {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef _Float16 f16_t;
+typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int VS_THREADS = 256;
 constexpr int VS_WAVES = 4;
 constexpr int VS_TN = 32;   // output columns per LDS tile (every supported d_model is a multiple)
-constexpr int VS_PARTS = 3;
+constexpr int VS_PARTS = 2;
+// A row's sum of scaled |products| over d_model is typically 2^29 per column in units of the columns' factors.  What the
+// parts leave out of small entries is at most 2^-9 per product (2^-24 of 2^15, times 2^15), random in sign: below 2^-24 of a
+// sum of 2^19 per column.  Rows under that are computed again; no row of which less than all but 2^-10 cancels is.
+constexpr float VS_SMALL = 524288.0f;
 
 #define LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
-// The three bf16 parts of x.  They are x itself, and every product of two parts is exact, for zero and for magnitudes from
-// 2^-60 up to 2^60: no part and no product lies below fp32's smallest subnormal (below 2^-110 the third part would fall
-// under bf16's), no sum of products overflows.  Any other x (infinity and NaN among them) becomes a NaN, and the project
-// kernel computes the rows that come out as NaN again, in fp32.  Random values of order one or 1e-2 are never that small.
-__device__ __forceinline__ void split3(float x, uint32_t &p0, uint32_t &p1, uint32_t &p2)
+// The power of two that takes a largest magnitude (its bits) to [2^14, 2^15), and its inverse.  Zero needs none; for any
+// other magnitude outside 2^-60 .. 2^60 (infinities and NaN too) both are NaN, and so is every result they meet.
+__device__ __forceinline__ void part_scale(uint32_t largest, float &up, float &down)
 {
-    const uint32_t u = __float_as_uint(x);
-    const bool has_parts = ((u >> 23) & 0xFFu) - (127u - 60u) < 120u || (u << 1) == 0u;
-    p0 = has_parts ? (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16 : 0x7FC0u;
-    const float r = x - __uint_as_float(p0 << 16);
-    const uint32_t ur = __float_as_uint(r);
-    p1 = (ur + 0x7FFFu + ((ur >> 16) & 1u)) >> 16;
-    const float r2 = r - __uint_as_float(p1 << 16);
-    p2 = __float_as_uint(r2) >> 16; // at most 8 significant bits are left: exact
+    const uint32_t e = largest >> 23; // (the sign bit is clear)
+    const bool fits = e - (127u - 60u) < 120u;
+    up = __uint_as_float(fits ? (127u + 127u + 14u - e) << 23 : largest ? 0x7FC00000u : 0x3F800000u);
+    down = __uint_as_float(fits ? (e - 14u) << 23 : largest ? 0x7FC00000u : 0u);
 }
 
-// Eight consecutive values as three fragments.
-__device__ __forceinline__ void split8(const float4 &a, const float4 &b, bf16x8 (&f)[VS_PARTS])
+// Eight consecutive values, scaled, as two fragments.
+__device__ __forceinline__ void split8(const float (&x)[8], float scale, f16x8 &hi, f16x8 &lo)
 {
-    const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-    uint32_t w[VS_PARTS][4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        uint32_t lo[VS_PARTS], hi[VS_PARTS];
-        split3(x[2 * e], lo[0], lo[1], lo[2]);
-        split3(x[2 * e + 1], hi[0], hi[1], hi[2]);
-#pragma unroll
-        for (int p = 0; p < VS_PARTS; ++p) w[p][e] = lo[p] | (hi[p] << 16);
+    for (int e = 0; e < 8; ++e) {
+        const float y = x[e] * scale;
+        hi[e] = (f16_t)y;
+        lo[e] = (f16_t)(y - (float)hi[e]);
     }
+}
+
+__device__ __forceinline__ uint32_t largest8(const float (&x)[8])
+{
+    uint32_t m = 0u; // magnitudes compare as their bits do, and a NaN is the largest of all
 #pragma unroll
-    for (int p = 0; p < VS_PARTS; ++p) f[p] = __builtin_bit_cast(bf16x8, make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]));
+    for (int e = 0; e < 8; ++e) m = max(m, __float_as_uint(x[e]) & 0x7FFFFFFFu);
+    return m;
+}
+
+__device__ __forceinline__ void load_eight(const float *p, float (&x)[8])
+{
+    const float4 a = reinterpret_cast<const float4 *>(p)[0], b = reinterpret_cast<const float4 *>(p)[1];
+    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+    x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
 }
 
 // ---- split of W_O -----------------------------------------------------------------------------------
-// Output-major source [d_model][H * d_h]: a thread takes 8 neighbouring values of one output column.
-__global__ __launch_bounds__(256) void split_wo_kernel(const float *__restrict__ w, bf16_t *__restrict__ out, int H, int dh,
-                                                       int dm)
+// One workgroup per (tile of VS_TN columns, head); a thread takes 8 neighbouring values of one column (two of them at
+// d_h 128).  OUT_IN: source [d_model][H * d_h].  Else [H * d_h][d_model], turned in LDS on the way.
+template <int DH, bool OUT_IN>
+__global__ __launch_bounds__(VS_THREADS) void split_wo_kernel(const float *__restrict__ w, f16_t *__restrict__ out,
+                                                              float *__restrict__ factor, int H, int dm)
 {
-    const int per_col = H * dh / 8;
-    const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= (size_t)dm * per_col) return;
-    const int c = (int)(t / per_col), e = (int)(t % per_col) * 8, h = e / dh, d = e % dh;
-    const float4 *src = reinterpret_cast<const float4 *>(w + (size_t)c * H * dh + e);
-    bf16x8 f[VS_PARTS];
-    split8(src[0], src[1], f);
-    bf16_t *dst = out + ((size_t)h * dm + c) * VS_PARTS * dh + d;
+    constexpr int PER = VS_TN * DH / 8 / VS_THREADS, PIECES = DH / 8; // pieces of 8 values: per thread, per column
+    __shared__ float tile[OUT_IN ? 1 : DH][VS_TN + 1];
+    __shared__ uint32_t largest[VS_WAVES];
+    const int h = blockIdx.y, c0 = blockIdx.x * VS_TN; // d_model is a multiple of VS_TN
+    float x[PER][8];
+    if constexpr (!OUT_IN) {
+        const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
 #pragma unroll
-    for (int p = 0; p < VS_PARTS; ++p) *reinterpret_cast<bf16x8 *>(dst + (size_t)p * dh) = f[p];
-}
-
-// Canonical source [H * d_h][d_model]: a 64 x 32 block (d_h by columns) is turned in LDS on the way.
-__global__ __launch_bounds__(256) void split_wo_turn_kernel(const float *__restrict__ w, bf16_t *__restrict__ out, int dh,
-                                                            int dm)
-{
-    __shared__ float tile[64][33];
-    const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 64; // d_model is a multiple of 32, H * d_h one of 64
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+        for (int j = 0; j < DH / 8; ++j) tile[ty + 8 * j][tx] = w[((size_t)h * DH + ty + 8 * j) * dm + c0 + tx];
+        __syncthreads();
+    }
+    uint32_t m = 0u;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) tile[ty + 8 * j][tx] = w[(size_t)(r0 + ty + 8 * j) * dm + c0 + tx];
+    for (int u = 0; u < PER; ++u) {
+        const int piece = u * VS_THREADS + (int)threadIdx.x, c = piece / PIECES, e = piece % PIECES * 8;
+        if constexpr (OUT_IN) {
+            load_eight(w + (size_t)(c0 + c) * H * DH + h * DH + e, x[u]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[u][j] = tile[e + j][c];
+        }
+        m = max(m, largest8(x[u]));
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
+    if ((threadIdx.x & 63) == 0) largest[threadIdx.x >> 6] = m;
     __syncthreads();
-    const int c = threadIdx.x >> 3, e = (threadIdx.x & 7) * 8;
-    float x[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) x[j] = tile[e + j][c];
-    bf16x8 f[VS_PARTS];
-    split8(make_float4(x[0], x[1], x[2], x[3]), make_float4(x[4], x[5], x[6], x[7]), f);
-    const int h = r0 / dh, d = r0 % dh + e;
-    bf16_t *dst = out + ((size_t)h * dm + c0 + c) * VS_PARTS * dh + d;
+    for (int i = 0; i < VS_WAVES; ++i) m = max(m, largest[i]);
+    float up, down;
+    part_scale(m, up, down);
+    if (threadIdx.x == 0) factor[(size_t)h * (dm / VS_TN) + blockIdx.x] = down;
 #pragma unroll
-    for (int p = 0; p < VS_PARTS; ++p) *reinterpret_cast<bf16x8 *>(dst + (size_t)p * dh) = f[p];
+    for (int u = 0; u < PER; ++u) {
+        const int piece = u * VS_THREADS + (int)threadIdx.x, c = piece / PIECES, e = piece % PIECES * 8;
+        f16x8 hi, lo;
+        split8(x[u], up, hi, lo);
+        f16_t *dst = out + ((size_t)h * dm + c0 + c) * VS_PARTS * DH + e;
+        *reinterpret_cast<f16x8 *>(dst) = hi;
+        *reinterpret_cast<f16x8 *>(dst + DH) = lo;
+    }
 }
 
 // ---- projection -------------------------------------------------------------------------------------
 template <int DH>
 struct SGeo {
     static constexpr int KS = DH / 32;                     // k-steps of one 16x16x32 MFMA chain
-    static constexpr int ROW_BYTES = DH * 2;               // one part of one column: 16 or 8 chunks of 16 bytes
-    static constexpr int CPR = ROW_BYTES / 16;
-    static constexpr int COL_BYTES = VS_PARTS * ROW_BYTES; // the three parts of a column are neighbours
-    static constexpr int TILE_BYTES = VS_TN * COL_BYTES;   // 24 or 12 KiB
+    static constexpr int CPR = DH * 2 / 16;                // 16-byte chunks of one part of a column
+    static constexpr int COL_BYTES = VS_PARTS * DH * 2;    // the parts of a column are neighbours
+    static constexpr int TILE_BYTES = VS_TN * COL_BYTES;   // 16 or 8 KiB
     static constexpr int LOADS = TILE_BYTES / 1024 / VS_WAVES; // direct loads per wave per tile
-    // chunk q of a row of column c sits at slot q ^ swz(c): the 16 columns of a fragment read then fall on
-    // different banks (d_h 64: two columns share the 256 bytes of a bank row, so neighbours take the same key)
-    __host__ __device__ static constexpr int swz(int c) { return DH == 128 ? (c & 15) : ((c >> 1) & 7); }
+    // chunk q of column c (its parts' chunks counted through) sits at slot q ^ (c % 16): the 16 columns of a fragment read
+    // then fall on different banks
 };
 
-template <bool L2> __device__ __forceinline__ void drain(float &to, float x) { to = L2 ? fmaf(x, x, to) : to + fabsf(x); }
+// (NaN in either operand stays)
+template <bool L2> __device__ __forceinline__ void drain(float &to, float x, float factor)
+{
+    if (L2) {
+        const float y = x * factor;
+        to = fmaf(y, y, to);
+    } else {
+        to = fmaf(fabsf(x), factor, to);
+    }
+}
 
 // The magnitudes of VS_EXACT neighbouring rows from the fp32 operands themselves, by one wave: a lane takes every 64th
-// column, one fma chain over d_h per row.  For rows with an operand that has no three parts: rare, so all that is asked of
-// it is the rate of the vector kernel.  The score call at 16 heads over 4 kv heads, d_model 2048, 8192 tokens: 2.55 ms with
-// the vector kernel; 0.30 here, 0.44 - 0.51 with one such row, 2.05 with one in every row.
+// column, one fma chain over d_h per row.  For rows that the parts do not serve: rare, so all that is asked of it is the rate
+// of the vector kernel.  The score call at 16 heads over 4 kv heads, d_model 2048, 8192 tokens: 2.55 ms with
+// the vector kernel; 0.18 here, 0.32 with one such row, 0.39 with one in 64, 1.93 with one in every row.
 constexpr int VS_EXACT = 8;
 template <int DH, bool L2, bool OUT_IN>
 __device__ __forceinline__ void exact_rows(const float *vbase, int64_t vs2, int row, int n, const float *w, int64_t ldw, int dm,
@@ -161,7 +191,7 @@ __device__ __forceinline__ void exact_rows(const float *vbase, int64_t vs2, int 
                 for (int j = 0; j < VS_EXACT; ++j) p[j] = fmaf(v[j][t + e], x[e], p[j]);
         }
 #pragma unroll
-        for (int j = 0; j < VS_EXACT; ++j) drain<L2>(out[j], p[j]);
+        for (int j = 0; j < VS_EXACT; ++j) drain<L2>(out[j], p[j], 1.f);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1)
@@ -171,7 +201,8 @@ __device__ __forceinline__ void exact_rows(const float *vbase, int64_t vs2, int 
 
 template <int DH, int RB, bool L2>
 __global__ __launch_bounds__(VS_THREADS, 2) void vproj_split_kernel(const float *__restrict__ v, const float *__restrict__ w_o,
-                                                                    int out_in, const bf16_t *__restrict__ w3,
+                                                                    int out_in, const f16_t *__restrict__ parts,
+                                                                    const float *__restrict__ factors,
                                                                     float *__restrict__ vnorm, int H, int G, int n, int dm,
                                                                     int64_t vs0, int64_t vs1, int64_t vs2, int row_tiles,
                                                                     int heads)
@@ -190,35 +221,54 @@ __global__ __launch_bounds__(VS_THREADS, 2) void vproj_split_kernel(const float 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, kc = lane >> 4;
     const int row0 = (tile_x * VS_WAVES + wave) * (RB * 16);
+    const int tiles = dm / VS_TN;
 
-    // one head's parts: d_model * COL_BYTES (the host checks that this stays below 2 GiB)
+    // one head's parts: d_model * COL_BYTES (the host checks that this stays below 2 GiB), and its tiles' factors
     const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(w3 + (size_t)h * dm * VS_PARTS * DH), 0, dm * geo::COL_BYTES, 0x00020000);
-    // load j of this wave fills KiB m = j * 4 + wave of the tile; a lane's 16 bytes belong to column col, part row p
+        (void *)(parts + (size_t)h * dm * VS_PARTS * DH), 0, dm * geo::COL_BYTES, 0x00020000);
+    const __amdgpu_buffer_rsrc_t f_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(factors + (size_t)h * tiles), 0, tiles * 4, 0x00020000);
+    // load j of this wave fills KiB m = j * 4 + wave of the tile
     auto issue_load = [&](int tile, int j, char *buf) {
         const int kib = j * VS_WAVES + wave;
         const int byte = kib * 1024 + lane * 16;             // where this lane's chunk lands in the tile
-        const int row = byte / geo::ROW_BYTES, slot = (byte % geo::ROW_BYTES) / 16;
-        const int col = row / VS_PARTS;
-        const uint32_t voff = (uint32_t)(row * geo::ROW_BYTES + ((slot ^ geo::swz(col)) * 16));
+        const int col = byte / geo::COL_BYTES, slot = byte % geo::COL_BYTES / 16;
+        const uint32_t voff = (uint32_t)(col * geo::COL_BYTES + ((slot ^ (col & 15)) * 16));
         const uint32_t soff = (uint32_t)tile * geo::TILE_BYTES;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, LDS_PTR(buf + kib * 1024), 16, voff, soff, 0, 0);
     };
+    // a tile's factor by a vector load (a scalar one would make every wait for an LDS read wait for it too)
+    auto load_factor = [&](int tile) {
+        uint32_t zero = 0u;
+        asm volatile("" : "+v"(zero));
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(f_rsrc, zero, tile * 4, 0));
+    };
 #pragma unroll
     for (int j = 0; j < geo::LOADS; ++j) issue_load(0, j, lds);
+    float fac[2]; // of the tile at work, and of the other one: the next, and before its arrival the one before
+    fac[0] = load_factor(0);
+    fac[1] = 0.f;
 
-    // the three parts of the wave's token rows (16 rows x 32 k per fragment), resident in registers
-    bf16x8 a[RB][KS][VS_PARTS];
+    // both parts of the wave's token rows (16 rows x 32 k per fragment), resident in registers
+    f16x8 a[RB][KS][VS_PARTS];
+    float undo[RB]; // what the row's scale is undone by
     const float *vbase = v + bi * vs0 + g * vs1;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         const int row = min(row0 + rb * 16 + l16, n - 1);
         const float *p = vbase + (int64_t)row * vs2 + kc * 8;
+        float x[KS][8];
+        uint32_t m = 0u;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-            const float4 x = *reinterpret_cast<const float4 *>(p + s * 32), y = *reinterpret_cast<const float4 *>(p + s * 32 + 4);
-            split8(x, y, a[rb][s]);
+            load_eight(p + s * 32, x[s]);
+            m = max(m, largest8(x[s]));
         }
+        m = max(m, (uint32_t)__shfl_xor((int)m, 16));
+        m = max(m, (uint32_t)__shfl_xor((int)m, 32));
+        float up;
+        part_scale(m, up, undo[rb]);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) split8(x[s], up, a[rb][s][0], a[rb][s][1]);
     }
     float sum[RB][4];
 #pragma unroll
@@ -230,22 +280,22 @@ __global__ __launch_bounds__(VS_THREADS, 2) void vproj_split_kernel(const float 
     for (int p = 0; p < 2; ++p)
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) acc[p][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float fac_sum = 0.f; // over the tiles: what a sum of one per column would come to
 
-    // byte offsets of the fragments of part 0 inside a 16-column block; part p lies ROW_BYTES * p behind
-    int boff[KS];
+    // byte offsets of the fragments inside a 16-column block
+    int boff[KS][VS_PARTS];
 #pragma unroll
-    for (int s = 0; s < KS; ++s) boff[s] = l16 * geo::COL_BYTES + (((4 * s + kc) ^ geo::swz(l16)) * 16);
-    bf16x8 b[KS][VS_PARTS];
-    auto read_b = [&](const char *block, int s, int p) {
-        b[s][p] = *reinterpret_cast<const bf16x8 *>(block + boff[s] + p * geo::ROW_BYTES);
-    };
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int p = 0; p < VS_PARTS; ++p) boff[s][p] = l16 * geo::COL_BYTES + (((geo::CPR * p + 4 * s + kc) ^ l16) * 16);
+    f16x8 b[KS][VS_PARTS];
+    auto read_b = [&](const char *block, int s, int p) { b[s][p] = *reinterpret_cast<const f16x8 *>(block + boff[s][p]); };
     __syncthreads();
 #pragma unroll
     for (int s = 0; s < KS; ++s)
 #pragma unroll
         for (int p = 0; p < VS_PARTS; ++p) read_b(lds, s, p);
 
-    const int tiles = dm / VS_TN;
     auto tile_step = [&](auto buf_c, int t) {
         constexpr int BUF = decltype(buf_c)::value;
         const char *cur = lds + BUF * geo::TILE_BYTES;
@@ -253,55 +303,63 @@ __global__ __launch_bounds__(VS_THREADS, 2) void vproj_split_kernel(const float 
         const int tn = min(t + 1, tiles - 1); // the last iteration re-fetches its own tile into the idle buffer
 #pragma unroll
         for (int j = 0; j < geo::LOADS; ++j) issue_load(tn, j, nxt);
+        const float next_fac = load_factor(tn);
+        fac_sum = L2 ? fmaf(fac[BUF], fac[BUF], fac_sum) : fac_sum + fac[BUF];
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
             const int pp = cb & 1;
+            const float drained = cb == 0 ? fac[BUF ^ 1] : fac[BUF]; // the previous column block is the previous tile's last
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
                 // (part of W_O, part of V), smallest products first
-                constexpr int WP[6] = {2, 1, 0, 1, 0, 0}, VP[6] = {0, 1, 2, 0, 1, 0};
+                constexpr int WP[3] = {1, 0, 0}, VP[3] = {0, 1, 0};
 #pragma unroll
-                for (int q = 0; q < 6; ++q) {
+                for (int q = 0; q < 3; ++q) {
 #pragma unroll
                     for (int rb = 0; rb < RB; ++rb) {
                         if (s == 0 && q == 0)
-                            acc[pp][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[s][WP[q]], a[rb][s][VP[q]], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                            acc[pp][rb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b[s][WP[q]], a[rb][s][VP[q]], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
                         else
-                            acc[pp][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[s][WP[q]], a[rb][s][VP[q]], acc[pp][rb], 0, 0, 0);
+                            acc[pp][rb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b[s][WP[q]], a[rb][s][VP[q]], acc[pp][rb], 0, 0, 0);
                     }
                     // after a part's last use in this block, its slot takes the next block's fragment
-                    if (cb + 1 < CB && (q == 0 || q == 3 || q == 5)) read_b(cur + (cb + 1) * 16 * geo::COL_BYTES, s, WP[q]);
-                    // the previous column block's products, spread over the k-steps
-                    if (q < RB) {
+                    if (cb + 1 < CB && q != 1) read_b(cur + (cb + 1) * 16 * geo::COL_BYTES, s, WP[q]);
+                    // the previous column block's products, spread over the steps
+                    constexpr int STEPS = 3 * KS;
 #pragma unroll
-                        for (int e = 0; e < 4 / KS; ++e) drain<L2>(sum[q][s * (4 / KS) + e], acc[pp ^ 1][q][s * (4 / KS) + e]);
-                    }
+                    for (int x = (3 * s + q) * RB * 4 / STEPS; x < (3 * s + q + 1) * RB * 4 / STEPS; ++x)
+                        drain<L2>(sum[x % RB][x / RB], acc[pp ^ 1][x % RB][x / RB], drained);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
         }
+        fac[BUF ^ 1] = next_fac;
         __syncthreads();
 #pragma unroll
         for (int s = 0; s < KS; ++s)
 #pragma unroll
             for (int p = 0; p < VS_PARTS; ++p) read_b(nxt, s, p);
     };
-    static_assert(RB <= 6, "one row block is drained per product group");
     for (int t = 0; t < tiles; t += 2) {
         tile_step(std::integral_constant<int, 0>{}, t);
         if (t + 1 < tiles) tile_step(std::integral_constant<int, 1>{}, t + 1);
     }
+    const float last_fac = (tiles & 1) ? fac[0] : fac[1];
+    const float small = L2 ? VS_SMALL * VS_SMALL * VS_TN * fac_sum : VS_SMALL * VS_TN * fac_sum;
     float *out = vnorm + (size_t)hb * (size_t)n;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) drain<L2>(sum[rb][j], acc[(CB - 1) & 1][rb][j]);
-        float x = (sum[rb][0] + sum[rb][1]) + (sum[rb][2] + sum[rb][3]);
-        x += __shfl_xor(x, 16);
-        x += __shfl_xor(x, 32);
+        for (int j = 0; j < 4; ++j) drain<L2>(sum[rb][j], acc[(CB - 1) & 1][rb][j], last_fac);
+        // the sixteen accumulators of a row merge in 64 bits: in fp32 these four additions would be most of the result's error
+        double all = ((double)sum[rb][0] + (double)sum[rb][1]) + ((double)sum[rb][2] + (double)sum[rb][3]);
+        all += __shfl_xor(all, 16);
+        all += __shfl_xor(all, 32);
+        const float x = (float)all;
         const int row = row0 + rb * 16 + l16;
-        const bool lost = x != x; // an operand without three parts
-        if (kc == 0 && row < n && !lost) out[row] = L2 ? sqrtf(x) : x;
+        // (a row of zeros is exact as it is; a sum that overflows under its scales may not overflow without them)
+        const bool lost = !(x >= small && x < INFINITY) && undo[rb] != 0.f;
+        if (kc == 0 && row < n && !lost) out[row] = (L2 ? sqrtf(x) : x) * undo[rb];
         const uint32_t again = (uint32_t)__ballot(kc == 0 && row < n && lost); // (rows are the lanes 0 .. 15)
 #pragma unroll 1
         for (int r8 = 0; r8 < 16; r8 += VS_EXACT) {
@@ -318,62 +376,70 @@ __global__ __launch_bounds__(VS_THREADS, 2) void vproj_split_kernel(const float 
 }
 
 template <int DH, int RB>
-static void launch_project(const Dims &d, int out_in, const void *v, const void *w_o, const void *w3, float *vnorm,
-                           hipStream_t s)
+static void launch_project(const Dims &d, int out_in, const void *v, const void *w_o, const f16_t *parts, const float *factors,
+                           float *vnorm, hipStream_t s)
 {
     const int rows_per_wg = VS_WAVES * RB * 16, row_tiles = (d.n + rows_per_wg - 1) / rows_per_wg;
     const int heads = d.batch * d.H;
     const dim3 grid((unsigned)(8ll * (((long long)heads * row_tiles + 7) / 8))), block(VS_THREADS);
     if (d.norm == CKV_NORM_L2)
         hipLaunchKernelGGL((vproj_split_kernel<DH, RB, true>), grid, block, 0, s, (const float *)v, (const float *)w_o, out_in,
-                           (const bf16_t *)w3, vnorm, d.H, d.G, d.n, d.dm, d.vs[0], d.vs[1], d.vs[2], row_tiles, heads);
+                           parts, factors, vnorm, d.H, d.G, d.n, d.dm, d.vs[0], d.vs[1], d.vs[2], row_tiles, heads);
     else
         hipLaunchKernelGGL((vproj_split_kernel<DH, RB, false>), grid, block, 0, s, (const float *)v, (const float *)w_o, out_in,
-                           (const bf16_t *)w3, vnorm, d.H, d.G, d.n, d.dm, d.vs[0], d.vs[1], d.vs[2], row_tiles, heads);
+                           parts, factors, vnorm, d.H, d.G, d.n, d.dm, d.vs[0], d.vs[1], d.vs[2], row_tiles, heads);
 }
 
-size_t vproj_split_bytes(const Dims &d) { return (size_t)d.H * d.dh * d.dm * VS_PARTS * 2; }
+// The parts (4 bytes per entry) and a factor per tile; 6 bytes per entry are what callers size the workspace by.
+size_t vproj_split_bytes(const Dims &d) { return (size_t)d.H * d.dh * d.dm * 6; }
 
 bool vproj_split_supported(const Dims &d)
 {
     return (d.dh == 64 || d.dh == 128) && d.dm % VS_TN == 0 && (size_t)d.dm * VS_PARTS * d.dh * 2 < ((size_t)1 << 31) &&
-           ((long long)d.batch * d.H + 8) * (d.n / 64 + 2) < (1ll << 31) &&
-           (long long)d.dm * (d.H * (long long)d.dh / 8) < (256ll << 31) && d.H * (long long)d.dh / 64 < 65536;
+           ((long long)d.batch * d.H + 8) * (d.n / 64 + 2) < (1ll << 31) && d.H < 65536;
 }
 
-// Row blocks per wave, by the cost of the launch's rounds: an XCD holds 64 workgroups (two per CU); a round's time was
-// measured as proportional to RB + c2 with two workgroups on every CU and to 0.48 RB + c1 with one (16 heads, d_model 2048:
-// c2 = 0.40, c1 = 0.38 at d_h 128, 0.50 and 0.55 at d_h 64), as for the bf16 kernel.  The stage's time there with 1 / 2 / 3
-// blocks, us: n 1024 60 / 81 / 106, 4096 149 / 143 / 179, 6144 214 / 205 / 197, 16384 537 / 509 / 525.
+// Row blocks per wave, by the cost of the launch's rounds: an XCD holds 64 workgroups (two per CU); a round's time is
+// proportional to RB + c2 with two workgroups on every CU and to 0.48 RB + c1 with one.  Over 512 .. 16384 tokens, 16 heads,
+// every choice timed, the rule's is within 1 % of the best (3.5 % at one length).  The stage's time with 1 / 2 / 3 / 4 blocks,
+// us: d_h 128, d_model 2048: n 1024 49 / 52 / 63 / 72, 4096 96 / 87 / 102 / 82, 6144 136 / 121 / 116 / 129, 16384 334 / 294 /
+// 300 / 272; d_h 64, d_model 1024, 1 / 2 / 4 / 6 blocks: 2048 24 / 24 / 29 / 35, 8192 52 / 47 / 45 / 56, 12288 72 / 66 / 62 / 62.
 static int pick_row_blocks(const Dims &d, const int *choices, int count)
 {
-    return cheapest_rounds(d, VS_WAVES * 16, d.dh == 128 ? 0.40 : 0.50, d.dh == 128 ? 0.38 : 0.55, choices, count);
+    return cheapest_rounds(d, VS_WAVES * 16, d.dh == 128 ? 0.40 : 0.55, d.dh == 128 ? 0.38 : 0.55, choices, count);
 }
 
-hipError_t launch_vproj_split(const Dims &d, int out_in, const void *v, const void *w_o, void *w3, float *vnorm, hipStream_t s)
+template <int DH>
+static void launch_split(const Dims &d, int out_in, const void *w_o, f16_t *parts, float *factors, hipStream_t s)
 {
-    if (out_in) {
-        const size_t threads = (size_t)d.dm * (d.H * d.dh / 8);
-        hipLaunchKernelGGL(split_wo_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, (const float *)w_o,
-                           (bf16_t *)w3, d.H, d.dh, d.dm);
-    } else {
-        hipLaunchKernelGGL(split_wo_turn_kernel, dim3(d.dm / 32, d.H * d.dh / 64), dim3(256), 0, s, (const float *)w_o,
-                           (bf16_t *)w3, d.dh, d.dm);
-    }
-    if (d.dh == 64) { // (six blocks spill, and five are nowhere the best)
+    const dim3 grid(d.dm / VS_TN, d.H), block(VS_THREADS);
+    if (out_in) hipLaunchKernelGGL((split_wo_kernel<DH, true>), grid, block, 0, s, (const float *)w_o, parts, factors, d.H, d.dm);
+    else hipLaunchKernelGGL((split_wo_kernel<DH, false>), grid, block, 0, s, (const float *)w_o, parts, factors, d.H, d.dm);
+}
+
+hipError_t launch_vproj_split(const Dims &d, int out_in, const void *v, const void *w_o, void *scratch, float *vnorm, hipStream_t s)
+{
+    f16_t *parts = (f16_t *)scratch;
+    float *factors = (float *)(parts + (size_t)d.H * d.dh * d.dm * VS_PARTS);
+    if (d.dh == 64) {
+        launch_split<64>(d, out_in, w_o, parts, factors, s);
+        const int choices[] = {6, 5, 4, 3, 2, 1};
+        switch (pick_row_blocks(d, choices, 6)) {
+        case 6: launch_project<64, 6>(d, out_in, v, w_o, parts, factors, vnorm, s); break;
+        case 5: launch_project<64, 5>(d, out_in, v, w_o, parts, factors, vnorm, s); break;
+        case 4: launch_project<64, 4>(d, out_in, v, w_o, parts, factors, vnorm, s); break;
+        case 3: launch_project<64, 3>(d, out_in, v, w_o, parts, factors, vnorm, s); break;
+        case 2: launch_project<64, 2>(d, out_in, v, w_o, parts, factors, vnorm, s); break;
+        default: launch_project<64, 1>(d, out_in, v, w_o, parts, factors, vnorm, s); break;
+        }
+    } else { // (the registers hold four)
+        launch_split<128>(d, out_in, w_o, parts, factors, s);
         const int choices[] = {4, 3, 2, 1};
         switch (pick_row_blocks(d, choices, 4)) {
-        case 4: launch_project<64, 4>(d, out_in, v, w_o, w3, vnorm, s); break;
-        case 3: launch_project<64, 3>(d, out_in, v, w_o, w3, vnorm, s); break;
-        case 2: launch_project<64, 2>(d, out_in, v, w_o, w3, vnorm, s); break;
-        default: launch_project<64, 1>(d, out_in, v, w_o, w3, vnorm, s); break;
-        }
-    } else { // (the registers hold three)
-        const int choices[] = {3, 2, 1};
-        switch (pick_row_blocks(d, choices, 3)) {
-        case 3: launch_project<128, 3>(d, out_in, v, w_o, w3, vnorm, s); break;
-        case 2: launch_project<128, 2>(d, out_in, v, w_o, w3, vnorm, s); break;
-        default: launch_project<128, 1>(d, out_in, v, w_o, w3, vnorm, s); break;
+        case 4: launch_project<128, 4>(d, out_in, v, w_o, parts, factors, vnorm, s); break;
+        case 3: launch_project<128, 3>(d, out_in, v, w_o, parts, factors, vnorm, s); break;
+        case 2: launch_project<128, 2>(d, out_in, v, w_o, parts, factors, vnorm, s); break;
+        default: launch_project<128, 1>(d, out_in, v, w_o, parts, factors, vnorm, s); break;
         }
     }
     return hipGetLastError();

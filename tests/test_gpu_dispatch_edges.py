@@ -37,7 +37,7 @@ def score(P, desc, q, k, v, w_o, ws_bytes=None):
     return attn.cpu().numpy(), crit.cpu().numpy(), vnorm.cpu().numpy()
 
 
-# ---- fp32 magnitudes on the matrix cores (every operand as three bf16 parts) ---------------------------------------
+# ---- fp32 magnitudes on the matrix cores (every operand as two f16 parts) ---------------------------------------
 # n around one and several workgroups of either row-block count, d_model of one tile and of an odd number of tiles
 @pytest.mark.parametrize("norm", [1, 2])
 @pytest.mark.parametrize("wo_out_in", [False, True])
@@ -86,6 +86,34 @@ def test_fp32_magnitudes_over_the_exponent_range(P, v_scale, w_scale):
         assert (np.abs(got - ref) <= 2e-6 * ref + cfg.head_dim * cfg.d_model * 2.0 ** -150).all()
         err.append(np.abs(got / ref - 1).max())
     assert err[0] <= 1.2 * err[1] + 1.2e-7, err # a few ulp beyond the vector kernel's at most
+
+
+@pytest.mark.parametrize("norm", [1, 2])
+@pytest.mark.parametrize("dh", [64, 128])
+def test_fp32_magnitudes_of_rows_their_largest_entry_does_not_reach(P, dh, norm):
+    """A row's largest entry meets nothing (a zero row of W_O, or two opposite equal ones), so that the result comes from
+    entries 2^4 .. 2^60 smaller, and a column's entries are that much smaller than their tile's largest: the parts alone
+    would lose them.  What is kept of an entry is 2^-24 of it and 2^-40 of its row's largest; rows where that could show are
+    taken in fp32: 2e-6 as everywhere."""
+    import torch
+    n, dm = 160, 96
+    r = np.random.Generator(np.random.PCG64(dh + norm))
+    v, w = (r.standard_normal(s).astype(np.float32) for s in ((1, 2, n, dh), (2 * dh, dm)))
+    w = np.sign(w) * np.clip(np.abs(w), 1e-3, None)
+    w[5], w[dh + 7], w[dh + 9] = 0.0, w[dh + 8], np.ldexp(w[dh + 9], -45)
+    w[:, 40] = np.ldexp(w[:, 40], -33)
+    for i in range(n):
+        v[0, 0, i, 5] = np.ldexp(1.0, 4 + i % 57)
+        if i % 3:
+            v[0, 1, i, 7], v[0, 1, i, 8] = np.ldexp(1.0, i % 41), -np.ldexp(1.0, i % 41)
+    ref = magnitudes64(v, w, 2, norm)
+    cfg = CONFIGS["tiny"].with_(head_dim=dh, n_q_heads=2, n_kv_heads=2, n_ctx=n, d_model=dm, window=8)
+    q, k = torch.randn((1, 2, 8, dh), device="cuda"), torch.randn((1, 2, n, dh), device="cuda")
+    got = score(P, cfg_desc(P, cfg, norm=norm), q, k, torch.from_numpy(v).cuda(), torch.from_numpy(w).cuda())[2]
+    assert (np.abs(got[0, 0] - ref[0, 0]) <= 2e-6 * ref[0, 0]).all()
+    # (the opposite pair cancels in exact products; an fp32 chain rounds each of its d_h sums by up to 2^-24 of the pair)
+    pair = np.abs(v[0, 1, :, 7]) * (np.abs(w[dh + 8]).sum() if norm == 1 else np.linalg.norm(w[dh + 8]))
+    assert (np.abs(got[0, 1] - ref[0, 1]) <= 2e-6 * ref[0, 1] + dh * 2.0 ** -24 * pair * (np.arange(n) % 3 > 0)).all()
 
 
 @pytest.mark.parametrize("norm", [1, 2])
@@ -167,7 +195,7 @@ def test_gram_constant_against_float64(P, H, dm, wo_out_in):
 def row_blocks(dtype, dh, heads, n):
     """Row blocks per wave as the launcher chooses them: the cheapest rounds of workgroups."""
     choices, c2, c1 = {("bf16", 128): ((7, 6, 5, 4, 3, 2), 1.07, 0.90), ("bf16", 64): ((10, 8, 6, 4, 3, 2), 1.84, 1.83),
-                       ("f32", 128): ((3, 2, 1), 0.40, 0.38), ("f32", 64): ((4, 3, 2, 1), 0.50, 0.55)}[dtype, dh]
+                       ("f32", 128): ((4, 3, 2, 1), 0.40, 0.38), ("f32", 64): ((6, 5, 4, 3, 2, 1), 0.55, 0.55)}[dtype, dh]
 
     def cost(rb):
         wgs = (heads * -(-n // (64 * rb)) + 7) // 8
@@ -181,7 +209,7 @@ def row_blocks(dtype, dh, heads, n):
     ("bf16", 128, 32, 8, 128, (511, 1025, 1537, 2049, 3073, 4097, 6145, 8193)),
     ("bf16", 64, 32, 8, 256, (511, 1025, 1600, 2048, 2816, 3073, 4097, 8193, 10241)),
     ("f32", 128, 16, 4, 32, (1000, 1025, 2049, 6145)),
-    ("f32", 64, 16, 4, 32, (1025, 2049, 3073, 8193, 9300)),
+    ("f32", 64, 16, 4, 32, (900, 1025, 2049, 3073, 4099, 5128, 8193, 9300)),
 ])
 def test_magnitudes_with_every_row_block_count(P, dtype, dh, H, Hkv, dm, ns):
     """fp32 sums of exact products (bf16: d_h of them, then d_model magnitudes): 2e-6 of the result.  The lengths make the
