@@ -301,6 +301,19 @@ CKV_API int criticalkv_compact(const ckv_layer_desc *desc, const void *k, const 
                                void *hip_stream);
 
 /*
+ * criticalkv_compact with new rows behind the kept ones, in one launch: what the next pass of a chunked prefill scores.
+ *   k_out[bi,g,j,:] = k[bi,g,idx[bi,g,j],:] for j < count[bi,g];  k_out[bi,g,max_budget + i,:] = k_new[bi,g,i,:]
+ * likewise v_out [batch, Hkv, max_budget + n_new, d_h] contiguous; rows count[bi,g] .. max_budget - 1 are left untouched.
+ *
+ * in : as criticalkv_compact; k_new, v_new [batch, Hkv, n_new, d_h] with element strides {batch, head, token} and a
+ *      contiguous last dimension, 16-byte aligned rows; n_new >= 1
+ */
+CKV_API int criticalkv_compact_append(const ckv_layer_desc *desc, const void *k, const void *v, const int32_t *idx,
+                                      const int32_t *count, int32_t max_budget, const void *k_new, const void *v_new,
+                                      int32_t n_new, const int64_t *k_new_stride, const int64_t *v_new_stride,
+                                      void *k_out, void *v_out, void *hip_stream);
+
+/*
  * Measurement aids, no part of the pass: what the device sustains for the two resources the pass is priced against.
  * Benchmarks report them beside their roofline fractions (the published peaks assume clocks and access patterns
  * that real data and real kernels do not reach).

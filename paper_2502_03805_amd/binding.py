@@ -24,7 +24,7 @@ CKV_STATIC_SCRATCH_BYTES = 12 << 20
 EXPORTS = ("criticalkv_workspace_bytes", "criticalkv_score", "criticalkv_score_profiled", "criticalkv_select",
            "criticalkv_compact", "criticalkv_strerror", "criticalkv_gram_bytes", "criticalkv_prepare_gram",
            "criticalkv_allocate", "criticalkv_diagnostics", "criticalkv_select_noalloc", "criticalkv_prepared_wo_bytes",
-           "criticalkv_prepare_wo", "criticalkv_probe_mfma_bf16", "criticalkv_probe_hbm_read")
+           "criticalkv_prepare_wo", "criticalkv_probe_mfma_bf16", "criticalkv_probe_hbm_read", "criticalkv_compact_append")
 STAGES = ("wo_layout", "attn_stats", "attn_colsum", "vproj", "combine")
 
 
@@ -107,6 +107,8 @@ def load() -> ctypes.CDLL:
         lib.criticalkv_diagnostics.argtypes = [dp, vp, vp, vp, vp, vp, i32, vp, vp, ctypes.c_size_t, vp]
         lib.criticalkv_compact.restype = ctypes.c_int
         lib.criticalkv_compact.argtypes = [dp, vp, vp, vp, vp, i32, vp, vp, vp]
+        lib.criticalkv_compact_append.restype = ctypes.c_int
+        lib.criticalkv_compact_append.argtypes = [dp, vp, vp, vp, vp, i32, vp, vp, i32, vp, vp, vp, vp, vp]
         lib.criticalkv_strerror.restype = ctypes.c_char_p
         lib.criticalkv_strerror.argtypes = [ctypes.c_int]
         _lib = lib
@@ -240,3 +242,14 @@ def criticalkv_compact(desc: LayerDesc, k, v, idx, count, max_budget: int, k_out
                                    _ptr(k_out), _ptr(v_out), _stream(stream))
     if rc != CKV_OK:
         raise CriticalKVError(rc, "criticalkv_compact")
+
+
+def criticalkv_compact_append(desc: LayerDesc, k, v, idx, count, max_budget: int, k_new, v_new, k_out, v_out, *,
+                              stream=None) -> None:
+    """k_new, v_new: [b, Hkv, n_new, d_h], any strides over the first three dimensions."""
+    strides = [(ctypes.c_int64 * 3)(*t.stride()[:3]) for t in (k_new, v_new)]
+    rc = load().criticalkv_compact_append(ctypes.byref(desc), _ptr(k), _ptr(v), _ptr(idx), _ptr(count), int(max_budget),
+                                          _ptr(k_new), _ptr(v_new), int(k_new.shape[2]), *strides, _ptr(k_out),
+                                          _ptr(v_out), _stream(stream))
+    if rc != CKV_OK:
+        raise CriticalKVError(rc, "criticalkv_compact_append")

@@ -465,6 +465,29 @@ int criticalkv_compact(const ckv_layer_desc *desc, const void *k, const void *v,
     return e == hipSuccess ? CKV_OK : CKV_E_HIP;
 }
 
+int criticalkv_compact_append(const ckv_layer_desc *desc, const void *k, const void *v, const int32_t *idx,
+                              const int32_t *count, int32_t max_budget, const void *k_new, const void *v_new, int32_t n_new,
+                              const int64_t *k_new_stride, const int64_t *v_new_stride, void *k_out, void *v_out,
+                              void *hip_stream)
+{
+    Dims d;
+    int rc = resolve(desc, &d);
+    if (rc != CKV_OK) return rc;
+    if (!k || !v || !idx || !count || !k_new || !v_new || !k_new_stride || !v_new_stride || !k_out || !v_out) return CKV_E_INVALID_ARG;
+    if (misaligned16(k) || misaligned16(v) || misaligned16(k_new) || misaligned16(v_new) || misaligned16(k_out) || misaligned16(v_out))
+        return CKV_E_INVALID_ARG;
+    if (max_budget < 1 || max_budget > d.n || n_new < 1 || n_new > INT32_MAX - max_budget) return CKV_E_INVALID_ARG;
+    const int64_t per16 = 16 / (int64_t)elem_size(desc->dtype);
+    for (const int64_t *st : {k_new_stride, v_new_stride})
+        for (int j = 0; j < 3; ++j) {
+            if (st[j] < 0) return CKV_E_INVALID_ARG;
+            if (st[j] % per16) return CKV_E_UNSUPPORTED;
+        }
+    hipError_t e = launch_compact_append(d, desc->dtype, k, v, idx, count, max_budget, k_new, v_new, n_new, k_new_stride,
+                                         v_new_stride, k_out, v_out, (hipStream_t)hip_stream);
+    return e == hipSuccess ? CKV_OK : CKV_E_HIP;
+}
+
 const char *criticalkv_strerror(int code)
 {
     switch (code) {

@@ -119,5 +119,9 @@ hipError_t launch_diagnostics(const Dims &d, int dtype, int out_in, const void *
                               int max_budget, float *part, float *out, hipStream_t s);
 hipError_t launch_compact(const Dims &d, int dtype, const void *k, const void *v, const int32_t *idx,
                           const int32_t *count, int max_budget, void *k_out, void *v_out, hipStream_t s);
+// the same with n_new rows (strides in elements) behind the max_budget gathered ones of every head
+hipError_t launch_compact_append(const Dims &d, int dtype, const void *k, const void *v, const int32_t *idx,
+                                 const int32_t *count, int max_budget, const void *k_new, const void *v_new, int n_new,
+                                 const int64_t *ks_new, const int64_t *vs_new, void *k_out, void *v_out, hipStream_t s);
 
 } // namespace ckv

@@ -122,6 +122,18 @@ def test_null_pointers_workspace_and_ranges(lib):
     assert lib.criticalkv_compact(ctypes.byref(d), p, p, p, None, 10, p, p, None) == P.CKV_E_INVALID_ARG
 
 
+def test_compact_append_validates_before_any_device_call(lib):
+    d, p, st = good_desc(), 4096, (ctypes.c_int64 * 3)(128, 128, 128)
+
+    def call(desc=d, k_new=p, v_new=p, n_new=5, ks=st, vs=st, out=p, max_budget=10):
+        return lib.criticalkv_compact_append(ctypes.byref(desc), p, p, p, p, max_budget, k_new, v_new, n_new, ks, vs, out, p, None)
+
+    for bad in (dict(k_new=None), dict(v_new=p + 2), dict(n_new=0), dict(n_new=2 ** 31 - 5), dict(ks=None), dict(out=None),
+                dict(out=p + 8), dict(max_budget=0), dict(max_budget=d.n_ctx + 1), dict(vs=(ctypes.c_int64 * 3)(128, -128, 128))):
+        assert call(**bad) == P.CKV_E_INVALID_ARG, bad
+    assert call(ks=(ctypes.c_int64 * 3)(128, 128, 129)) == P.CKV_E_UNSUPPORTED
+
+
 def test_noalloc_select_and_prepared_wo_validate_before_any_device_call(lib):
     d = good_desc()
     buf = ctypes.create_string_buffer(1024)

@@ -459,3 +459,46 @@ def test_select_and_allocate_on_a_few_keys_in_all(P, heads, n):
         assert_select_exact(P, attn, crit, B, 0.5)
     for total in range(0, heads * n + 1):
         assert np.array_equal(run_allocate(P, attn, total, 0.25), O.allocate(attn.astype(np.float64), total, np.float32(0.25)))
+
+
+# ---- the gather with new rows behind the kept ones -------------------------------------------------------------------
+@pytest.mark.parametrize("dtype,dh", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("n,mb,n_new", [(1, 1, 1), (40, 17, 3), (300, 300, 129)])
+def test_compact_append_is_a_gather_and_a_concatenation(P, dtype, dh, n, mb, n_new):
+    """Counts below max_budget leave their rows alone; new rows with strides of their own."""
+    import torch
+    b, Hkv = 2, 3
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    cfg = CONFIGS["tiny"].with_(n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=dh, n_ctx=n, window=1, batch=b, dtype=dtype)
+    k, v = (torch.randn((b, Hkv, n, dh), device="cuda").to(dt) for _ in range(2))
+    k_new = torch.randn((b, n_new, Hkv, dh + 8), device="cuda").to(dt)[..., :dh].permute(0, 2, 1, 3)
+    v_new = torch.randn((b, Hkv, n_new + 2, dh), device="cuda").to(dt)[:, :, 1:-1]
+    count = torch.tensor([[0, 1, mb]] * b, dtype=torch.int32, device="cuda").clamp(max=mb)
+    idx = torch.stack([torch.randperm(n)[:mb].sort().values for _ in range(b * Hkv)]).view(b, Hkv, mb).int().cuda()
+    k_out = torch.full((b, Hkv, mb + n_new, dh), 7.0, device="cuda", dtype=dt)
+    v_out = torch.full_like(k_out, 7.0)
+    P.criticalkv_compact_append(cfg_desc(P, cfg), k, v, idx, count, mb, k_new, v_new, k_out, v_out)
+    for src, new, out in ((k, k_new, k_out), (v, v_new, v_out)):
+        rows = torch.gather(src, 2, idx.long()[..., None].expand(-1, -1, -1, dh))
+        rows = torch.where((torch.arange(mb, device="cuda") < count[..., None])[..., None], rows, torch.full_like(rows, 7.0))
+        assert torch.equal(out, torch.cat([rows, new], dim=2))
+
+
+def test_chunked_prefill_with_chunks_the_gather_cannot_append(P):
+    """Chunks that fit the budget, an empty one, and rows that begin off a 16-byte boundary: the same as contiguous ones."""
+    import torch
+    from paper_2502_03805_amd.chunked import chunked_prefill_evict
+    cfg = CONFIGS["llama32k"].with_(n_q_heads=4, n_kv_heads=2, d_model=128, window=16)
+    mk = lambda n: cfg_desc(P, cfg.with_(n_ctx=n), flags=P.CKV_CAUSAL_TAIL | P.CKV_PROTECT_WINDOW)
+    lengths = (60, 30, 0, 200, 77, 0, 50)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)
+    w, qs = rnd(512, 128), [rnd(1, 4, 16, 128) for _ in lengths]
+    ks, vs = ([rnd(1, 2, n, 128) for n in lengths] for _ in range(2))
+    odd = lambda t: torch.cat([t, t[..., :1]], dim=-1)[..., :128] # row stride 129
+    first = lambda i, t: t if i == 0 else odd(t)
+    a = chunked_prefill_evict(mk, qs, ks, vs, w, 100, 0.5)
+    c = chunked_prefill_evict(mk, iter(qs), [first(i, t) for i, t in enumerate(ks)], iter(vs), w, 100, 0.5)
+    assert torch.equal(a[0], c[0]) and torch.equal(a[1], c[1]) and a[0].shape == (1, 2, 100, 128) and a[0].is_contiguous()
+    assert [x is None for x in a[2]] == [True, True, True, False, False, True, False]
+    assert all((x is None) == (y is None) and (x is None or torch.equal(x, y)) for x, y in zip(a[2], c[2]))
