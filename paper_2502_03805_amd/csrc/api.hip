@@ -237,16 +237,18 @@ static int score_attention(const ScorePlan &p, const ckv_layer_desc *desc, const
         return e == hipSuccess ? CKV_OK : CKV_E_HIP;
     }
     mark(ev, 2 * CKV_STAGE_ATTN_STATS, s);
-    e = p.tile_a ? launch_attn_stats_mfma(d, q_win, k, p.part, p.chunks, s)
+    e = p.tile_a ? launch_attn_stats_mfma(d, q_win, k, p.part, s)
         : p.wave_a ? launch_attn_stats_wave(d, q_win, k, p.part, p.chunks, s)
                    : launch_attn_stats_generic(d, desc->dtype, q_win, k, p.part, p.chunks, s);
     if (e != hipSuccess) return CKV_E_HIP;
-    e = (p.tile_a || p.wave_a) ? launch_attn_stats_reduce_log2(d, p.part, p.chunks, p.stats, s)
-                               : launch_attn_stats_reduce(d, p.part, p.chunks, p.stats, s);
+    const bool merges = p.tile_a && attn_mfma_merges(d);
+    if (!merges)
+        e = (p.tile_a || p.wave_a) ? launch_attn_stats_reduce_log2(d, p.part, p.chunks, p.stats, s)
+                                   : launch_attn_stats_reduce(d, p.part, p.chunks, p.stats, s);
     if (e != hipSuccess) return CKV_E_HIP;
     mark(ev, 2 * CKV_STAGE_ATTN_STATS + 1, s);
     mark(ev, 2 * CKV_STAGE_ATTN_COLSUM, s);
-    e = p.tile_a ? launch_attn_colsum_mfma(d, q_win, k, p.stats, p.a_raw, s)
+    e = p.tile_a ? launch_attn_colsum_mfma(d, q_win, k, merges ? p.part : p.stats, p.a_raw, s)
         : p.wave_a ? launch_attn_colsum_wave(d, q_win, k, p.stats, p.a_raw, s)
                    : launch_attn_colsum_generic(d, desc->dtype, q_win, k, p.stats, p.a_raw, s);
     if (e != hipSuccess) return CKV_E_HIP;
@@ -296,8 +298,13 @@ static int score_impl(const ckv_layer_desc *desc, const void *q_win, const void 
     // it, and the two key sweeps, which live on HBM bandwidth, find the memory system quiet (a streaming read right
     // after a large write runs at 3.3 instead of 5.2 TB/s on this part).
     if ((rc = score_layout(p, desc, w_o, ev)) != CKV_OK) return rc;
-    if ((rc = score_magnitudes(p, desc, v, w_o, ev)) != CKV_OK) return rc;
-    if ((rc = score_attention(p, desc, q_win, k, ev)) != CKV_OK) return rc;
+    if (!ev && p.tile_a && p.mfma_v && !p.attn_only && vproj_colsum_taken(p.d)) { // (stages are timed one by one)
+        if (launch_attn_stats_mfma(p.d, q_win, k, p.part, p.s) != hipSuccess) return CKV_E_HIP;
+        if (launch_vproj_colsum(p.d, q_win, k, v, p.w_t, p.part, p.a_raw, p.vnorm, p.s) != hipSuccess) return CKV_E_HIP;
+    } else {
+        if ((rc = score_magnitudes(p, desc, v, w_o, ev)) != CKV_OK) return rc;
+        if ((rc = score_attention(p, desc, q_win, k, ev)) != CKV_OK) return rc;
+    }
     mark(ev, 2 * CKV_STAGE_COMBINE, p.s);
     if (launch_combine(p.d, p.a_raw, p.vnorm, attn, crit, p.s) != hipSuccess) return CKV_E_HIP;
     mark(ev, 2 * CKV_STAGE_COMBINE + 1, p.s);

@@ -64,8 +64,9 @@ hipError_t launch_attn_stats_reduce(const Dims &d, const float *part, int chunks
 // window attention, pass 2: a_raw[b,h,i] = reduce_w exp(s - max_w) / sum_w
 hipError_t launch_attn_colsum_generic(const Dims &d, int dtype, const void *q, const void *k, const float *stats,
                                       float *a_raw, hipStream_t s);
-hipError_t launch_attn_stats_mfma(const Dims &d, const void *q, const void *k, float *part, int chunks,
-                                  hipStream_t s);
+// (attn_mfma_merges: pass 2 takes the chunks' pairs in `part` instead of the reduced rows)
+bool attn_mfma_merges(const Dims &d);
+hipError_t launch_attn_stats_mfma(const Dims &d, const void *q, const void *k, float *part, hipStream_t s);
 // matrix-core path: partials are in the log2 domain; per row E = log2(sum 2^t) (+ log2 W for the mean)
 hipError_t launch_attn_stats_reduce_log2(const Dims &d, const float *part, int chunks, float *stats, hipStream_t s);
 hipError_t launch_attn_colsum_mfma(const Dims &d, const void *q, const void *k, const float *stats, float *a_raw,
@@ -83,6 +84,10 @@ hipError_t launch_attn_f32(const Dims &d, const void *q, const void *k, float *p
 hipError_t launch_vproj_generic(const Dims &d, int dtype, const void *v, const void *w_t, float *vnorm,
                                 hipStream_t s);
 hipError_t launch_vproj_mfma(const Dims &d, const void *v, const void *w_t, float *vnorm, hipStream_t s);
+// the projection and pass 2 of the shared-tile attention in one launch (short contexts)
+bool vproj_colsum_taken(const Dims &d);
+hipError_t launch_vproj_colsum(const Dims &d, const void *q, const void *k, const void *v, const void *w_t, const float *part,
+                               float *a_raw, float *vnorm, hipStream_t s);
 // Row blocks per wave of a projection launch: of `choices`, the one whose rounds of workgroups cost least (the first of
 // equals).  An XCD runs 64 workgroups at a time; a round costs RB + c2 with more than 32 of them, 0.48 RB + c1 with fewer.
 int cheapest_rounds(const Dims &d, int rows_per_block, double c2, double c1, const int *choices, int count);

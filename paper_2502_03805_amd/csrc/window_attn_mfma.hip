@@ -18,89 +18,9 @@
 // lane % 32 at k offset 8 * (lane / 32); accumulator j is row 8*(j/4) + 4*(lane/32) + j%4, column lane%32.
 //   pass 1 computes K . Q^T (lane = one query row, registers = 16 keys): row statistics stay lane-local;
 //   pass 2 computes Q . K^T (lane = one key, registers = 16 query rows): the window sum is lane-local.
-#include <float.h>
-
-#include "common.hpp"
+#include "window_attn_mfma.hpp"
 
 namespace ckv {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-
-constexpr int AM_DH = 128;
-constexpr int AM_TILE_KEYS = 64;
-constexpr int AM_TILE_BYTES = AM_TILE_KEYS * AM_DH * 2; // 16 KiB
-constexpr int AM_CHUNK_MIN = 256;                       // fewest keys per workgroup (the host picks 256, 512 or 1024)
-constexpr int AM_MAX_WAVES = 16;                       // pass 1: waves per workgroup, one per (head, 32-row block)
-constexpr int AM_COLSUM_WAVES = 8;                     // pass 2: waves per workgroup, one per head
-constexpr float AM_LOG2E = 1.4426950408889634f;
-constexpr float AM_NEG = -1.0e30f;
-
-#define LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
-#define GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void *)(p))
-
-struct AttnArgs {
-    const bf16_t *q;
-    const bf16_t *k;
-    int H, G, n, W, chunks;
-    int chunk_keys; // keys per workgroup, a multiple of the tile
-    int qbs;        // 32-row blocks of the window: a wave owns one (query head, row block)
-    int wpw;        // (head, row block) pairs per workgroup: a multiple of qbs, so a head's blocks share a workgroup
-    int causal; // window row w sees keys <= n - W + w only
-    float c; // scale * log2(e)
-    int64_t ks0, ks1, ks2;
-};
-
-// Q fragments of one head: block qb covers window rows (qb0+qb)*32 .. +31 (zero past W).
-template <int QB>
-__device__ __forceinline__ void load_q_frags(const AttnArgs &A, int bi, int head, int qb0, int l32, int half,
-                                             bf16x8 (&qf)[QB][8])
-{
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const int w = (qb0 + qb) * 32 + l32;
-        const bf16_t *p = A.q + (((size_t)bi * A.H + head) * A.W + min(w, A.W - 1)) * AM_DH + half * 8;
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            bf16x8 x = *reinterpret_cast<const bf16x8 *>(p + s * 16);
-            if (w >= A.W) x = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-            qf[qb][s] = x;
-        }
-    }
-}
-
-// Direct global->LDS load of one 64-key tile, shared among the nw waves of the workgroup.
-// Instruction j fills LDS KiB j = keys 4j .. 4j+3; lane i writes slot i % 16 of key 4j + i / 16 and
-// fetches 16-byte chunk (i % 16) ^ (key & 15) of that key row.  Rows past n-1 re-read row n-1.
-// The loads are buffer loads (not flat/global ones) so that the compiler keeps exact LDS wait counts.
-__device__ __forceinline__ void load_k_tile(__amdgpu_buffer_rsrc_t krsrc, int64_t ks2, int key0, int n, char *buf,
-                                            int wave, int nw, int lane)
-{
-    for (int j = wave; j < AM_TILE_BYTES / 1024; j += nw) {
-        const int key_in_tile = 4 * j + (lane >> 4);
-        const int key = min(key0 + key_in_tile, n - 1);
-        const uint32_t voff = (uint32_t)(((int64_t)key * ks2 + (((lane & 15) ^ (key_in_tile & 15)) * 8)) * 2);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, LDS_PTR(buf + j * 1024), 16, voff, 0, 0, 0);
-    }
-}
-
-// Buffer descriptor over one kv head's keys (token stride ks2 elements; the host checks n * ks2 * 2 < 2 GiB).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_k_rsrc(const bf16_t *kbase, int64_t ks2, int n)
-{
-    return __builtin_amdgcn_make_buffer_rsrc((void *)kbase, 0, (int)(((int64_t)(n - 1) * ks2 + AM_DH) * 2), 0x00020000);
-}
-
-__device__ __forceinline__ void read_k_frags(const char *tile, int kb, int l32, int half, bf16x8 (&kf)[8])
-{
-    const char *row = tile + (kb * 32 + l32) * (AM_DH * 2);
-#pragma unroll
-    for (int s = 0; s < 8; ++s) kf[s] = *reinterpret_cast<const bf16x8 *>(row + (((2 * s + half) ^ (l32 & 15)) * 16));
-}
-
-__device__ __forceinline__ f32x16 zero16()
-{
-    return f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-}
 
 // ---- pass 1 ---------------------------------------------------------------------------------------
 template <int QB>
@@ -179,9 +99,9 @@ __global__ __launch_bounds__(64 * AM_MAX_WAVES) void attn_stats_mfma_kernel(Attn
         const float lt = l[qb] * __builtin_amdgcn_exp2f(m[qb] - mt) + lo * __builtin_amdgcn_exp2f(mo - mt);
         const int w = (qb0 + qb) * 32 + l32;
         if (head_ok && half == 0 && w < A.W) {
-            float *dst = part + ((((size_t)bi * A.H + head) * A.W + w) * (size_t)A.chunks + chunk) * 2;
-            dst[0] = mt;
-            dst[1] = lt;
+            const size_t bh = (size_t)bi * A.H + head;
+            const size_t at = A.merge ? (bh * A.chunks + chunk) * A.W + w : (bh * A.W + w) * A.chunks + chunk;
+            reinterpret_cast<float2 *>(part)[at] = make_float2(mt, lt);
         }
     }
 }
@@ -206,72 +126,12 @@ __global__ __launch_bounds__(64) void attn_stats_reduce_log2_kernel(const float 
     }
 }
 
-// ---- pass 2 ---------------------------------------------------------------------------------------
 template <int QB>
 __global__ __launch_bounds__(64 * AM_COLSUM_WAVES) void attn_colsum_mfma_kernel(AttnArgs A, const float *__restrict__ stats,
                                                                              float *__restrict__ a_raw)
 {
-    __shared__ __attribute__((aligned(1024))) char lds[2 * AM_TILE_BYTES];
-    const int chunk = blockIdx.x, bi = blockIdx.y / (A.H / A.G), g = blockIdx.y % (A.H / A.G);
-    const int nw = blockDim.x >> 6;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int l32 = lane & 31, half = lane >> 5;
-    const int head = g * A.G + blockIdx.z * AM_COLSUM_WAVES + wave;
-    const bool head_ok = blockIdx.z * AM_COLSUM_WAVES + wave < A.G;
-    const bf16_t *kbase = A.k + bi * A.ks0 + g * A.ks1;
-    const __amdgpu_buffer_rsrc_t krsrc = make_k_rsrc(kbase, A.ks2, A.n);
-    const int key_begin = chunk * A.chunk_keys;
-    const int key_end = min(key_begin + A.chunk_keys, A.n);
-    const int tiles = (key_end - key_begin + AM_TILE_KEYS - 1) / AM_TILE_KEYS;
-
-    bf16x8 qf[QB][8];
-    load_q_frags<QB>(A, bi, head_ok ? head : g * A.G, 0, l32, half, qf);
-    // E of the 16 window rows a lane's accumulators belong to (+inf past W: weight 0)
-    float e[QB][16];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int w = qb * 32 + 8 * (j / 4) + 4 * half + (j % 4);
-            e[qb][j] = (head_ok && w < A.W) ? stats[(((size_t)bi * A.H + head) * A.W + w) * 2] : INFINITY;
-        }
-    float *out = a_raw + ((size_t)bi * A.H + (head_ok ? head : g * A.G)) * (size_t)A.n;
-
-    load_k_tile(krsrc, A.ks2, key_begin, A.n, lds, wave, nw, lane);
-    __syncthreads();
-    for (int t = 0; t < tiles; ++t) {
-        const char *cur = lds + (t & 1) * AM_TILE_BYTES;
-        if (t + 1 < tiles)
-            load_k_tile(krsrc, A.ks2, key_begin + (t + 1) * AM_TILE_KEYS, A.n, lds + ((t + 1) & 1) * AM_TILE_BYTES, wave,
-                        nw, lane);
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            const int key0 = key_begin + t * AM_TILE_KEYS + kb * 32;
-            if (key0 >= key_end) break;
-            bf16x8 kf[8];
-            read_k_frags(cur, kb, l32, half, kf);
-            float colsum = 0.f;
-            const bool tail = A.causal && key0 + 31 > A.n - A.W; // some window rows do not see these keys
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                f32x16 acc = zero16();
-#pragma unroll
-                for (int s = 0; s < 8; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[qb][s], kf[s], acc, 0, 0, 0);
-                // acc[j]: window row qb*32 + 8*(j/4) + 4*half + j%4, key key0 + l32
-                if (tail) {
-#pragma unroll
-                    for (int j = 0; j < 16; ++j)
-                        if (key0 + l32 > A.n - A.W + qb * 32 + 8 * (j / 4) + 4 * half + (j % 4)) acc[j] = -INFINITY;
-                }
-#pragma unroll
-                for (int j = 0; j < 16; ++j) colsum += __builtin_amdgcn_exp2f(fmaf(acc[j], A.c, -e[qb][j]));
-            }
-            colsum += __shfl_xor(colsum, 32);
-            const int key = key0 + l32;
-            if (head_ok && half == 0 && key < A.n) out[key] = colsum;
-        }
-        __syncthreads();
-    }
+    __shared__ __attribute__((aligned(1024))) char lds[attn_colsum_lds<QB>()];
+    attn_colsum_body<QB>(A, stats, a_raw, lds, blockIdx.x, blockIdx.y, blockIdx.z * AM_COLSUM_WAVES);
 }
 
 bool attn_mfma_supported(const Dims &d)
@@ -291,11 +151,20 @@ static int attn_chunk_keys(const Dims &d)
 }
 int mfma_attn_chunks(const Dims &d) { const int keys = attn_chunk_keys(d); return (d.n + keys - 1) / keys; }
 
-static AttnArgs make_args(const Dims &d, const void *q, const void *k, int chunks)
+// Short contexts: the waves of pass 2 merge the chunks' pairs themselves (a few KiB out of L2 under the first key tile's
+// latency) instead of a launch of their own between the sweeps.  Attention-only call, 32 heads over 8, us,
+// launch between / merged: 12 chunks 20.8 / 18.5, 32 22.2 / 20.0, 47 25.7 / 24.7, 64 27.7 / 27.4 (256 keys each), 41.0 / 40.5 (512),
+// 94 36.0 / 37.1, 128 115.5 / 120.6 (1024): up to 64.
+constexpr int AM_MERGE_CHUNKS = 64;
+bool attn_mfma_merges(const Dims &d) { return mfma_attn_chunks(d) <= AM_MERGE_CHUNKS; }
+
+AttnArgs attn_mfma_args(const Dims &d, const void *q, const void *k)
 {
     AttnArgs A;
     A.q = (const bf16_t *)q; A.k = (const bf16_t *)k;
-    A.H = d.H; A.G = d.G; A.n = d.n; A.W = d.W; A.chunks = chunks; A.causal = d.causal;
+    A.H = d.H; A.G = d.G; A.n = d.n; A.W = d.W; A.chunks = mfma_attn_chunks(d); A.causal = d.causal;
+    A.merge = attn_mfma_merges(d);
+    A.post = d.window_sum ? 0.0f : log2f((float)d.W);
     A.chunk_keys = attn_chunk_keys(d);
     A.qbs = (d.W + 31) / 32;
     A.wpw = (AM_MAX_WAVES / A.qbs) * A.qbs;
@@ -304,11 +173,11 @@ static AttnArgs make_args(const Dims &d, const void *q, const void *k, int chunk
     return A;
 }
 
-hipError_t launch_attn_stats_mfma(const Dims &d, const void *q, const void *k, float *part, int chunks, hipStream_t s)
+hipError_t launch_attn_stats_mfma(const Dims &d, const void *q, const void *k, float *part, hipStream_t s)
 {
-    const AttnArgs A = make_args(d, q, k, chunks);
+    const AttnArgs A = attn_mfma_args(d, q, k);
     const int pairs = d.G * A.qbs, nw = pairs < A.wpw ? pairs : A.wpw;
-    dim3 grid(chunks, d.batch * d.Hkv, (pairs + A.wpw - 1) / A.wpw), block(64 * nw);
+    dim3 grid(A.chunks, d.batch * d.Hkv, (pairs + A.wpw - 1) / A.wpw), block(64 * nw);
     hipLaunchKernelGGL(attn_stats_mfma_kernel<1>, grid, block, 0, s, A, part);
     return hipGetLastError();
 }
@@ -324,7 +193,7 @@ hipError_t launch_attn_stats_reduce_log2(const Dims &d, const float *part, int c
 hipError_t launch_attn_colsum_mfma(const Dims &d, const void *q, const void *k, const float *stats, float *a_raw,
                                    hipStream_t s)
 {
-    const AttnArgs A = make_args(d, q, k, mfma_attn_chunks(d));
+    const AttnArgs A = attn_mfma_args(d, q, k);
     const int nw = d.G < AM_COLSUM_WAVES ? d.G : AM_COLSUM_WAVES;
     dim3 grid(A.chunks, d.batch * d.Hkv, (d.G + AM_COLSUM_WAVES - 1) / AM_COLSUM_WAVES), block(64 * nw);
     const int qb = (d.W + 31) / 32;

@@ -502,3 +502,42 @@ def test_chunked_prefill_with_chunks_the_gather_cannot_append(P):
     assert torch.equal(a[0], c[0]) and torch.equal(a[1], c[1]) and a[0].shape == (1, 2, 100, 128) and a[0].is_contiguous()
     assert [x is None for x in a[2]] == [True, True, True, False, False, True, False]
     assert all((x is None) == (y is None) and (x is None or torch.equal(x, y)) for x, y in zip(a[2], c[2]))
+
+
+# ---- short contexts: rows merged by the second sweep, and that sweep beside the projection ---------------------------
+@pytest.mark.parametrize("G,Hkv,W,b,norm,ns", [
+    (4, 8, 32, 1, 1, (100, 511, 600, 1025, 1601, 2100, 3072, 3500, 3700)), # every row-block count; two workgroups per CU
+    (1, 2, 7, 2, 1, (40, 257, 4100)), (3, 2, 20, 1, 1, (1, 300, 2049)), (2, 1, 33, 1, 1, (300,)), (4, 1, 32, 1, 2, (500,)),
+    (4, 2, 32, 1, None, (16383, 16384, 16385)), (2, 2, 64, 1, None, (5000,)), # 64 and 65 chunks
+])
+def test_short_contexts_against_float64(P, G, Hkv, W, b, norm, ns):
+    """fp32 softmax sums of bf16 products (d_h exact terms) and exponentials of an ulp each: 4e-6 of the result by the 2-norm;
+    the stage by stage call is the same computation in other launches."""
+    import ctypes
+    import torch
+    H = G * Hkv
+    for n in ns:
+        W_n = min(W, n)
+        cfg = CONFIGS["llama32k"].with_(n_q_heads=H, n_kv_heads=Hkv, d_model=512, n_ctx=n, window=W_n, batch=b, pool_kernel=1)
+        g = torch.Generator(device="cuda").manual_seed(n)
+        q, k, v = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in
+                   ((b, H, W_n, 128), (b, Hkv, n, 128), (b, Hkv, n, 128)))
+        w = (0.02 * torch.randn((H * 128, 512), generator=g, device="cuda")).to(torch.bfloat16)
+        for causal in (0, P.CKV_CAUSAL_TAIL):
+            desc = cfg_desc(P, cfg, norm=norm or 1, flags=causal | (0 if norm else P.CKV_ATTN_ONLY))
+            ws = torch.empty(P.workspace_bytes(desc, 1), dtype=torch.uint8, device="cuda")
+            attn, crit = (torch.full((b, Hkv, n), float("nan"), device="cuda") for _ in range(2))
+            vnorm = torch.full((b, H, n), float("nan"), device="cuda") if norm else None
+            P.criticalkv_score(desc, q, k, v, w, attn, crit, vnorm, workspace=ws)
+            s = torch.einsum("bgrwd,bgnd->bgrwn", q.double().view(b, Hkv, G, W_n, 128), k.double()) / 128 ** 0.5
+            if causal:
+                s.masked_fill_(torch.arange(n, device="cuda") > n - W_n + torch.arange(W_n, device="cuda")[:, None], -np.inf)
+            ref = s.softmax(-1).mean((2, 3))
+            assert (attn.double() - ref).norm() <= 4e-6 * ref.norm(), (n, causal)
+            if norm:
+                p = torch.einsum("bgnd,grdc->bgrnc", v.double(), w.double().view(Hkv, G, 128, 512)).reshape(b, H, n, 512)
+                ref = p.abs().sum(-1) if norm == 1 else p.square().sum(-1).sqrt()
+                assert ((vnorm.double() / ref - 1).abs() <= (2e-6 if norm == 1 else 2e-5)).all(), (n, causal)
+            again = [torch.empty_like(t) if t is not None else None for t in (attn, crit, vnorm)]
+            P.criticalkv_score_profiled(desc, q, k, v, w, *again, workspace=ws, stage_events=(ctypes.c_void_p * 10)())
+            assert all(x is None or torch.equal(x, y) for x, y in zip(again, (attn, crit, vnorm))), (n, causal)
