@@ -301,6 +301,10 @@ static int score_impl(const ckv_layer_desc *desc, const void *q_win, const void 
     if (!ev && p.tile_a && p.mfma_v && !p.attn_only && vproj_colsum_taken(p.d)) { // (stages are timed one by one)
         if (launch_attn_stats_mfma(p.d, q_win, k, p.part, p.s) != hipSuccess) return CKV_E_HIP;
         if (launch_vproj_colsum(p.d, q_win, k, v, p.w_t, p.part, p.a_raw, p.vnorm, p.s) != hipSuccess) return CKV_E_HIP;
+    } else if (!ev && p.f32_a && p.split_v && split_colsum_taken(p.d)) {
+        if (launch_score_f32_short(p.d, desc->flags & CKV_WO_OUT_IN, q_win, k, v, w_o, p.base + p.ws.w_split, p.part, p.part_floats,
+                                   p.stats, p.a_raw, p.vnorm, p.s) != hipSuccess)
+            return CKV_E_HIP;
     } else {
         if ((rc = score_magnitudes(p, desc, v, w_o, ev)) != CKV_OK) return rc;
         if ((rc = score_attention(p, desc, q_win, k, ev)) != CKV_OK) return rc;

@@ -97,6 +97,11 @@ bool vproj_split_supported(const Dims &d);
 size_t vproj_split_bytes(const Dims &d);
 hipError_t launch_vproj_split(const Dims &d, int out_in, const void *v, const void *w_o, void *scratch, float *vnorm,
                               hipStream_t s);
+// fp32 magnitudes and both sweeps, side by side where they do not depend on each other (short contexts)
+bool split_colsum_taken(const Dims &d);
+hipError_t launch_score_f32_short(const Dims &d, int out_in, const void *q, const void *k, const void *v, const void *w_o,
+                                  void *scratch, float *part, size_t part_floats, float *stats, float *a_raw, float *vnorm,
+                                  hipStream_t s);
 // L2 norm through the Gram matrix W_O^h W_O^h^T (bf16, d_h = 128)
 bool vproj_l2_mfma_supported(const Dims &d);
 size_t vproj_l2_workspace_bytes(const Dims &d);

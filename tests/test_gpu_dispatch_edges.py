@@ -541,3 +541,30 @@ def test_short_contexts_against_float64(P, G, Hkv, W, b, norm, ns):
             again = [torch.empty_like(t) if t is not None else None for t in (attn, crit, vnorm)]
             P.criticalkv_score_profiled(desc, q, k, v, w, *again, workspace=ws, stage_events=(ctypes.c_void_p * 10)())
             assert all(x is None or torch.equal(x, y) for x, y in zip(again, (attn, crit, vnorm))), (n, causal)
+
+
+@pytest.mark.parametrize("dh,H,Hkv,W,b,wo_out_in,ns", [
+    (64, 4, 4, 8, 1, True, (8, 33, 1024, 2049, 2080)),   # 65 ranges and more: the pairs are merged by a launch between
+    (64, 16, 4, 40, 1, False, (512, 1025, 2049, 3073, 4099, 5121, 6145)),
+    (128, 16, 4, 32, 1, True, (512, 1100, 2100, 3100, 4097)), (128, 2, 1, 33, 3, False, (100,)),
+])
+def test_short_fp32_contexts_against_float64(P, dh, H, Hkv, W, b, wo_out_in, ns):
+    """The sweeps beside the split and the project kernel (every row-block count, and the first lengths past them): fp32 chains
+    of d_h products and exponentials of an ulp each, 2e-6 by the 2-norm, as for the launches by themselves."""
+    import torch
+    G = H // Hkv
+    for n in ns:
+        cfg = CONFIGS["tiny"].with_(n_q_heads=H, n_kv_heads=Hkv, head_dim=dh, d_model=96, n_ctx=n, window=W, batch=b, pool_kernel=1)
+        g = torch.Generator(device="cuda").manual_seed(n)
+        q, k, v = (torch.randn(s, generator=g, device="cuda") for s in ((b, H, W, dh), (b, Hkv, n, dh), (b, Hkv, n, dh)))
+        w = torch.randn((H * dh, 96), generator=g, device="cuda")
+        for causal in (0, P.CKV_CAUSAL_TAIL):
+            desc = cfg_desc(P, cfg, flags=causal | (P.CKV_WO_OUT_IN if wo_out_in else 0))
+            attn, _, vnorm = score(P, desc, q, k, v, w.t().contiguous() if wo_out_in else w)
+            s = torch.einsum("bgrwd,bgnd->bgrwn", q.double().view(b, Hkv, G, W, dh), k.double()) / dh ** 0.5
+            if causal:
+                s.masked_fill_(torch.arange(n, device="cuda") > n - W + torch.arange(W, device="cuda")[:, None], -np.inf)
+            ref = s.softmax(-1).mean((2, 3)).cpu().numpy()
+            assert np.linalg.norm(attn - ref) <= 2e-6 * np.linalg.norm(ref), (n, causal)
+            p = torch.einsum("bgnd,grdc->bgrnc", v.double(), w.double().view(Hkv, G, dh, 96)).reshape(b, H, n, 96).abs().sum(-1)
+            assert np.abs(vnorm / p.cpu().numpy() - 1).max() <= 2e-6, (n, causal)
