@@ -16,6 +16,11 @@ __device__ __forceinline__ float bf16_to_f32(bf16_t x) { return __uint_as_float(
 __device__ __forceinline__ float to_f32(float x) { return x; }
 __device__ __forceinline__ float to_f32(bf16_t x) { return bf16_to_f32(x); }
 
+// 16 bytes past the caches' replacement order (what is read once, or written for a reader that comes much later).
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+__device__ __forceinline__ u32x4 load16_once(const void *p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p)); }
+__device__ __forceinline__ void store16_once(void *p, u32x4 x) { __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(p)); }
+
 // Problem sizes resolved from the descriptor (strides filled in).
 struct Dims {
     int batch, H, Hkv, G, dh, dm, n, W, pool_k;

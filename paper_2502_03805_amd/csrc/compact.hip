@@ -15,7 +15,14 @@ struct NewRows { // rows appended to the gathered ones (none: n = 0)
     int64_t ks0, ks1, ks2, vs0, vs1, vs2;
 };
 
-template <bool APPEND>
+// STREAM: rows pass the caches by on both sides.  Where K and V together are longer than the Infinity Cache (256 MiB) they
+// come from HBM, and in the ordinary order reads and write-backs push each other out.  8 heads of 131072 rows, us, ordinary /
+// nontemporal stores / both: 52429 kept 82 / 78 / 70 (6.1 TB/s; a copy of 1 GiB runs at 5.1), 19661 kept 33.5 / 30 / 28; fp32
+// rows, 8 heads of 60000, 18000 kept 58 / 55 / 50.  Shorter ones may still be there from the sweeps: 16 heads of 20011, 4002
+// kept, in a chain of calls on rotating inputs 11.4 / 12.4 (both).
+constexpr long long CP_STREAM_BYTES = 256ll << 20;
+
+template <bool APPEND, bool STREAM>
 __global__ __launch_bounds__(CP_THREADS) void compact_kernel(const char *__restrict__ k, const char *__restrict__ v,
                                                              const int32_t *__restrict__ idx,
                                                              const int32_t *__restrict__ count, char *__restrict__ k_out,
@@ -44,11 +51,18 @@ __global__ __launch_bounds__(CP_THREADS) void compact_kernel(const char *__restr
         vrow = v + (bi * vs0 + g * vs1 + (int64_t)i * vs2) * esize;
     }
     // the K piece and the V piece of the same row: one index read, two loads in flight per lane
-    const uint4 kk = reinterpret_cast<const uint4 *>(krow)[piece];
-    const uint4 vv = reinterpret_cast<const uint4 *>(vrow)[piece];
+    const u32x4 *kp = reinterpret_cast<const u32x4 *>(krow) + piece, *vp = reinterpret_cast<const u32x4 *>(vrow) + piece;
+    const u32x4 kk = STREAM ? load16_once(kp) : *kp;
+    const u32x4 vv = STREAM ? load16_once(vp) : *vp;
     const size_t o = ((size_t)head * (max_budget + (APPEND ? N.n : 0)) + j) * (size_t)row_bytes;
-    reinterpret_cast<uint4 *>(k_out + o)[piece] = kk;
-    reinterpret_cast<uint4 *>(v_out + o)[piece] = vv;
+    u32x4 *ko = reinterpret_cast<u32x4 *>(k_out + o) + piece, *vo = reinterpret_cast<u32x4 *>(v_out + o) + piece;
+    if (STREAM) {
+        store16_once(ko, kk);
+        store16_once(vo, vv);
+    } else {
+        *ko = kk;
+        *vo = vv;
+    }
 }
 
 template <bool APPEND>
@@ -59,7 +73,9 @@ static hipError_t launch(const Dims &d, int dtype, const void *k, const void *v,
     const int row_bytes = d.dh * esize;
     const long long threads = ((long long)max_budget + N.n) * (row_bytes / 16);
     dim3 grid((unsigned)((threads + CP_THREADS - 1) / CP_THREADS), d.batch * d.Hkv);
-    hipLaunchKernelGGL(compact_kernel<APPEND>, grid, dim3(CP_THREADS), 0, s, (const char *)k, (const char *)v, idx, count,
+    const bool stream = 2ll * d.batch * d.Hkv * d.n * row_bytes > CP_STREAM_BYTES;
+    const auto kernel = stream ? compact_kernel<APPEND, true> : compact_kernel<APPEND, false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(CP_THREADS), 0, s, (const char *)k, (const char *)v, idx, count,
                        (char *)k_out, (char *)v_out, d.Hkv, d.n, max_budget, row_bytes, d.ks[0], d.ks[1], d.ks[2],
                        d.vs[0], d.vs[1], d.vs[2], esize, N);
     return hipGetLastError();
