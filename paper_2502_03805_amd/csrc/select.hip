@@ -61,8 +61,8 @@ struct SelArgs {
 // Monotone map float -> uint32 (larger float, larger key); -0 and +0 share a key.
 __device__ __forceinline__ uint32_t order_key(uint32_t u)
 {
-    if (u == 0x80000000u) u = 0u;
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    u = __float_as_uint(__uint_as_float(u) + 0.f); // (-0 becomes +0)
+    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
 }
 
 // B: entries the head keeps in all; kept: how many of them are the kept window's (the last `kept` entries);
@@ -459,13 +459,15 @@ __global__ __launch_bounds__(SEL_THREADS) void select_write_kernel(SelArgs A)
 //   * the thread that sums a bin also clears it, so a digit costs three barriers
 //   * ties are ranked only when the threshold's ties do not all fit
 //
-// What bounds it: at short rows the six digits' barriers (about 0.9 us each, and 3 us for a launch that only loads and
-// stores); at long ones instruction issue of one CU (about 5 vector instructions and an LDS atomic per key and digit), so
-// the time grows with the row while the sliced kernels cost eight launches whatever its length.  Eight heads, us, sliced / one
-// workgroup: n 512 34.8 / 8.9, 3072 36.3 / 9.4, 8192 36.6 / 12.7, 16384 37.1 / 19.4, 24576 36 / 25.2, 32768 36 / 38 (before the
-// waves' totals were summed by row shifts, which took 1.5 - 2 us off): rows of up to 24576 keys are taken whole.  (Merging
-// runs of equal digits into one atomic, as the sliced kernels do, costs more instructions than it saves atomics here: 8192
-// keys 18.5 instead of 17.3 us.)
+//   * a key that does not compete (outside the row, chosen already) is 0, so that no mask has to be asked for it
+//
+// What bounds it: at short rows the six digits' barriers (about 0.7 us each, and 3 us for a launch that only loads and
+// stores); at long ones the passes over the keys on one CU (a few vector instructions and an LDS atomic per key and digit, 2.3
+// us a digit at 20011 keys), so the time grows with the row while the sliced kernels cost eight launches whatever its
+// length.  Eight heads in a graph, us, sliced / one workgroup, with a mask of the competing keys / like this: n 1024 36 / 11.2 /
+// 10.6, 3072 36 / 11.5 / 10.9, 8192 37 / 14.8 / 13.7, 16384 37 / 21.6 / 19.3, 20011 37 / 26.4 / 23.4, 24576 38 / 27.4 / 24.6: rows of up
+// to 24576 keys are taken whole (32 keys a thread spill).  (Merging runs of equal digits into one atomic, as the sliced
+// kernels do, costs more instructions than it saves atomics here: 8192 keys 18.5 instead of 17.3 us when that was tried.)
 constexpr int SEL_ROW_MAX = 24576;
 constexpr int ROW_THREADS = 1024;
 constexpr int ROW_WAVES = ROW_THREADS / 64;
@@ -513,23 +515,28 @@ __device__ __forceinline__ void row_scan(RowShared &sh, const uint32_t (&x)[NP],
     }
 }
 
-// The threshold of the `want` largest of the keys that `live` marks: its key and how many of its ties still fit, and
-// whether that is all of them.  The histogram is clear on entry and on exit.
+// The threshold of the `want` largest keys: its key, how many of its ties still fit, and whether that is all of them.  Keys
+// of 0 do not compete (no float but a NaN has that image); 0 as the threshold says that there are fewer than `want` others.
+// The histogram is clear on entry and on exit.
 template <int KPT>
-__device__ __forceinline__ void row_threshold(RowShared &sh, const uint32_t (&key)[KPT], uint32_t live, uint32_t want,
-                                              uint32_t &tau, uint32_t &fit, bool &all_fit)
+__device__ __forceinline__ void row_threshold(RowShared &sh, const uint32_t (&key)[KPT], uint32_t want, uint32_t &tau,
+                                              uint32_t &fit, bool &all_fit)
 {
     constexpr int PER = SEL_BINS / ROW_THREADS, COPIES = row_copies(KPT);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t prefix = 0u, pmask = 0u, rest = want;
+    uint32_t *mine = sh.hist + (lane & (COPIES - 1));
+    uint32_t prefix = 0u, rest = want; // the threshold's digits so far
+    uint32_t one = 1u;
+    asm volatile("" : "+v"(one)); // (a register, not an instruction per key)
 #pragma unroll
     for (int pass = 0; pass < 3; ++pass) {
-        const int shift = pass == 0 ? DSHIFT0 : pass == 1 ? DSHIFT1 : 0;
-        const uint32_t mask = pass == 2 ? DMASK2 : DMASK0;
+        const int width = pass == 2 ? DSHIFT1 : DSHIFT0 - DSHIFT1, shift = pass == 0 ? DSHIFT0 : pass == 1 ? DSHIFT1 : 0;
 #pragma unroll
         for (int j = 0; j < KPT; ++j) {
-            const bool on = ((live >> j) & 1u) && (key[j] & pmask) == prefix;
-            if (on) atomicAdd(&sh.hist[((key[j] >> shift) & mask) * COPIES + (lane & (COPIES - 1))], 1u);
+            const bool on = pass == 0 ? key[j] != 0u : (key[j] >> (shift + width)) == prefix;
+            // (the last digit is asked of few keys: most waves have none at a given j)
+            if (pass == 2 && __builtin_amdgcn_ballot_w64(on) == 0ull) continue;
+            if (on) atomicAdd(&mine[(pass == 0 ? key[j] >> shift : (key[j] >> shift) & ((1u << width) - 1u)) * COPIES], one);
         }
         __syncthreads();
         // bins in descending order, PER per thread
@@ -563,8 +570,7 @@ __device__ __forceinline__ void row_threshold(RowShared &sh, const uint32_t (&ke
             run += h[j];
         }
         __syncthreads();
-        prefix |= sh.digit << shift;
-        pmask |= mask << shift;
+        prefix = pass == 0 ? sh.digit : (prefix << width) | sh.digit;
         rest -= sh.above;
         all_fit = sh.inside == rest;
     }
@@ -611,26 +617,18 @@ __device__ __forceinline__ void row_load(const uint32_t *row, int n, RowPlace at
     }
 }
 
-// The bits among `live` of the keys above the threshold and of the first `fit` of its ties in token order.
+// Where not all of the threshold's ties fit: those behind the first `fit` in token order drop below it, so that the keys at
+// or above it are the chosen ones.
 template <int KPT>
-__device__ __forceinline__ uint32_t row_above(RowShared &sh, const uint32_t (&key)[KPT], uint32_t live, uint32_t tau,
-                                              uint32_t fit, bool all_fit)
+__device__ __forceinline__ void row_fit_ties(RowShared &sh, uint32_t (&key)[KPT], uint32_t tau, uint32_t fit, bool all_fit)
 {
     constexpr int QUADS = KPT / 4, NP = (QUADS + 1) / 2;
-    uint32_t gt = 0u, ties = 0u;
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-        gt |= (key[j] > tau ? 1u : 0u) << j;
-        ties |= (key[j] == tau ? 1u : 0u) << j;
-    }
-    gt &= live;
-    ties &= live;
-    if (all_fit) return gt | ties; // uniform over the workgroup
+    if (all_fit || tau == 0u) return; // uniform over the workgroup
     uint32_t cnt[NP], excl[NP], total[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) cnt[p] = 0u;
 #pragma unroll
-    for (int q = 0; q < QUADS; ++q) cnt[q >> 1] += (uint32_t)__popc((ties >> (4 * q)) & 15u) << (16 * (q & 1));
+    for (int j = 0; j < KPT; ++j) cnt[j >> 3] += (key[j] == tau ? 1u : 0u) << (16 * ((j >> 2) & 1));
     row_scan<NP>(sh, cnt, excl, total);
     uint32_t before = 0u;
 #pragma unroll
@@ -638,13 +636,28 @@ __device__ __forceinline__ uint32_t row_above(RowShared &sh, const uint32_t (&ke
         uint32_t rank = before + ((excl[q >> 1] >> (16 * (q & 1))) & 0xFFFFu);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            if ((ties >> (4 * q + e)) & 1u) {
-                gt |= (rank < fit ? 1u : 0u) << (4 * q + e);
+            if (key[4 * q + e] == tau) {
+                if (rank >= fit) key[4 * q + e] = tau - 1u;
                 ++rank;
             }
         before += (total[q >> 1] >> (16 * (q & 1))) & 0xFFFFu;
     }
-    return gt;
+}
+
+// The row's keys from its words; 0 for the positions of the quads that lie outside tokens 0 .. n_rank - 1.
+template <int KPT>
+__device__ __forceinline__ void row_keys(uint32_t (&key)[KPT], int shift, int n_rank)
+{
+#pragma unroll
+    for (int q = 0; q < KPT / 4; ++q) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) key[4 * q + e] = order_key(key[4 * q + e]);
+        if ((q == 0 && shift) || (q + 1) * 4 * ROW_THREADS - shift > n_rank) { // uniform: not all of these are inside
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if ((uint32_t)(row_token(4 * q + e) - shift) >= (uint32_t)n_rank) key[4 * q + e] = 0u;
+        }
+    }
 }
 
 template <int KPT>
@@ -665,56 +678,53 @@ __global__ __launch_bounds__(ROW_THREADS) void select_row_kernel(SelArgs A)
     head_budget(A, head, B, b1, b2, kept);
     for (int b = threadIdx.x * 4; b < SEL_BINS * 4; b += ROW_THREADS * 4) *reinterpret_cast<uint4 *>(&sh.hist[b]) = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
-    // bit j: the token competes (it is inside the row and not of the kept window)
-    uint32_t rank_ok = 0u;
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-        key1[j] = order_key(key1[j]);
-        rank_ok |= (token(j) >= 0 && token(j) < A.n_rank ? 1u : 0u) << j;
-    }
-    uint32_t taken = 0u; // stage 1 and the kept window
+    row_keys<KPT>(key1, at.shift, A.n_rank);
+    // stage 1: chosen are the keys at or above tau1; nothing is with SEL_TAKEN, but for the kept window, which gets that key
+    uint32_t tau1 = SEL_TAKEN, tau2 = SEL_TAKEN, fit;
+    bool all_fit;
     if (b1 > 0) { // uniform over the workgroup, as everything derived from the budget
-        uint32_t live = rank_ok, tau, fit;
-        bool all_fit;
+        row_threshold<KPT>(sh, key1, (uint32_t)b1, tau1, fit, all_fit);
+        row_fit_ties<KPT>(sh, key1, tau1, fit, all_fit);
+        tau1 = max(tau1, 1u); // (fewer competitors than b1: all of them)
+    }
+    if (kept > 0) {
 #pragma unroll
         for (int j = 0; j < KPT; ++j)
-            if (key1[j] == SEL_TAKEN) live &= ~(1u << j);
-        row_threshold<KPT>(sh, key1, live, (uint32_t)b1, tau, fit, all_fit);
-        taken = row_above<KPT>(sh, key1, rank_ok, tau, fit, all_fit);
+            if (token(j) >= A.n - kept && token(j) < A.n) key1[j] = SEL_TAKEN;
     }
     if (LATE) row_load<KPT>(crit, A.n, at, key2);
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-        key2[j] = order_key(key2[j]);
-        if (token(j) >= A.n - kept && token(j) < A.n) taken |= 1u << j;
-        if ((taken >> j) & 1u) key2[j] = SEL_TAKEN;
-    }
     // the stage-2 keys with stage-1 entries marked are what the diagnostics read back
     uint32_t *k2 = A.keys2 + (size_t)head * A.n;
-    uint32_t marked = 0u;
 #pragma unroll
     for (int q = 0; q < QUADS; ++q) {
+        uint32_t marked[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int j = 4 * q + e;
+            const uint32_t k = order_key(key2[j]);
+            const bool taken = key1[j] >= tau1;
+            marked[e] = taken ? SEL_TAKEN : k;
+            key2[j] = taken || key1[j] == 0u ? 0u : k; // (0 in key1: outside, or not of those that compete)
+        }
         const int i0 = token(4 * q); // keys2 starts on a 16-byte boundary as the scores do: its rows are shifted alike
         if (i0 >= 0 && i0 + 3 < A.n) {
-            *reinterpret_cast<uint4 *>(k2 + i0) = make_uint4(key2[4 * q], key2[4 * q + 1], key2[4 * q + 2], key2[4 * q + 3]);
+            *reinterpret_cast<uint4 *>(k2 + i0) = make_uint4(marked[0], marked[1], marked[2], marked[3]);
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (i0 + e >= 0 && i0 + e < A.n) k2[i0 + e] = key2[4 * q + e];
+                if (i0 + e >= 0 && i0 + e < A.n) k2[i0 + e] = marked[e];
         }
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            marked |= (key2[4 * q + e] == SEL_TAKEN && i0 + e >= 0 && i0 + e < A.n ? 1u : 0u) << (4 * q + e);
     }
-    uint32_t sel = marked;
     if (b2 > 0) {
-        uint32_t tau, fit;
-        bool all_fit;
-        row_threshold<KPT>(sh, key2, rank_ok & ~marked, (uint32_t)b2, tau, fit, all_fit);
-        sel |= row_above<KPT>(sh, key2, rank_ok, tau, fit, all_fit);
+        row_threshold<KPT>(sh, key2, (uint32_t)b2, tau2, fit, all_fit);
+        row_fit_ties<KPT>(sh, key2, tau2, fit, all_fit);
+        tau2 = max(tau2, 1u);
     }
     // ordered write
-    uint32_t cnt[NP], excl[NP], total[NP];
+    asm volatile("" : "+v"(tau1)); // (compared anew: kept from above, the comparisons would take more scalar registers than there are)
+    uint32_t cnt[NP], excl[NP], total[NP], sel = 0u;
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) sel |= (key1[j] >= tau1 || key2[j] >= tau2 ? 1u : 0u) << j;
 #pragma unroll
     for (int p = 0; p < NP; ++p) cnt[p] = 0u;
 #pragma unroll
@@ -824,18 +834,13 @@ __global__ __launch_bounds__(ROW_THREADS) void allocate_row_kernel(SelArgs A, Al
     row_load<KPT>(A.attn + (size_t)row * A.n, A.n, at, key);
     for (int b = threadIdx.x * 4; b < SEL_BINS * 4; b += ROW_THREADS * 4) *reinterpret_cast<uint4 *>(&sh.hist[b]) = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
-    uint32_t inside = 0u, live = 0u;
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-        key[j] = order_key(key[j]);
-        const int i = row_token(j) - at.shift;
-        inside |= (i >= 0 && i < A.n ? 1u : 0u) << j;
-        live |= (key[j] != SEL_TAKEN ? 1u : 0u) << j;
-    }
-    uint32_t tau, fit;
+    row_keys<KPT>(key, at.shift, A.n);
+    uint32_t tau, fit, sel = 0u;
     bool all_fit;
-    row_threshold<KPT>(sh, key, inside & live, (uint32_t)A.max_budget, tau, fit, all_fit);
-    const uint32_t sel = row_above<KPT>(sh, key, inside, tau, fit, all_fit);
+    row_threshold<KPT>(sh, key, (uint32_t)A.max_budget, tau, fit, all_fit);
+    row_fit_ties<KPT>(sh, key, tau, fit, all_fit);
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) sel |= (key[j] >= max(tau, 1u) ? 1u : 0u) << j;
     // the histogram is clear again: its words count the heads' entries (the host takes this kernel for Hkv <= 4 * SEL_BINS)
     __syncthreads();
 #pragma unroll

@@ -568,3 +568,16 @@ def test_short_fp32_contexts_against_float64(P, dh, H, Hkv, W, b, wo_out_in, ns)
             assert np.linalg.norm(attn - ref) <= 2e-6 * np.linalg.norm(ref), (n, causal)
             p = torch.einsum("bgnd,grdc->bgrnc", v.double(), w.double().view(Hkv, G, dh, 96)).reshape(b, H, n, 96).abs().sum(-1)
             assert np.abs(vnorm / p.cpu().numpy() - 1).max() <= 2e-6, (n, causal)
+
+
+@pytest.mark.parametrize("n", [7, 4093, 9001, 20011])
+def test_select_of_rows_with_signed_zeros_and_infinities(P, n):
+    """Keys at the ends of the order: -0 and +0 are one key, -inf competes (it is not a position outside the row), +inf is first."""
+    from test_gpu_parity import assert_select_exact
+    r = np.random.Generator(np.random.PCG64(n))
+    pool = np.array([-np.inf, -1.0, -1e-45, -0.0, 0.0, 1e-45, 2.0, np.inf], np.float32)
+    attn, crit = pool[r.integers(0, 8, (1, 3, n))], pool[r.integers(0, 8, (1, 3, n))]
+    attn[0, 2], crit[0, 2] = -np.inf, pool[r.integers(0, 3, n)]
+    for B in sorted({1, n // 3, n // 2 + 1, n - 1, n}):
+        for alpha in (0.0, 0.5, 1.0):
+            assert_select_exact(P, attn, crit, B, alpha, max_budget=n)
