@@ -142,6 +142,10 @@ def _ptr(t) -> Optional[int]:
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
+        if torch.cuda.is_initialized():
+            # what torch.cuda.current_stream() wraps in an object: 0.3 us instead of 2.9, three times in a pass whose kernels
+            # take 27 us
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
         stream = torch.cuda.current_stream()
     return stream.cuda_stream or None
 

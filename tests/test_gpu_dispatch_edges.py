@@ -581,3 +581,13 @@ def test_select_of_rows_with_signed_zeros_and_infinities(P, n):
     for B in sorted({1, n // 3, n // 2 + 1, n - 1, n}):
         for alpha in (0.0, 0.5, 1.0):
             assert_select_exact(P, attn, crit, B, alpha, max_budget=n)
+
+
+def test_calls_go_to_the_current_stream(P):
+    import torch
+    from paper_2502_03805_amd import binding as B
+    assert B._stream(None) == (torch.cuda.current_stream().cuda_stream or None)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert B._stream(None) == side.cuda_stream != 0
+    assert B._stream(side) == side.cuda_stream and B._stream(None) == (torch.cuda.current_stream().cuda_stream or None)
