@@ -186,6 +186,8 @@ __global__ __launch_bounds__(256) void gram_finish_kernel(const float *__restric
 // (measured 6 % slower with five), so such groups take one head per workgroup.
 constexpr int GR_RB = 4;
 constexpr int GR_BLOCK_ROWS = GR_RB * 16;
+constexpr int GR_AHEAD = 3;           // vproj_l2_long_kernel: k-chunks of V held twice
+constexpr int GR_LONG_BLOCKS = 4;     // blocks per wave from which it is taken
 
 template <int HEADS>
 __global__ __launch_bounds__(HEADS * 256, HEADS == 1 ? 2 : 1) void vproj_l2_resident_kernel(const bf16_t *__restrict__ v,
@@ -307,7 +309,6 @@ __global__ __launch_bounds__(HEADS * 256, HEADS == 1 ? 2 : 1) void vproj_l2_resi
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int rb = 0; rb < GR_RB; ++rb) {
-                typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
                 const u32x4 w = __builtin_bit_cast(u32x4, sp < 2 ? va[CUR][rb][sp] : vb[rb][sp - 2]);
                 const uint32_t w0 = w[2 * half], w1 = w[2 * half + 1];
                 nsq[rb] = fmaf(acc[rb][0], __uint_as_float(w0 << 16), nsq[rb]);
@@ -331,6 +332,188 @@ __global__ __launch_bounds__(HEADS * 256, HEADS == 1 ? 2 : 1) void vproj_l2_resi
     for (int blk = wave; blk < nblk; blk += 2 * GR_WAVES) {
         block_step(std::integral_constant<int, 0>{}, blk);
         if (blk + GR_WAVES < nblk) block_step(std::integral_constant<int, 1>{}, blk + GR_WAVES);
+    }
+}
+
+// The same for two heads per workgroup and long ranges (GR_LONG_BLOCKS blocks per wave and more).  In the kernel above a
+// wave runs matrix and vector work in turns, waits for half of a block's V rows at its start, and the older of a SIMD's two
+// waves, which is served first, ends early.  Here
+//   * a slab's epilogue runs under the next slab's MFMAs (two accumulator sets), and each Gram fragment's registers are
+//     refilled as soon as its MFMAs are issued
+//   * the longest slabs come first, both heads inside: a block's last k-chunk of V is needed by the first slabs only, so its
+//     registers take the next block's half a block ahead, the other three are held twice
+//   * the blocks of a range go to the workgroup's waves as they ask
+// Score call at 32 heads over 8, us, the kernel above / equal shares / this: 131072 tokens 267 / 259 / 257, 4 x 20011 182 / 177 /
+// 174; MFMA busy 60 -> 72 % of a CU's cycles.  The code of a block is a straight line over both heads (10 KiB, twice), which a
+// wave with one or two blocks only fetches: 8192 tokens 35.5 / 36.2, 30011 (3.75 blocks per wave) 78.0 / 77.5; one head per
+// workgroup (five heads per group, 131072 tokens): 464 / 466.
+__global__ __launch_bounds__(512, 1) void vproj_l2_long_kernel(const bf16_t *__restrict__ v, const bf16_t *__restrict__ gram,
+                                                               float *__restrict__ vnorm, int H, int G, int n, int64_t vs0,
+                                                               int64_t vs1, int64_t vs2, int pairs, int ranges, int rows_per_range)
+{
+    constexpr int GR_HEADS = 2, GR_WAVES = 8;
+    __shared__ __attribute__((aligned(1024))) char lds[GR_HEADS * 2 * GL_G_BYTES]; // per head: G_hi | G_lo, XOR-swizzled
+    __shared__ int next_block;
+    const int Hkv = H / G, hgroups = G / GR_HEADS; // (G is even)
+    // (work items, the Gram matrices' place in LDS and the choice of an MFMA's 16 rows of G as in the kernel above)
+    const int items = pairs * ranges, per_xcd = (items + 7) >> 3;
+    const int hl = ((int)blockIdx.x >> 3) % hgroups * GR_HEADS; // first head of this workgroup inside its kv group
+    const int k_in_xcd = ((int)blockIdx.x >> 3) / hgroups, item = ((int)blockIdx.x & 7) * per_xcd + k_in_xcd;
+    if (k_in_xcd >= per_xcd || item >= items) return; // uniform over the workgroup
+    const int range = item % ranges, pair = item / ranges;
+    const int bi = pair / Hkv, g = pair % Hkv, h = g * G + hl;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, kc = lane >> 4;
+    const int row_begin = range * rows_per_range;            // a multiple of GR_BLOCK_ROWS
+    const int row_end = min(n, row_begin + rows_per_range);
+    if (row_begin >= row_end) return;                        // uniform over the workgroup
+    const int nblk = (row_end - row_begin + GR_BLOCK_ROWS - 1) / GR_BLOCK_ROWS;
+    const bf16_t *vbase = v + bi * vs0 + g * vs1;
+
+    for (int hh = 0; hh < GR_HEADS; ++hh) {
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)(gram + (size_t)(h + hh) * 2 * GL_DH * GL_DH), 0, 2 * GL_G_BYTES, 0x00020000);
+#pragma unroll
+        for (int j = 0; j < 64 / GR_WAVES; ++j) {
+            const int kib = j * GR_WAVES + wave;
+            const int urow = (kib * 4 + (lane >> 4)) & (GL_DH - 1);
+            const int f = ((urow >> 3) & 3) * 4 + (urow & 3);
+            const uint32_t voff = (uint32_t)(kib * 1024 + (lane >> 4) * 256 + (((lane & 15) ^ f) * 16));
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, LDS_PTR(lds + hh * 2 * GL_G_BYTES + kib * 1024), 16, voff, 0, 0, 0);
+        }
+    }
+    const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)vbase, 0, (int)(((int64_t)(n - 1) * vs2 + GL_DH) * 2), 0x00020000);
+    const uint32_t row_bytes = (uint32_t)(vs2 * 2);
+    // 64 bytes of each row of a block (k-chunk s) as B fragments
+    auto load_v = [&](int blk, int s, bf16x8 (&dst)[GR_RB]) {
+        const int row0 = row_begin + blk * GR_BLOCK_ROWS;
+#pragma unroll
+        for (int rb = 0; rb < GR_RB; ++rb) {
+            const uint32_t voff = (uint32_t)min(row0 + rb * 16 + l16, n - 1) * row_bytes + (uint32_t)(kc * 16);
+            dst[rb] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(vrsrc, voff + s * 64, 0, 0));
+        }
+    };
+    bf16x8 va[2][GR_AHEAD][GR_RB], vb[GR_RB];
+    if (wave < nblk) {
+#pragma unroll
+        for (int s = 0; s < GR_AHEAD; ++s) load_v(wave, s, va[0][s]);
+        load_v(wave, GR_AHEAD, vb);
+    }
+    if (threadIdx.x == 0) next_block = 2 * GR_WAVES;
+    __syncthreads(); // the Gram matrices have landed (every wave waits for its own loads first)
+    if (wave >= nblk) return; // after the only barrier
+
+    const int a_row = 8 * (l16 >> 2) + (l16 & 3);          // + 32 * sp + 4 * half
+    const int a_f = 4 * (l16 >> 2) + (l16 & 3);            // f(u) of that row: bits 3-4 and 0-1 of u
+    float *out = vnorm + ((size_t)bi * H + h) * (size_t)n;
+
+    // A unit of work is 16 rows of one head's G (a slab): 2 * (sp + 1) fragments of four MFMAs each.  The units of a block run
+    // from the longest slabs to the shortest, the heads inside, so that a V chunk's last use comes early.
+    constexpr int UNITS = 8 * GR_HEADS;
+    auto unit_sp = [](int u) { return 3 - u / (2 * GR_HEADS); };
+    auto unit_half = [](int u) { return u / GR_HEADS % 2; };
+    auto unit_head = [](int u) { return u % GR_HEADS; };
+    bf16x8 gf[4][2]; // fragments of k-chunk s: G_lo, G_hi
+    int ga[4]; // LDS offset of this lane's row at chunk s, slab 0 of the first head
+#pragma unroll
+    for (int s = 0; s < 4; ++s) ga[s] = a_row * 256 + ((4 * s + kc) ^ a_f) * 16;
+    auto read_g = [&](int u, int s, int p) {
+        gf[s][p] = *reinterpret_cast<const bf16x8 *>(lds + ga[s] + unit_head(u) * 2 * GL_G_BYTES + (1 - p) * GL_G_BYTES +
+                                                      (32 * unit_sp(u) + 4 * unit_half(u)) * 256);
+    };
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) read_g(0, s, p);
+
+    // One block of rows from register set CUR; the other set receives the wave's next block meanwhile.
+    auto block_step = [&](auto cur_c, int blk, int nxt) __attribute__((always_inline)) {
+        constexpr int CUR = decltype(cur_c)::value;
+        // (opaque, or the compiler lifts the reads of what never changes out of the loop and spills them)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(ga[s]));
+        auto chunk = [&](int s, int rb) -> bf16x8 & { return s < GR_AHEAD ? va[CUR][s][rb] : vb[rb]; };
+#pragma unroll
+        for (int s = 0; s < GR_AHEAD; ++s) load_v(nxt, s, va[CUR ^ 1][s]); // unconditional (clamped rows)
+        float nsq[GR_HEADS][GR_RB];
+#pragma unroll
+        for (int hh = 0; hh < GR_HEADS; ++hh)
+#pragma unroll
+            for (int rb = 0; rb < GR_RB; ++rb) nsq[hh][rb] = 0.f;
+        f32x4 acc[2][GR_RB];
+        // one of the 16 products of a finished unit's epilogue: N^2 += Y[u] v[u]
+        auto epilogue = [&](int u, int item) __attribute__((always_inline)) {
+            const int rb = item % GR_RB, j = item / GR_RB;
+            const uint32_t w = __builtin_bit_cast(u32x4, chunk(unit_sp(u), rb))[2 * unit_half(u) + (j >> 1)];
+            float &to = nsq[unit_head(u)][rb];
+            to = fmaf(acc[u & 1][rb][j], __uint_as_float(j & 1 ? w & 0xFFFF0000u : w << 16), to);
+        };
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u) {
+            const int sp = unit_sp(u), next = (u + 1) % UNITS, sp_next = unit_sp(next), groups = 2 * (sp + 1);
+#pragma unroll
+            for (int s = 0; s <= sp; ++s)
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    const int g = 2 * s + p;
+#pragma unroll
+                    for (int rb = 0; rb < GR_RB; ++rb)
+                        acc[u & 1][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf[s][p], chunk(s, rb), g == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[u & 1][rb], 0, 0, 0);
+                    // the fragment's slot takes the next unit's; the block's last unit also fetches those that it has no use for
+                    if (s <= sp_next) read_g(next, s, p);
+                    if (sp < sp_next) {
+#pragma unroll
+                        for (int x = 1 + s; x < 4; x += sp + 1) read_g(next, x, p);
+                    }
+                    // the unit before: its epilogue under these MFMAs
+                    if (u > 0) {
+#pragma unroll
+                        for (int i = g * 4 * GR_RB / groups; i < (g + 1) * 4 * GR_RB / groups; ++i) epilogue(u - 1, i);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            if (u == 2 * GR_HEADS) load_v(nxt, GR_AHEAD, vb); // (the slabs that meet chunk 3 are through)
+        }
+#pragma unroll
+        for (int i = 0; i < 4 * GR_RB; ++i) epilogue(UNITS - 1, i);
+        // (pinned here: the epilogues of a row block would otherwise sink behind the branch around the store before its own,
+        // and their accumulators would have to be kept until then)
+#pragma unroll
+        for (int hh = 0; hh < GR_HEADS; ++hh)
+#pragma unroll
+            for (int rb = 0; rb < GR_RB; ++rb) asm volatile("" : "+v"(nsq[hh][rb]));
+        const int row0 = row_begin + blk * GR_BLOCK_ROWS;
+#pragma unroll
+        for (int hh = 0; hh < GR_HEADS; ++hh)
+#pragma unroll
+            for (int rb = 0; rb < GR_RB; ++rb) {
+                float x = nsq[hh][rb];
+                x += __shfl_xor(x, 16);
+                x += __shfl_xor(x, 32);
+                const int row = row0 + rb * 16 + l16;
+                if (kc == 0 && row < row_end) out[(size_t)hh * n + row] = sqrtf(fmaxf(x, 0.f));
+            }
+    };
+    // A wave's first two blocks are its own, the others go to whoever asks next: of the two waves of a SIMD the older one is
+    // served first, and with equal shares the other would run the last sixth of its blocks alone.
+    auto take = [&]() __attribute__((always_inline)) {
+        int t = 0;
+        if (lane == 0) t = atomicAdd(&next_block, 1);
+        return t;
+    };
+    int blk = wave, nxt = wave + GR_WAVES;
+    while (blk < nblk) {
+        int t = take();
+        block_step(std::integral_constant<int, 0>{}, blk, nxt);
+        blk = nxt;
+        nxt = __builtin_amdgcn_readfirstlane(t);
+        if (blk >= nblk) break;
+        t = take();
+        block_step(std::integral_constant<int, 1>{}, blk, nxt);
+        blk = nxt;
+        nxt = __builtin_amdgcn_readfirstlane(t);
     }
 }
 
@@ -373,7 +556,10 @@ hipError_t launch_vproj_l2_mfma(const Dims &d, const void *v, const void *gram, 
     int rows_per_range = (d.n + ranges - 1) / ranges;
     rows_per_range = (rows_per_range + GR_BLOCK_ROWS - 1) / GR_BLOCK_ROWS * GR_BLOCK_ROWS;
     const dim3 grid((unsigned)(8 * ((pairs * ranges + 7) / 8) * (d.G / heads))), block(waves * 64);
-    if (heads == 2)
+    if (heads == 2 && rows_per_range >= GR_LONG_BLOCKS * waves * GR_BLOCK_ROWS)
+        hipLaunchKernelGGL(vproj_l2_long_kernel, grid, block, 0, s, (const bf16_t *)v, (const bf16_t *)gram, vnorm, d.H, d.G,
+                           d.n, d.vs[0], d.vs[1], d.vs[2], pairs, ranges, rows_per_range);
+    else if (heads == 2)
         hipLaunchKernelGGL(vproj_l2_resident_kernel<2>, grid, block, 0, s, (const bf16_t *)v, (const bf16_t *)gram, vnorm,
                            d.H, d.G, d.n, d.vs[0], d.vs[1], d.vs[2], pairs, ranges, rows_per_range);
     else

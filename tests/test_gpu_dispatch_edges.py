@@ -591,3 +591,21 @@ def test_calls_go_to_the_current_stream(P):
     with torch.cuda.stream(side):
         assert B._stream(None) == side.cuda_stream != 0
     assert B._stream(side) == side.cuda_stream and B._stream(None) == (torch.cuda.current_stream().cuda_stream or None)
+
+
+@pytest.mark.parametrize("n", [1984, 1985, 2111, 4097])
+def test_l2_magnitudes_of_long_ranges(P, n):
+    """One range per head pair: 31 blocks of rows per workgroup (the kernel for short ranges) and 32 and more, which its eight
+    waves take as they ask; ragged last blocks.  2e-5 as for the other lengths, and the same bits on every call."""
+    import torch
+    b, H, Hkv = 8, 64, 32
+    g = torch.Generator(device="cuda").manual_seed(n)
+    cfg = CONFIGS["llama32k"].with_(n_q_heads=H, n_kv_heads=Hkv, d_model=512, n_ctx=n, window=8, batch=b)
+    q, k, v = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((b, H, 8, 128), (b, Hkv, n, 128), (b, Hkv, n, 128)))
+    w = (0.02 * torch.randn((H * 128, 512), generator=g, device="cuda")).to(torch.bfloat16)
+    got = torch.from_numpy(score(P, cfg_desc(P, cfg, norm=2), q, k, v, w)[2]).cuda()
+    for bi, h in ((0, 0), (0, 1), (3, 31), (7, 62), (7, 63)):
+        ref = (v[bi, h * Hkv // H].double() @ w[h * 128:(h + 1) * 128].double()).square().sum(-1).sqrt()
+        assert (got[bi, h].double() / ref - 1).abs().max() <= 2e-5, (bi, h)
+    for _ in range(3):
+        assert torch.equal(torch.from_numpy(score(P, cfg_desc(P, cfg, norm=2), q, k, v, w)[2]).cuda(), got)
