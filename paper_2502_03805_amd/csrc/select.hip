@@ -460,12 +460,14 @@ __global__ __launch_bounds__(SEL_THREADS) void select_write_kernel(SelArgs A)
 //   * ties are ranked only when the threshold's ties do not all fit
 //
 //   * a key that does not compete (outside the row, chosen already) is 0, so that no mask has to be asked for it
+//   * the digits end when all keys that share them fit: scores without ties are mostly told apart by two
 //
 // What bounds it: at short rows the six digits' barriers (about 0.7 us each, and 3 us for a launch that only loads and
 // stores); at long ones the passes over the keys on one CU (a few vector instructions and an LDS atomic per key and digit, 2.3
 // us a digit at 20011 keys), so the time grows with the row while the sliced kernels cost eight launches whatever its
-// length.  Eight heads in a graph, us, sliced / one workgroup, with a mask of the competing keys / like this: n 1024 36 / 11.2 /
-// 10.6, 3072 36 / 11.5 / 10.9, 8192 37 / 14.8 / 13.7, 16384 37 / 21.6 / 19.3, 20011 37 / 26.4 / 23.4, 24576 38 / 27.4 / 24.6: rows of up
+// length.  Eight heads in a graph, us, sliced / one workgroup, with a mask of the competing keys and all six digits / like
+// this: n 1024 36 / 11.2 / 9.7, 3072 36 / 11.4 / 10.1, 8192 37 / 14.8 / 12.8, 16384 37 / 21.6 / 17.9, 20011 37 / 26.5 / 21.6 (23.5 with
+// all digits), 24576 38 / 27.5 / 22.9: rows of up
 // to 24576 keys are taken whole (32 keys a thread spill).  (Merging runs of equal digits into one atomic, as the sliced
 // kernels do, costs more instructions than it saves atomics here: 8192 keys 18.5 instead of 17.3 us when that was tried.)
 constexpr int SEL_ROW_MAX = 24576;
@@ -515,8 +517,8 @@ __device__ __forceinline__ void row_scan(RowShared &sh, const uint32_t (&x)[NP],
     }
 }
 
-// The threshold of the `want` largest keys: its key, how many of its ties still fit, and whether that is all of them.  Keys
-// of 0 do not compete (no float but a NaN has that image); 0 as the threshold says that there are fewer than `want` others.
+// The threshold of the `want` largest keys: its key, how many of its ties still fit, and whether that is all of them (then it
+// is a bound between the chosen and the others, and its last digits may be left at 0).  Keys of 0 do not compete (no float but a NaN has that image); 0 as the threshold says that there are fewer than `want` others.
 // The histogram is clear on entry and on exit.
 template <int KPT>
 __device__ __forceinline__ void row_threshold(RowShared &sh, const uint32_t (&key)[KPT], uint32_t want, uint32_t &tau,
@@ -573,8 +575,9 @@ __device__ __forceinline__ void row_threshold(RowShared &sh, const uint32_t (&ke
         prefix = pass == 0 ? sh.digit : (prefix << width) | sh.digit;
         rest -= sh.above;
         all_fit = sh.inside == rest;
+        tau = prefix << shift;
+        if (all_fit) break; // uniform: every key with these digits is chosen, whatever its others
     }
-    tau = prefix;
     fit = rest;
 }
 
