@@ -55,6 +55,7 @@ struct SelArgs {
     int32_t *count;
     double alpha;
     int n, max_budget, n_slices;
+    int share;  // allocation: rows of one batch item share a histogram and a threshold (1: every row has its own)
     int n_rank; // entries 0 .. n_rank-1 compete in the two stages (n minus the kept window)
 };
 
@@ -197,28 +198,32 @@ __global__ __launch_bounds__(256) void select_zero_kernel(uint32_t *p, size_t wo
 
 // Histogram of one digit over a slice.  STAGE 0 reads attn floats, STAGE 1 the stage-2 key array.
 // PASS 0 histograms digit 0 of every entry; PASS 1 / 2 first decode the previous digit(s) of the threshold.
-template <int STAGE, int PASS>
+// COUNT: slices keep their counts above the threshold (stage 2, and the allocation, whose A.share rows make up one).
+template <int STAGE, int PASS, bool COUNT = STAGE == 1>
 __global__ __launch_bounds__(SEL_THREADS) void select_hist_kernel(SelArgs A)
 {
     __shared__ SelShared sh;
     const int slice = blockIdx.x, head = blockIdx.y;
     int B, b1, b2, kept;
     head_budget(A, head, B, b1, b2, kept);
-    const uint32_t want = STAGE == 0 ? (uint32_t)b1 : (uint32_t)b2;
+    const bool alloc = STAGE == 0 && COUNT;
+    const uint32_t want = alloc ? (uint32_t)A.max_budget : STAGE == 0 ? (uint32_t)b1 : (uint32_t)b2;
     if (want == 0) return;
-    uint32_t *hist = A.hist + ((size_t)head * 2 + STAGE) * 3 * SEL_BINS;
-    uint32_t *st = A.state + ((size_t)head * 2 + STAGE) * ST_WORDS;
+    const int owner = alloc ? head / A.share : head; // whose threshold this row's keys are compared with
+    const bool first = slice == 0 && threadIdx.x == 0 && (!alloc || head % A.share == 0);
+    uint32_t *hist = A.hist + ((size_t)owner * 2 + STAGE) * 3 * SEL_BINS;
+    uint32_t *st = A.state + ((size_t)owner * 2 + STAGE) * ST_WORDS;
     uint32_t prefix = 0u, pmask = 0u;
     if (PASS == 1) {
         uint32_t d0, a0;
         find_digit(sh, hist, 2048, want, d0, a0);
-        if (slice == 0 && threadIdx.x == 0) { st[ST_D0] = d0; st[ST_A0] = a0; }
+        if (first) { st[ST_D0] = d0; st[ST_A0] = a0; }
         prefix = d0 << DSHIFT0; pmask = DMASK0 << DSHIFT0;
     } else if (PASS == 2) {
         const uint32_t d0 = st[ST_D0], a0 = st[ST_A0];
         uint32_t d1, a1;
         find_digit(sh, hist + SEL_BINS, 2048, want - a0, d1, a1);
-        if (slice == 0 && threadIdx.x == 0) { st[ST_D1] = d1; st[ST_A1] = a1; }
+        if (first) { st[ST_D1] = d1; st[ST_A1] = a1; }
         prefix = (d0 << DSHIFT0) | (d1 << DSHIFT1);
         pmask = (DMASK0 << DSHIFT0) | (DMASK1 << DSHIFT1);
     }
@@ -237,8 +242,8 @@ __global__ __launch_bounds__(SEL_THREADS) void select_hist_kernel(SelArgs A)
     for (int j = 0; j < 8; ++j) {
         const uint32_t key = STAGE == 0 ? order_key(w[j]) : w[j];
         const bool on = (i0 + j < A.n_rank) && key != SEL_TAKEN && (key & pmask) == prefix;
-        if (STAGE == 1 && PASS >= 1) {
-            // stage 2: entries that beat the threshold at the digit this kernel has just decided (and agree with it
+        if (COUNT && PASS >= 1) {
+            // entries that beat the threshold at the digit this kernel has just decided (and agree with it
             // on the digit before): the ordered write adds these per-slice counts up instead of counting again
             constexpr uint32_t M0 = DMASK0 << DSHIFT0;
             const bool above = (i0 + j < A.n_rank) && key != SEL_TAKEN && (key & pmask) > prefix &&
@@ -261,16 +266,16 @@ __global__ __launch_bounds__(SEL_THREADS) void select_hist_kernel(SelArgs A)
         const uint32_t c = sh.hist[b];
         if (c) atomicAdd(&dst[b], c);
     }
-    if (STAGE == 0 && PASS == 2) { // the slice's own counts: the mark kernel reads its ties from here
+    if (STAGE == 0 && PASS == 2 && !COUNT) { // the slice's own counts: the mark kernel reads its ties from here
         uint32_t *mine = A.slice_hist + ((size_t)head * A.n_slices + slice) * 1024;
         for (int b = threadIdx.x; b < 1024; b += SEL_THREADS) mine[b] = sh.hist[b];
     }
-    if (STAGE == 1 && PASS >= 1) {
+    if (COUNT && PASS >= 1) {
         uint32_t *sl = A.slices + (size_t)head * 3 * A.n_slices;
         const uint32_t tot = block_sum(sh, n_above);
         if (threadIdx.x == 0) sl[PASS * A.n_slices + slice] = tot;
     }
-    if (STAGE == 1 && PASS == 2) {
+    if (COUNT && PASS == 2) {
         // the slice's digit-2 counts as suffix sums: suf[b] = entries of the slice (with the threshold's first two
         // digits) whose digit 2 is >= b; suf[1024] = 0.  The write kernel reads suf[d2 + 1] and suf[d2].
         static_assert(SEL_THREADS * 4 == 1024, "four bins per thread");
@@ -771,6 +776,7 @@ static SelArgs make_sel_args(int heads, int n, int protect, const float *attn, c
     A.alpha = (double)alpha;
     A.n = n; A.max_budget = max_budget;
     A.n_rank = n - protect;
+    A.share = 1;
     A.n_slices = (n + SEL_SLICE - 1) / SEL_SLICE;
     A.slice_hist = A.slices + (size_t)heads * 3 * A.n_slices;
     A.slice_suf = A.slice_hist + (size_t)heads * A.n_slices * 1024;
@@ -817,15 +823,17 @@ hipError_t launch_select(const Dims &d, const float *attn, const float *crit, co
 // The P entries with the largest pooled score among all Hkv * n entries of a batch item are an order statistic of one row
 // of Hkv * n keys: its threshold comes from the selection's stage-1 digits, and a head's share is the number of its
 // entries above the threshold plus those of its ties that still fit (ties go to lower entries first, i.e. to lower heads).
-// Only counts are needed, no membership and no index list: one launch where the row fits a workgroup, six otherwise
-// (clear, three digits, count, finish) -- the whole selection and a binary search in its list took ten (two rows of eight
-// heads x 20011: 39.5 us in a chain of calls, now 23).
+// Only counts are needed, no membership and no index list: one launch where the row fits a workgroup, five where heads are
+// about a slice long and more (clear, three digits, totals), six otherwise (clear, three digits, count, finish) -- the whole
+// selection and a binary search in its list took ten (two rows of eight heads x 20011: 39.5 us in a chain of calls, now 20.6).
 struct AllocArgs {
     int32_t *budget_out; // [batch][Hkv]
     uint32_t *above;     // [batch][Hkv]: entries above the threshold per head
     uint32_t *ties;      // [batch][Hkv * n] (the first Hkv words of a row are used)
     int Hkv, n, floor_each;
 };
+
+constexpr int ALLOC_MAX_HEADS = 64; // a head's workgroup also reads the slices of all heads before it
 
 template <int KPT>
 __global__ __launch_bounds__(ROW_THREADS) void allocate_row_kernel(SelArgs A, AllocArgs L)
@@ -921,7 +929,7 @@ __global__ __launch_bounds__(SEL_THREADS) void allocate_count_kernel(SelArgs A, 
 // One workgroup per row: the heads' counts become budgets.  A launch of its own, and no ticket that lets the last workgroup
 // of the count kernel do it: that needs a release by every wave that counted, and the write-backs of L2 these cost grow with
 // the launch (the whole allocation, us, with one release per workgroup / like this: 64 rows of 8 heads x 8000 110 / 56, one
-// of 8 x 131072 55 / 45, two of 8 x 20011 24.9 / 23.2).
+// of 8 x 131072 55 / 45, two of 8 x 20011 24.9 / 23.2; the line to the kernel above lies where launch_allocate draws it).
 __global__ __launch_bounds__(SEL_THREADS) void allocate_finish_kernel(SelArgs A, AllocArgs L)
 {
     __shared__ SelShared sh;
@@ -938,6 +946,39 @@ __global__ __launch_bounds__(SEL_THREADS) void allocate_finish_kernel(SelArgs A,
             L.budget_out[(size_t)row * L.Hkv + g] = min(L.n, L.floor_each + (int)(a + min(fit > before ? fit - before : 0u, t)));
         carry += total;
     }
+}
+
+// The same from counts that the histogram kernels kept per slice of every head (slices do not cross heads there): one
+// workgroup per head adds up its slices' entries above the threshold and the ties before and inside it.
+__global__ __launch_bounds__(SEL_THREADS) void allocate_total_kernel(SelArgs A, AllocArgs L)
+{
+    __shared__ SelShared sh;
+    const int g = blockIdx.x, row = blockIdx.y, ns = A.n_slices;
+    const uint32_t *st = A.state + (size_t)row * 2 * ST_WORDS;
+    const uint32_t d0_above = st[ST_A0], d1_above = st[ST_A1];
+    uint32_t d2, a2;
+    find_digit(sh, A.hist + (size_t)row * 2 * 3 * SEL_BINS + 2 * SEL_BINS, 1024, (uint32_t)A.max_budget - d0_above - d1_above, d2, a2);
+    const uint32_t fit = (uint32_t)A.max_budget - d0_above - d1_above - a2;
+    const size_t first = (size_t)row * L.Hkv; // the batch item's first head
+    uint32_t before = 0u, above = 0u, ties = 0u;
+    for (int s = threadIdx.x; s < (g + 1) * ns; s += SEL_THREADS) {
+        const size_t head = first + s / ns;
+        const int slice = s % ns;
+        const uint32_t *suf = A.slice_suf + (head * ns + slice) * 1025 + d2;
+        const uint32_t gt = suf[1], t = suf[0] - gt;
+        if (s >= g * ns) {
+            const uint32_t *sl = A.slices + head * 3 * ns + slice;
+            above += sl[ns] + sl[2 * ns] + gt;
+            ties += t;
+        } else {
+            before += t;
+        }
+    }
+    before = block_sum(sh, before);
+    above = block_sum(sh, above);
+    ties = block_sum(sh, ties);
+    if (threadIdx.x == 0)
+        L.budget_out[first + g] = min(L.n, L.floor_each + (int)(above + min(fit > before ? fit - before : 0u, ties)));
 }
 
 __global__ void allocate_floor_kernel(AllocArgs L, int heads)
@@ -970,6 +1011,22 @@ hipError_t launch_allocate(const Dims &d, const float *attn, int total, float fl
         else if (span <= 8 * ROW_THREADS) hipLaunchKernelGGL(allocate_row_kernel<8>, grid, block, 0, s, A, L);
         else if (span <= 16 * ROW_THREADS) hipLaunchKernelGGL(allocate_row_kernel<16>, grid, block, 0, s, A, L);
         else hipLaunchKernelGGL(allocate_row_kernel<24>, grid, block, 0, s, A, L);
+        return hipGetLastError();
+    }
+    // Heads of about a slice and more: slices of single heads, whose counts the histogram kernels keep, and five launches;
+    // shorter ones share slices and are counted in a launch of their own.  us, launch of its own / kept
+    // counts: 16 heads x 20011 in two rows 23.3 / 20.6, 8 x 131072 39.3 / 33.1, 64 rows of 8 x 8000 47.4 / 42.0, 24 x 1100 19.8 /
+    // 19.5, 40 x 5000 22.4 / 21.7, 256 x 1024 22.9 / 24.3.
+    if (d.n >= SEL_SLICE / 2 && d.Hkv <= ALLOC_MAX_HEADS) {
+        SelArgs S = make_sel_args(d.batch * d.Hkv, d.n, 0, attn, attn, nullptr, 1.0f, P, nullptr, nullptr, keys2, scratch);
+        S.share = d.Hkv;
+        const size_t words = (size_t)d.batch * 2 * 3 * SEL_BINS;
+        const dim3 slices(S.n_slices, d.batch * d.Hkv), threads(SEL_THREADS);
+        hipLaunchKernelGGL(select_zero_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, scratch, words);
+        hipLaunchKernelGGL((select_hist_kernel<0, 0, true>), slices, threads, 0, s, S);
+        hipLaunchKernelGGL((select_hist_kernel<0, 1, true>), slices, threads, 0, s, S);
+        hipLaunchKernelGGL((select_hist_kernel<0, 2, true>), slices, threads, 0, s, S);
+        hipLaunchKernelGGL(allocate_total_kernel, dim3(d.Hkv, d.batch), threads, 0, s, S, L);
         return hipGetLastError();
     }
     const size_t hist_words = (size_t)d.batch * (2 * 3 * SEL_BINS + 2 * ST_WORDS);

@@ -609,3 +609,20 @@ def test_l2_magnitudes_of_long_ranges(P, n):
         assert (got[bi, h].double() / ref - 1).abs().max() <= 2e-5, (bi, h)
     for _ in range(3):
         assert torch.equal(torch.from_numpy(score(P, cfg_desc(P, cfg, norm=2), q, k, v, w)[2]).cuda(), got)
+
+
+@pytest.mark.parametrize("b,Hkv,n", [(1, 30, 1023), (2, 30, 1024), (1, 64, 1025), (1, 65, 1025), (3, 13, 2047), (2, 13, 2048), (1, 13, 2049),
+                                     (2, 3, 20011)])
+def test_allocate_where_slices_belong_to_heads(P, b, Hkv, n):
+    """Around the lengths and head counts from which the histogram kernels keep the heads' counts; rows that start off a
+    16-byte boundary, ties across heads and slices, a head that gets everything, pools of one slot and of all."""
+    from oracle import cpu_oracle as O
+    from test_gpu_parity import run_allocate
+    r = np.random.Generator(np.random.PCG64(n + Hkv))
+    tied = r.integers(0, 3, (b, Hkv, n)).astype(np.float32)
+    one = r.random((b, Hkv, n)).astype(np.float32)
+    one[:, Hkv // 2] += 2
+    for attn in (tied, one, r.lognormal(0, 2, (b, Hkv, n)).astype(np.float32)):
+        for total, floor_frac in ((1, 0.0), (n, 0.0), (Hkv * n // 3, 0.25), (Hkv * n - 1, 0.0), (Hkv * n, 0.5)):
+            got = run_allocate(P, attn, total, floor_frac)
+            assert np.array_equal(got, O.allocate(attn.astype(np.float64), total, np.float32(floor_frac))), (total, floor_frac)
