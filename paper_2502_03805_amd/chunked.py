@@ -53,7 +53,8 @@ def chunked_prefill_evict(make_desc: Callable[[int], "B.LayerDesc"], q_windows: 
             bud = torch.full((b, Hkv), budget, dtype=torch.int32, device=k_all.device)
         B.criticalkv_score(desc, q_win, k_all, v_all, w_o, attn, crit, None, workspace=ws, stream=stream)
         B.criticalkv_select(desc, attn, crit, bud, alpha, budget, idx, count, workspace=ws, stream=stream)
-        appended = chunk is not None and _appendable(k_all, chunk[1]) and _appendable(v_all, chunk[2])
+        appended = (chunk is not None and chunk[1].shape == chunk[2].shape and _appendable(k_all, chunk[1]) and
+                    _appendable(v_all, chunk[2]))
         rows = budget + (chunk[1].shape[2] if appended else 0)
         k_out = torch.empty((b, Hkv, rows, dh), dtype=k_all.dtype, device=k_all.device)
         v_out = torch.empty_like(k_out)
