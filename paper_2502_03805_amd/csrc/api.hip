@@ -241,7 +241,7 @@ static int score_attention(const ScorePlan &p, const ckv_layer_desc *desc, const
         : p.wave_a ? launch_attn_stats_wave(d, q_win, k, p.part, p.chunks, s)
                    : launch_attn_stats_generic(d, desc->dtype, q_win, k, p.part, p.chunks, s);
     if (e != hipSuccess) return CKV_E_HIP;
-    const bool merges = p.tile_a && attn_mfma_merges(d);
+    const bool merges = (p.tile_a && attn_mfma_merges(d)) || (p.wave_a && attn_wave_merges(d));
     if (!merges)
         e = (p.tile_a || p.wave_a) ? launch_attn_stats_reduce_log2(d, p.part, p.chunks, p.stats, s)
                                    : launch_attn_stats_reduce(d, p.part, p.chunks, p.stats, s);
@@ -249,7 +249,7 @@ static int score_attention(const ScorePlan &p, const ckv_layer_desc *desc, const
     mark(ev, 2 * CKV_STAGE_ATTN_STATS + 1, s);
     mark(ev, 2 * CKV_STAGE_ATTN_COLSUM, s);
     e = p.tile_a ? launch_attn_colsum_mfma(d, q_win, k, merges ? p.part : p.stats, p.a_raw, s)
-        : p.wave_a ? launch_attn_colsum_wave(d, q_win, k, p.stats, p.a_raw, s)
+        : p.wave_a ? launch_attn_colsum_wave(d, q_win, k, merges ? p.part : p.stats, p.a_raw, s)
                    : launch_attn_colsum_generic(d, desc->dtype, q_win, k, p.stats, p.a_raw, s);
     if (e != hipSuccess) return CKV_E_HIP;
     mark(ev, 2 * CKV_STAGE_ATTN_COLSUM + 1, s);

@@ -71,6 +71,7 @@ hipError_t launch_attn_colsum_generic(const Dims &d, int dtype, const void *q, c
                                       float *a_raw, hipStream_t s);
 // (attn_mfma_merges: pass 2 takes the chunks' pairs in `part` instead of the reduced rows)
 bool attn_mfma_merges(const Dims &d);
+bool attn_wave_merges(const Dims &d);
 hipError_t launch_attn_stats_mfma(const Dims &d, const void *q, const void *k, float *part, hipStream_t s);
 // matrix-core path: partials are in the log2 domain; per row E = log2(sum 2^t) (+ log2 W for the mean)
 hipError_t launch_attn_stats_reduce_log2(const Dims &d, const float *part, int chunks, float *stats, hipStream_t s);

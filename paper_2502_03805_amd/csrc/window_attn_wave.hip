@@ -54,6 +54,8 @@ struct AttnArgs {
     int chunks;   // workgroups along the keys
     int pairs;    // batch * kv heads * chunks
     int causal;   // window row w sees keys <= n - W + w only
+    int merge;    // the ranges' pairs lie [head][range][row] and pass 2 merges them, else [head][row][range] for a launch between
+    float post;   // log2 W for the window mean, 0 for the sum
     float c;      // scale * log2(e)
     int64_t ks0, ks1, ks2;
 };
@@ -254,9 +256,9 @@ __global__ __launch_bounds__(64 * AM_WAVES, 2) void attn_stats_wave_kernel(AttnA
         const int head = J.head0 + rb / A.qbs;
         const int w = (rb % A.qbs) * 32 + l32;
         if (rb < J.nrb && half == 0 && w < A.W) {
-            float *dst = part + ((((size_t)J.bi * A.H + head) * A.W + w) * (size_t)A.ranges + J.range) * 2;
-            dst[0] = mt;
-            dst[1] = lt;
+            const size_t bh = (size_t)J.bi * A.H + head;
+            const size_t at = A.merge ? (bh * A.ranges + J.range) * A.W + w : (bh * A.W + w) * A.ranges + J.range;
+            reinterpret_cast<float2 *>(part)[at] = make_float2(mt, lt);
         }
     }
 }
@@ -289,7 +291,30 @@ __global__ __launch_bounds__(64 * AM_WAVES, 2) void attn_colsum_wave_kernel(Attn
     // table entry (rb, hf, j) belongs to window row 8*(j/4) + 4*hf + j%4 of the block; rows past W get -inf
     // (weight 0).  Lane t < 32 writes entry (hf = t / 16, j = t % 16) of every row block.
     const float inv_c = 1.0f / A.c;
-    if (lane < 32) {
+    if (A.merge) { // (uniform) lane (row l32, half) takes the ranges of its half's parity, then the two halves merge
+#pragma unroll
+        for (int rb = 0; rb < QB; ++rb) {
+            const int rbc = min(rb, J.nrb - 1), w = (rbc % A.qbs) * 32 + l32;
+            const float2 *pairs = reinterpret_cast<const float2 *>(stats) +
+                                  ((size_t)J.bi * A.H + J.head0 + rbc / A.qbs) * A.ranges * A.W + min(w, A.W - 1);
+            float m = AM_NEG, l = 0.f;
+            for (int r0 = half; r0 < A.ranges; r0 += 16) {
+                float2 x[8]; // requested together; ranges past the last repeat it with weight 0
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[u] = pairs[(size_t)min(r0 + 2 * u, A.ranges - 1) * A.W];
+                float mn = m;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) mn = fmaxf(mn, x[u].x);
+                l *= __builtin_amdgcn_exp2f(m - mn);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) l += (r0 + 2 * u < A.ranges ? x[u].y : 0.f) * __builtin_amdgcn_exp2f(x[u].x - mn);
+                m = mn;
+            }
+            const float mo = __shfl_xor(m, 32), lo = __shfl_xor(l, 32), mt = fmaxf(m, mo);
+            l = l * __builtin_amdgcn_exp2f(m - mt) + lo * __builtin_amdgcn_exp2f(mo - mt);
+            if (half == 0) etab[wave][rb][(l32 >> 2) & 1][(l32 >> 3) * 4 + (l32 & 3)] = w < A.W ? -(mt + log2f(l) + A.post) * inv_c : -INFINITY;
+        }
+    } else if (lane < 32) {
         const int hf = lane >> 4, j = lane & 15;
 #pragma unroll
         for (int rb = 0; rb < QB; ++rb) {
@@ -393,6 +418,12 @@ static int attn_kpw(const Dims &d, int groups, int row_blocks, double *cost)
     return best;
 }
 
+// Launches of few ranges: pass 2 merges the rows' pairs itself, under its first key blocks' latency, instead of a launch
+// between.  Both sweeps and the combine (d_h 64: the score call), us, launch / merged: d_h 64, 4 heads per group, W 32: 1024 tokens 27.1 /
+// 24.8, 3000 38.1 / 36.3, 4 x 1024 44.5 / 41.2; 5 heads, W 64: 1024 23.8 / 21.6, 4096 28.1 / 26.6; with 33 to 64 ranges the same
+// within 1 % (8192: 36.7 / 37.5).
+constexpr int AM_MERGE_RANGES = 32;
+
 static AttnArgs make_args(const Dims &d, const void *q, const void *k)
 {
     AttnArgs A;
@@ -418,10 +449,13 @@ static AttnArgs make_args(const Dims &d, const void *q, const void *k)
     A.ranges = (d.n + kpw - 1) / kpw;
     A.chunks = (A.ranges + AM_WAVES - 1) / AM_WAVES;
     A.pairs = d.batch * d.Hkv * A.chunks;
+    A.merge = A.ranges <= AM_MERGE_RANGES;
+    A.post = d.window_sum ? 0.0f : log2f((float)d.W);
     A.c = d.scale * AM_LOG2E;
     A.ks0 = d.ks[0]; A.ks1 = d.ks[1]; A.ks2 = d.ks[2];
     return A;
 }
+bool attn_wave_merges(const Dims &d) { return make_args(d, nullptr, nullptr).merge; }
 int wave_attn_chunks(const Dims &d) { return make_args(d, nullptr, nullptr).ranges; }
 
 template <int DH>

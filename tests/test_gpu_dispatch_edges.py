@@ -626,3 +626,29 @@ def test_allocate_where_slices_belong_to_heads(P, b, Hkv, n):
         for total, floor_frac in ((1, 0.0), (n, 0.0), (Hkv * n // 3, 0.25), (Hkv * n - 1, 0.0), (Hkv * n, 0.5)):
             got = run_allocate(P, attn, total, floor_frac)
             assert np.array_equal(got, O.allocate(attn.astype(np.float64), total, np.float32(floor_frac))), (total, floor_frac)
+
+
+@pytest.mark.parametrize("dh,H,Hkv,W,b,ns", [
+    (64, 32, 8, 32, 1, (33, 1024, 3000, 4096, 4097, 4500)), (64, 6, 2, 40, 2, (100, 2000)), (128, 40, 8, 64, 1, (1024, 4096, 4200, 8192)),
+    (128, 6, 1, 128, 1, (700,)), (64, 3, 3, 5, 1, (9000,)),
+])
+def test_short_contexts_of_the_wave_private_sweeps_against_float64(P, dh, H, Hkv, W, b, ns):
+    """Around 32 ranges of keys, several heads per wave and windows of several row blocks among them: 4e-6 by the 2-norm, as for
+    the shared-tile sweeps."""
+    import torch
+    G = H // Hkv
+    for n in ns:
+        W_n = min(W, n)
+        cfg = CONFIGS["llama32k"].with_(n_q_heads=H, n_kv_heads=Hkv, head_dim=dh, d_model=512, n_ctx=n, window=W_n, batch=b, pool_kernel=1)
+        g = torch.Generator(device="cuda").manual_seed(n)
+        q, k = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((b, H, W_n, dh), (b, Hkv, n, dh)))
+        for causal in (0, P.CKV_CAUSAL_TAIL):
+            desc = cfg_desc(P, cfg, flags=causal | P.CKV_ATTN_ONLY)
+            ws = torch.empty(P.workspace_bytes(desc, 1), dtype=torch.uint8, device="cuda")
+            attn, crit = (torch.full((b, Hkv, n), float("nan"), device="cuda") for _ in range(2))
+            P.criticalkv_score(desc, q, k, None, None, attn, crit, None, workspace=ws)
+            s = torch.einsum("bgrwd,bgnd->bgrwn", q.double().view(b, Hkv, G, W_n, dh), k.double()) / dh ** 0.5
+            if causal:
+                s.masked_fill_(torch.arange(n, device="cuda") > n - W_n + torch.arange(W_n, device="cuda")[:, None], -np.inf)
+            ref = s.softmax(-1).mean((2, 3))
+            assert (attn.double() - ref).norm() <= 4e-6 * ref.norm(), (n, causal)
