@@ -2,8 +2,8 @@
 
 After each chunk of the prompt the cache kept so far, followed by the chunk's new K/V rows, is scored with
 the chunk's last W queries (causal inside the window, the window's own tokens protected), cut down to the
-budget and compacted; the compacted cache is what the next chunk sees.  Only orchestration and buffer
-concatenation happen here; every step of each pass runs in the library's kernels.
+budget and compacted; the compacted cache, which the gather writes with the next chunk's rows behind it, is what the
+next pass sees.  Only orchestration happens here; every step of each pass runs in the library's kernels.
 """
 from __future__ import annotations
 

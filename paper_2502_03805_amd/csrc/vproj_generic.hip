@@ -3,7 +3,7 @@
 //
 // Serves what the matrix-core kernels do not cover (bf16 with the 2-norm at d_h 64 or a d_model that 512 does not divide, with
 // the 1-norm a d_model that a tile of columns does not divide, CKV_NO_MFMA, fp32 layers whose workspace has no room for the
-// three-part copy of W_O).  One thread owns
+// two-part copy of W_O).  One thread owns
 // one token row (kept in registers); the head's W_O slice is streamed through LDS in tiles
 // of TC output columns and read as broadcasts.  The n x d_model products are reduced on the
 // fly and never stored.

@@ -4,10 +4,12 @@
 // An fp32 number is the sum of two f16 numbers once a power of two has brought it into f16's range:
 //   x * s = hi + lo,  hi = f16(x * s), lo = f16(x * s - hi), the difference exact.
 // A token's row of V and a tile of W_O (d_h rows by 32 columns of a head) have a scale each that takes their largest
-// entry to [2^14, 2^15).  lo rounds by at most 2^-24 of x (rms 2^-26), and by 2^-40 of the row's or tile's largest entry
-// where it is subnormal (the instruction takes subnormal operands as they are).  Of the four products of v * w the one that
-// is left out, lo * lo, is at most 2^-24 of it (rms 2^-27); the three others are exact in the MFMA's fp32 accumulators and
-// are added smallest first.  Nothing is held in 16 bits that was held in 32: the two parts together are the number.
+// entry to [2^14, 2^15).  The two parts hold 23 of fp32's 24 bits at least: a quarter of the values lose their last one
+// (2^-23 of x; rms 2^-24), and a subnormal lo rounds by 2^-40 of the row's or tile's largest entry (the instruction takes
+// subnormal operands as they are).  Of the four products of v * w the one that is left out, lo * lo, is at most 2^-22 of it
+// (rms 2^-24.6); the three others are exact in the MFMA's fp32 accumulators and are added smallest first.  In all 9e-8 of a
+// product (rms), random in sign: over the d_model columns of a magnitude that is far below the rounding of its sums, and the
+// last of these, which were most of the error, are in 64 bits.
 //
 //   split     W_O once per call into [head][d_model][2 parts][d_h] (and from the canonical layout to output-major), with
 //             a factor per tile that undoes its scale
