@@ -40,6 +40,7 @@ static int resolve(const ckv_layer_desc *desc, Dims *out)
     d.batch = c.batch; d.H = c.n_q_heads; d.Hkv = c.n_kv_heads; d.G = d.H / d.Hkv;
     d.dh = c.head_dim; d.dm = c.d_model; d.n = c.n_ctx; d.W = c.window; d.pool_k = c.pool_kernel;
     d.window_sum = c.window_reduce == CKV_SUM;
+    d.attn_only = (c.flags & CKV_ATTN_ONLY) != 0;
     d.norm = c.norm;
     d.causal = (c.flags & CKV_CAUSAL_TAIL) ? 1 : 0;
     d.protect = (c.flags & CKV_PROTECT_WINDOW) ? c.window : 0;
@@ -66,6 +67,9 @@ Workspace carve_workspace(const Dims &d, int dtype, int max_budget)
     size_t off = 0;
     const size_t per_head = (size_t)d.batch * d.H * d.n;
     w.max_chunks = (d.n + ATTN_MIN_CHUNK - 1) / ATTN_MIN_CHUNK;
+    // (grows with n: scratch of the longest context serves the shorter ones)
+    if (dtype == CKV_BF16)
+        w.max_chunks = std::max(w.max_chunks, std::min((d.n + ATTN_SHORT_CHUNK - 1) / ATTN_SHORT_CHUNK, ATTN_SHORT_WGS));
     w.a_raw = off; off = align256(off + per_head * 4);
     w.vnorm = off; off = align256(off + per_head * 4);
     w.stats_part = off; off = align256(off + (size_t)d.batch * d.H * d.W * w.max_chunks * 2 * 4);

@@ -26,6 +26,7 @@ struct Dims {
     int batch, H, Hkv, G, dh, dm, n, W, pool_k;
     int window_sum;
     int norm; // CKV_NORM_L1 or CKV_NORM_L2
+    int attn_only; // no magnitudes in this call
     int causal;  // window row w sees keys <= n - W + w only
     int protect; // trailing entries the selection keeps as they are (0 or W)
     float scale, eps;
@@ -50,7 +51,9 @@ struct Workspace {
     int max_chunks;    // capacity of stats_part per window row
 };
 
-constexpr int ATTN_MIN_CHUNK = 128; // fewest keys any attention kernel gives one workgroup (sizes stats_part)
+constexpr int ATTN_MIN_CHUNK = 128; // fewest keys an attention kernel gives one workgroup (sizes stats_part), and of those
+constexpr int ATTN_SHORT_CHUNK = 64; // bf16 launches that have no more workgroups than the chip has CUs
+constexpr int ATTN_SHORT_WGS = 256;
 int generic_attn_chunks(const Dims &d);
 int mfma_attn_chunks(const Dims &d);
 bool attn_mfma_supported(const Dims &d);  // shapes the matrix-core attention kernels cover (shared key tiles)
@@ -91,7 +94,8 @@ hipError_t launch_vproj_generic(const Dims &d, int dtype, const void *v, const v
                                 hipStream_t s);
 hipError_t launch_vproj_mfma(const Dims &d, const void *v, const void *w_t, float *vnorm, hipStream_t s);
 // the projection and pass 2 of the shared-tile attention in one launch (short contexts)
-bool vproj_colsum_taken(const Dims &d);
+bool vproj_colsum_room(const Dims &d);  // the projection leaves room for it
+bool vproj_colsum_taken(const Dims &d); // ... and pass 2 merges the rows itself
 hipError_t launch_vproj_colsum(const Dims &d, const void *q, const void *k, const void *v, const void *w_t, const float *part,
                                float *a_raw, float *vnorm, hipStream_t s);
 // Row blocks per wave of a projection launch: of `choices`, the one whose rounds of workgroups cost least (the first of

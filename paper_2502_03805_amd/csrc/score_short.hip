@@ -28,13 +28,14 @@ __global__ __launch_bounds__(VM_THREADS, 2) void vproj_colsum_kernel(VprojArgs P
 }
 
 // One workgroup of the projection per CU at most: the other half of the chip's slots is the sweep's.
-bool vproj_colsum_taken(const Dims &d)
+bool vproj_colsum_room(const Dims &d)
 {
-    if (d.norm != CKV_NORM_L1 || d.dh != AM_DH || d.W > 32 || d.G > VM_WAVES || !attn_mfma_merges(d)) return false;
+    if (d.attn_only || d.norm != CKV_NORM_L1 || d.dh != AM_DH || d.W > 32 || d.G > VM_WAVES || !vproj_mfma_supported(d)) return false;
     unsigned wgs;
     (void)vproj_mfma_args(d, vproj_mfma_row_blocks(d), nullptr, nullptr, nullptr, &wgs);
     return wgs <= 256;
 }
+bool vproj_colsum_taken(const Dims &d) { return vproj_colsum_room(d) && attn_mfma_merges(d); }
 
 hipError_t launch_vproj_colsum(const Dims &d, const void *q, const void *k, const void *v, const void *w_t, const float *part,
                                float *a_raw, float *vnorm, hipStream_t s)

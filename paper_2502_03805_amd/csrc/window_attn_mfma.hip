@@ -141,22 +141,34 @@ bool attn_mfma_supported(const Dims &d)
 // Keys per workgroup.  Longer chunks spread the fixed cost of a workgroup (its query fragments, the first tile's
 // latency) over more keys; measured, 1024 keys win as long as the launch still has two workgroups per CU
 // (Qwen 128K: both sweeps 20 % faster than with 256), 512 at Llama 32K, 256 below.
+// Short contexts leave CUs idle instead, and a sweep is as long as one workgroup's chain of tiles: 128 or 64 keys (one tile)
+// while that makes no more workgroups than there are CUs.  Attention-only call, 32 heads over 8, us, 256 keys / this: 200
+// tokens 18.4 / 13.0, 1024 18.9 / 13.2, 2048 18.9 / 14.0, 3072 19.2 / 15.9, 4096 19.3 / 16.2; 4 over 1, 16384 tokens 20.2 / 16.6.
+// With a second workgroup on a CU there is nothing to gain (6000 tokens, 128 keys: 20.0 / 20.4).
 static int attn_chunk_keys(const Dims &d)
 {
     const int qbs = (d.W + 31) / 32, wpw = (AM_MAX_WAVES / qbs) * qbs;
     const long long per_chunk_row = (long long)d.batch * d.Hkv * ((d.G * qbs + wpw - 1) / wpw);
-    for (int keys = 1024; keys > AM_CHUNK_MIN; keys >>= 1)
-        if (per_chunk_row * ((d.n + keys - 1) / keys) >= 512) return keys;
-    return AM_CHUNK_MIN;
+    const auto wgs = [&](int keys) { return per_chunk_row * ((d.n + keys - 1) / keys); };
+    int keys = 1024;
+    while (keys > 256 && wgs(keys) < 512) keys >>= 1;
+    if (keys == 256)
+        while (keys > ATTN_SHORT_CHUNK && wgs(keys / 2) <= ATTN_SHORT_WGS) keys >>= 1;
+    return keys;
 }
 int mfma_attn_chunks(const Dims &d) { const int keys = attn_chunk_keys(d); return (d.n + keys - 1) / keys; }
 
 // Short contexts: the waves of pass 2 merge the chunks' pairs themselves (a few KiB out of L2 under the first key tile's
 // latency) instead of a launch of their own between the sweeps.  Attention-only call, 32 heads over 8, us,
 // launch between / merged: 12 chunks 20.8 / 18.5, 32 22.2 / 20.0, 47 25.7 / 24.7, 64 27.7 / 27.4 (256 keys each), 41.0 / 40.5 (512),
-// 94 36.0 / 37.1, 128 115.5 / 120.6 (1024): up to 64.
+// 94 36.0 / 37.1, 128 115.5 / 120.6 (1024): up to 64.  The short chunks of few heads make more of them (4 heads over 1: 110 chunks
+// 15.7 / 16.1, 256 16.6 / 20.2), merged all the same where that puts pass 2 beside the projection (157 chunks 35.8 / 29.7, 256
+// 41.7 / 36.6, and 20000 tokens, 157 of 128 keys, 48.6 / 42.1).
 constexpr int AM_MERGE_CHUNKS = 64;
-bool attn_mfma_merges(const Dims &d) { return mfma_attn_chunks(d) <= AM_MERGE_CHUNKS; }
+bool attn_mfma_merges(const Dims &d)
+{
+    return mfma_attn_chunks(d) <= AM_MERGE_CHUNKS || (attn_chunk_keys(d) < 256 && vproj_colsum_room(d));
+}
 
 AttnArgs attn_mfma_args(const Dims &d, const void *q, const void *k)
 {

@@ -14,7 +14,6 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 constexpr int AM_DH = 128;
 constexpr int AM_TILE_KEYS = 64;
 constexpr int AM_TILE_BYTES = AM_TILE_KEYS * AM_DH * 2; // 16 KiB
-constexpr int AM_CHUNK_MIN = 256;                       // fewest keys per workgroup (the host picks 256, 512 or 1024)
 constexpr int AM_MAX_WAVES = 16;                       // pass 1: waves per workgroup, one per (head, 32-row block)
 constexpr int AM_COLSUM_WAVES = 8;                     // pass 2: waves per workgroup, one per head
 constexpr float AM_LOG2E = 1.4426950408889634f;

@@ -509,6 +509,9 @@ def test_chunked_prefill_with_chunks_the_gather_cannot_append(P):
     (4, 8, 32, 1, 1, (100, 511, 600, 1025, 1601, 2100, 3072, 3500, 3700)), # every row-block count; two workgroups per CU
     (1, 2, 7, 2, 1, (40, 257, 4100)), (3, 2, 20, 1, 1, (1, 300, 2049)), (2, 1, 33, 1, 1, (300,)), (4, 1, 32, 1, 2, (500,)),
     (4, 2, 32, 1, None, (16383, 16384, 16385)), (2, 2, 64, 1, None, (5000,)), # 64 and 65 chunks
+    # ranges of 64, 128 and 256 keys, either side of each line; ranges that rows of the window do not see at all
+    (4, 8, 32, 1, None, (64, 65, 129, 2048, 2049, 4096, 4097)), (1, 1, 96, 1, None, (97, 160, 192, 1000)), (2, 4, 64, 2, 1, (66, 2049)),
+    (4, 1, 32, 1, 1, (4096, 4097, 16384, 16385, 32768, 32769)), (4, 1, 32, 1, None, (4096, 4097, 16384, 16385, 32768, 32769)),
 ])
 def test_short_contexts_against_float64(P, G, Hkv, W, b, norm, ns):
     """fp32 softmax sums of bf16 products (d_h exact terms) and exponentials of an ulp each: 4e-6 of the result by the 2-norm;
