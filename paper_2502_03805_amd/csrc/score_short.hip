@@ -6,7 +6,8 @@
 // tiles there.  By itself the sweep is a launch of 7 us that fills an eighth of the chip.  Score call, 32 heads over 8,
 // d_model 4096, causal, us, apart and with a launch that reduces the rows / together and merged: 600 tokens 48.1 / 38.3, 1024
 // 51.8 / 43.2, 2048 69.3 / 60.4, 3072 89.0 / 79.4, 3500 96.7 / 88.2; from two workgroups per CU on there is no room beside the
-// projection and nothing to gain (3700 tokens: 105.0 / 103.4, by the merge alone).
+// projection and nothing to gain (3700 tokens: 105.0 / 103.4, by the merge alone).  (256 keys per workgroup of the
+// sweeps; with the 64 or 128 of short contexts, together: 600 tokens 37.0, 1024 41.0, 2048 57.7, 3072 78.3.)
 //
 // fp32 layers (below): the split of W_O beside the first sweep, and the project kernel beside the second one.
 #include "vproj_mfma.hpp"
